@@ -194,6 +194,11 @@ hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream)
 {
     if (a.M == 0 || a.N == 0)
         return hipSuccess;
+    if (skinny_gemm_preferred(a.M, a.N, a.K, 0)) {
+        const SkinnyGemmArgs few = {a.a_codes, a.a_scales, a.b_codes, a.b_scales, a.M, a.N,
+                                    a.K, 0, a.y, a.ld_y, a.acc_out};
+        return launch_skinny_gemm(few, stream);
+    }
     const hipError_t attr_err = prepare_fp4_gemm_kernels();
     if (attr_err != hipSuccess)
         return attr_err;

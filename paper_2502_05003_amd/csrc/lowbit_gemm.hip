@@ -836,6 +836,11 @@ hipError_t launch_lowbit_gemm(const GemmArgs &args, hipStream_t stream)
 {
     if (args.M == 0 || args.N == 0)
         return hipSuccess;
+    if (skinny_gemm_preferred(args.M, args.N, args.K, args.bits)) {
+        const SkinnyGemmArgs few = {args.a_codes, args.a_scales, args.b_codes, args.b_scales, args.M, args.N,
+                                    args.K, args.bits, args.y, args.ld_y, args.acc_out};
+        return launch_skinny_gemm(few, stream);
+    }
     GemmArgs a = args;
     // 1 and 2 bits with scratch from the caller: re-code, then the 4-bit tile kernels.  Without
     // scratch the general kernel below multiplies the narrow containers directly (slower).
@@ -878,7 +883,7 @@ hipError_t launch_lowbit_gemm(const GemmArgs &args, hipStream_t stream)
     }
     // fewer 256 x 128 tiles than three quarters of the chip's slots (two per CU): 128 x 128 tiles
     const int64_t big_tiles = ((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
-    if ((a.bits == 4 || a.bits == 3) && (a.K % TK) == 0 && a.M >= 128 && a.N >= 128 && big_tiles < 384) {
+    if ((a.bits == 4 || a.bits == 3) && (a.K % TK) == 0 && a.M > 64 && a.N >= 128 && big_tiles < 384) {
         const int tiles_m = (int)((a.M + STM - 1) / STM), tiles_n = (int)((a.N + STN - 1) / STN);
         const int per_xcd = (tiles_m * tiles_n + 7) / 8;
         const hipError_t err = prepare_lowbit_gemm_kernels();

@@ -71,6 +71,23 @@ struct Fp4GemmArgs {
 
 hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream);
 
+// The forward product for few activation rows, on either grid.
+struct SkinnyGemmArgs {
+    const uint8_t *a_codes;
+    const float *a_scales;
+    const uint8_t *b_codes;
+    const float *b_scales;
+    int64_t M, N, K;
+    int grid;         // 1 .. 4: bits of the Eq. 1 grid; 0: E2M1
+    void *y;          // bf16, may be null
+    int64_t ld_y;
+    void *acc_out;    // int32 (E2M1: fp32), may be null
+};
+
+// grid as in SkinnyGemmArgs
+bool skinny_gemm_preferred(int64_t M, int64_t N, int64_t K, int grid);
+hipError_t launch_skinny_gemm(const SkinnyGemmArgs &a, hipStream_t stream);
+
 struct BackwardArgs {
     const void *g;
     quest_dtype g_dtype;

@@ -1,0 +1,349 @@
+// The forward product for few activation rows (decoding, short prompts): y = xhat_h what_h^T on packed
+// codes (Algorithm 1, last step), integer grid and E2M1 grid.
+//
+// With a few dozen rows the product is a pass over the packed weights (5.8 MB for 5632 x 2048, 1 us
+// at the memory's rate) and everything else is latency, so the work is cut for as many loads in
+// flight as possible and no staging: a workgroup owns 16 NT weight rows and all of its waves split the
+// contraction between them in units of 128 elements, wave w taking units w, w + W, ..; a lane loads
+// its share of a unit (32 codes of one row, 16 bytes at 4 bits) straight into registers, where it is
+// the matrix instruction's operand after widening, and the waves' partial sums meet once in LDS.
+// The sums are exact (int32, or fp32 multiples of 1/4 below 2^24), so their order does not matter.
+//
+// Every container width is read as it is (no re-coding pass for 1 and 2 bits), and any K that is a
+// multiple of 64 is taken: the last half unit is one matrix instruction on half as many codes.
+#include "gemm_tile.h"
+#include "quest_internal.h"
+
+namespace quest {
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int kUnit = 128;   // contraction elements per unit: 32 codes per lane, lanes l, l + 16, l + 32, l + 48 share a row
+
+// GRID: 1, 2, 3, 4 = bits of the Eq. 1 grid, 0 = E2M1.
+template <int GRID>
+struct Codes {
+    static constexpr int kContainer = GRID == 0 || GRID == 3 ? 4 : GRID;   // bits
+    static constexpr int kWords = kContainer;                              // dwords of 32 codes
+    // The integer codes become signed bytes 2^shift u: the code at the top of its byte, the top bit
+    // inverted (offset binary to two's complement), the bit below the code set.  Products carry
+    // 2^(2 shift); 2^(2 shift) (L - 1)^2 K stays below 2^31 for K <= 65536.
+    static constexpr int kCarry = GRID == 0 ? 0 : 2 * (7 - GRID);
+    uint32_t w[kWords];
+
+    __device__ __forceinline__ void load(const uint8_t *p)
+    {
+        if constexpr (kWords == 4) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(p);
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        } else if constexpr (kWords == 2) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(p);
+            w[0] = v.x; w[1] = v.y;
+        } else {
+            w[0] = *reinterpret_cast<const uint32_t *>(p);
+        }
+    }
+    // sixteen codes; what is above them in the registers is zero
+    __device__ __forceinline__ void load_half(const uint8_t *p)
+    {
+        if constexpr (kWords == 4) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(p);
+            w[0] = v.x; w[1] = v.y; w[2] = 0; w[3] = 0;
+        } else if constexpr (kWords == 2) {
+            w[0] = *reinterpret_cast<const uint32_t *>(p);
+            w[1] = 0;
+        } else {
+            w[0] = *reinterpret_cast<const uint16_t *>(p);
+        }
+    }
+    // The 32 codes as two operands of sixteen signed bytes.  The order of the elements is permuted
+    // the same way in both factors of the product.
+    __device__ __forceinline__ void widen(v4i (&op)[2]) const
+    {
+        static_assert(GRID != 0, "E2M1 codes are an operand as they are");
+        constexpr uint32_t top = (0xffu << (8 - GRID)) & 0xffu;
+        constexpr uint32_t field = top * 0x01010101u;
+        constexpr uint32_t flip = (0x80u | (0x80u >> GRID)) * 0x01010101u;
+        constexpr int kPerWord = 8 / kContainer;   // dwords of bytes per dword of codes
+        int d[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int position = (i % kPerWord) * kContainer;       // the code's lowest bit in its byte
+            const int up = 8 - GRID - position;
+            const uint32_t v = w[i / kPerWord];
+            d[i] = (int)(((up >= 0 ? v << up : v >> -up) & field) ^ flip);
+        }
+        op[0] = v4i{d[0], d[1], d[2], d[3]};
+        op[1] = v4i{d[4], d[5], d[6], d[7]};
+    }
+};
+
+template <bool FLOAT>
+struct Sum {
+    typedef v4i type;
+};
+template <>
+struct Sum<true> {
+    typedef v4f type;
+};
+
+/*
+ * blockIdx.x: weight rows 16 NT blockIdx.x .., blockIdx.y: activation rows 16 MT blockIdx.y ..
+ * blockDim.x / 64 waves.  Dynamic LDS: waves * MT * NT * 1 KiB.
+ * The weights are the row operand, so a lane's four sums are four consecutive outputs of one row.
+ */
+template <int GRID, int MT, int NT, int BATCH>
+__global__ __launch_bounds__(512) void skinny_gemm_kernel(
+    const uint8_t *__restrict__ a_codes, const float *__restrict__ a_scales, const uint8_t *__restrict__ b_codes,
+    const float *__restrict__ b_scales, int M, int N, int K, uint16_t *__restrict__ y, int64_t ld_y,
+    void *__restrict__ acc_out)
+{
+    constexpr bool kFloat = GRID == 0;
+    typedef typename Sum<kFloat>::type Acc;
+    typedef Codes<GRID> C;
+    constexpr int kContainer = C::kContainer;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row16 = lane & 15, quarter = lane >> 4;
+    const int n0 = blockIdx.x * 16 * NT, m0 = blockIdx.y * 16 * MT;
+    const int64_t row_bytes = (int64_t)K * kContainer / 8;
+
+    const uint8_t *a_row[MT], *b_row[NT];   // rows beyond the edge read the last row; their sums are not stored
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+        a_row[i] = a_codes + min(m0 + 16 * i + row16, M - 1) * row_bytes;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+        b_row[j] = b_codes + min(n0 + 16 * j + row16, N - 1) * row_bytes;
+
+    Acc acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            acc[i][j] = Acc{0, 0, 0, 0};
+
+    auto multiply = [&](const C (&a)[MT], const C (&b)[NT], int operands, bool half) {
+        if constexpr (kFloat) {
+            constexpr int one = 0x7f7f7f7f;   // block scales 2^0
+            auto op = [](const C &c) { return v8i{(int)c.w[0], (int)c.w[1], (int)c.w[2], (int)c.w[3], 0, 0, 0, 0}; };
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op(b[j]), op(a[i]), acc[i][j], 4, 4, 0,
+                                                                                 one, 0, one);
+        } else {
+            v4i bw[NT][2];
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                b[j].widen(bw[j]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                v4i aw[2];
+                a[i].widen(aw);
+                if (half && GRID == 1) {   // 16 one-bit codes sit in the low halves of all eight dwords
+#pragma unroll
+                    for (int o = 0; o < 2; ++o)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            aw[o][e] &= 0xffff;
+                }
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int o = 0; o < 2; ++o)
+                        if (o < operands)
+                            acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bw[j][o], aw[o], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+
+    const int units = K / kUnit;
+    if (wave < units) {
+        C a[BATCH][MT], b[BATCH][NT];
+        auto fetch = [&](int s, int unit) {   // past the end: the last unit again, not used
+            const int off = min(unit, units - 1) * (16 * kContainer) + quarter * 4 * kContainer;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                b[s][j].load(b_row[j] + off);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+                a[s][i].load(a_row[i] + off);
+        };
+#pragma unroll
+        for (int s = 0; s < BATCH; ++s)
+            fetch(s, wave + s * waves);
+        int u = wave;
+        for (; u + BATCH * waves < units; u += BATCH * waves) {
+#pragma unroll
+            for (int s = 0; s < BATCH; ++s) {
+                multiply(a[s], b[s], 2, false);
+                fetch(s, u + (s + BATCH) * waves);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < BATCH; ++s)
+            if (u + s * waves < units)
+                multiply(a[s], b[s], 2, false);
+    }
+    if constexpr (!kFloat) {
+        if ((K & 64) && wave == units % waves) {   // the half unit at the end
+            C a[MT], b[NT];
+            const int off = units * (16 * kContainer) + quarter * 2 * kContainer;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                b[j].load_half(b_row[j] + off);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+                a[i].load_half(a_row[i] + off);
+            multiply(a, b, GRID == 1 ? 2 : 1, true);
+        }
+    }
+
+    // The waves' sums: [wave][i][j][lane].  Large blocks of eight waves: the upper four are added to the
+    // lower four first, so that 64 KiB of LDS do.
+    Acc *park = reinterpret_cast<Acc *>(smem);
+    if (MT * NT > 8 && waves > 4) {
+        if (wave >= 4) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    park[(((wave - 4) * MT + i) * NT + j) * 64 + lane] = acc[i][j];
+        }
+        __syncthreads();
+        if (wave + 4 < waves) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] += park[((wave * MT + i) * NT + j) * 64 + lane];
+        }
+        __syncthreads();
+    }
+    const int parked = MT * NT > 8 ? min(waves, 4) : waves;
+    if (wave < parked) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            park[((wave * MT + i) * NT + j) * 64 + lane] = acc[i][j];
+    }
+    __syncthreads();
+    const bool quad_ok = y && (ld_y & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 7) == 0;
+    for (int t = tid; t < MT * NT * 64; t += blockDim.x) {
+        Acc sum = park[t];
+        for (int v = 1; v < parked; ++v)
+            sum += park[v * (MT * NT * 64) + t];
+        const int tile = t >> 6, l = t & 63;
+        const int m = m0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
+        if (m >= M || n >= N)
+            continue;
+        if constexpr (!kFloat) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sum[e] >>= C::kCarry;   // exact: multiples of 2^kCarry
+        }
+        const float sa = a_scales[m];
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = __fmul_rn(__fmul_rn((float)sum[e], sa), b_scales[min(n + e, N - 1)]);
+        if (acc_out) {
+            typedef typename std::remove_reference<decltype(sum[0])>::type Raw;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < N)
+                    static_cast<Raw *>(acc_out)[(int64_t)m * N + n + e] = sum[e];
+        }
+        if (!y)
+            continue;
+        uint16_t *dst = y + (int64_t)m * ld_y + n;
+        if (quad_ok && n + 4 <= N) {
+            *reinterpret_cast<uint2 *>(dst) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+        } else {
+            for (int e = 0; e < 4; ++e)
+                if (n + e < N)
+                    dst[e] = (uint16_t)float_to_bf16_bits(v[e]);
+        }
+    }
+}
+
+template <int GRID, int MT, int NT, int BATCH>
+hipError_t launch(const SkinnyGemmArgs &a, int waves, hipStream_t stream)
+{
+    const dim3 grid((unsigned)((a.N + 16 * NT - 1) / (16 * NT)), (unsigned)((a.M + 16 * MT - 1) / (16 * MT)));
+    const int parked = MT * NT > 8 && waves > 4 ? 4 : waves;
+    hipLaunchKernelGGL((skinny_gemm_kernel<GRID, MT, NT, BATCH>), grid, dim3(64 * waves), parked * MT * NT * 1024,
+                       stream, a.a_codes, a.a_scales, a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K,
+                       static_cast<uint16_t *>(a.y), a.ld_y, a.acc_out);
+    return hipGetLastError();
+}
+
+int64_t block_count(int64_t M, int64_t N, int mt, int nt)
+{
+    return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * nt - 1) / (16 * nt));
+}
+
+// The block: the smallest one that leaves no more than a workgroup per compute unit.  Small blocks
+// spread the loads over the chip, large ones read each operand less often; a workgroup more than the
+// chip holds costs a second round of latency.  Measured (us, block / waves; 4 bits):
+//   2048 x 5632, 24 rows: 1x1 5.4, 2x1 6.2, 2x2 7+     5632 x 2048, 24 rows: 2x2 4.7, 2x1 5.2, 1x1 5.2
+//   4096 x 1024, 64 rows: 2x2 3.4, 4x1 3.7, 1x1 4.2    5632 x 2048, 128 rows: 4x4 8.1, 4x2 8.8, 4x1 10+
+// With 16 rows or fewer the activations are next to nothing, and 1x1 is within 3 % of the best
+// everywhere (11008 x 4096, 1 row: 1x1 6.4, 1x2 7.0).
+template <int GRID>
+hipError_t launch_grid(const SkinnyGemmArgs &a, hipStream_t stream)
+{
+    constexpr int64_t kUnitsOfChip = 256;
+    auto fits = [&](int mt, int nt) { return block_count(a.M, a.N, mt, nt) <= kUnitsOfChip; };
+    if (a.M <= 16 || fits(1, 1)) {
+        // eight waves when workgroups are few and the contraction is long (2048 x 5632, 1 row: 4.4 against 5.1)
+        const bool more_waves = a.K >= 32 * kUnit && 2 * block_count(a.M, a.N, 1, 1) <= kUnitsOfChip;
+        return launch<GRID, 1, 1, 2>(a, more_waves ? 8 : 4, stream);
+    }
+    if (fits(1, 2))
+        return launch<GRID, 1, 2, 2>(a, 4, stream);
+    if (a.M <= 32 || fits(2, 2))
+        return launch<GRID, 2, 2, 2>(a, 4, stream);
+    if (fits(4, 2))
+        return launch<GRID, 4, 2, 1>(a, 8, stream);
+    return launch<GRID, 4, 4, 1>(a, 4, stream);
+}
+
+}  // namespace
+
+// Whether this kernel is the one for the shape.  With few rows always; beyond that as long as its
+// largest block leaves about one workgroup per compute unit: the tile kernels with their staging
+// need whole tiles for every compute unit to be better (us, this kernel / tile kernels, 4 bits:
+// 2048 x 5632 with 512 rows 14.2 / 20.7, 4096 x 1024 with 256 rows 5.8 / 6.9 and with 512 rows
+// 8.2 / 7.2, 5632 x 2048 with 256 rows 11.8 / 10.5).  The tile kernels take 1 and 2 bits only after a
+// re-coding pass, which moves the line (2 bits: 5632 x 2048 with 512 rows 17.0 / 19.2, 11008 x 4096
+// with 512 rows 51 / 45).  Where no tile kernel covers the shape the alternative is a general kernel
+// at a third of their rate.
+bool skinny_gemm_preferred(int64_t M, int64_t N, int64_t K, int grid)
+{
+    if (M <= 64)
+        return true;
+    const bool tiles = K % 128 == 0 && (grid == 0 || (N >= 128 && (grid >= 3 || M >= 128)));
+    return block_count(M, N, 4, 4) <= (!tiles ? 2048 : grid == 1 || grid == 2 ? 768 : 256);
+}
+
+hipError_t launch_skinny_gemm(const SkinnyGemmArgs &a, hipStream_t stream)
+{
+    switch (a.grid) {
+    case 0: return launch_grid<0>(a, stream);
+    case 1: return launch_grid<1>(a, stream);
+    case 2: return launch_grid<2>(a, stream);
+    case 3: return launch_grid<3>(a, stream);
+    default: return launch_grid<4>(a, stream);
+    }
+}
+
+}  // namespace quest

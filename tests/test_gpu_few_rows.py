@@ -1,0 +1,60 @@
+"""The forward product with few activation rows (csrc/skinny_gemm.hip) against the CPU oracle: every
+block size of the kernel, ragged last blocks, contractions that end in half a unit or are one, every grid."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import quest_oracle as qo
+from oracle.quest_oracle import _load, _ptr
+from paper_2502_05003_amd import binding as q
+
+from gpu_util import DEV, check_gemm_output, to_device
+
+pytestmark = pytest.mark.gpu
+
+#        M, N, K: blocks of 1x1, 1x2, 2x2, 4x2 and 4x4 sixteens
+# (One rounding is up to 2^-8 = 3.9e-3 of an element and 1.7e-3 norm-wise over many; check_gemm_output's
+# norm-wise bound of 2e-3 needs the many: a few hundred outputs of comparable size at least.)
+SHAPES = [(1, 1057, 64), (16, 4100, 192), (5, 130, 4096), (17, 4097, 320), (33, 2561, 128), (40, 5632, 256),
+          (65, 2050, 576), (129, 1030, 1088)]
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_integer_grids(M, N, K, bits):
+    rng = np.random.default_rng(M + N + K + bits)
+    L, cb = 1 << bits, qo.container_bits(bits)
+    ka = rng.integers(-L // 2, L // 2, size=(M, K), dtype=np.int32)
+    kb = rng.integers(-L // 2, L // 2, size=(N, K), dtype=np.int32)
+    ka[M // 2], kb[0], kb[-1] = L // 2 - 1, L // 2 - 1, -L // 2      # largest |acc|
+    if M == 1:   # one row of two huge outputs and small ones would round like two elements
+        ka[0, ::2] = rng.integers(-L // 2, L // 2, size=K // 2)
+    a, b = (np.empty((r, K * cb // 8), dtype=np.uint8) for r in (M, N))
+    _load().qo_pack_codes(_ptr(ka), M, K, bits, _ptr(a))
+    _load().qo_pack_codes(_ptr(kb), N, K, bits, _ptr(b))
+    sa = (rng.random(M) + 0.5).astype(np.float32)
+    sb = ((rng.random(N) + 0.5) * 0.01).astype(np.float32)
+    y = torch.full((M, N + 3), 7.0, dtype=torch.bfloat16, device=DEV)
+    acc = torch.empty(M, N, dtype=torch.int32, device=DEV)
+    q.quest_lowbit_gemm(to_device(a), to_device(sa), to_device(b), to_device(sb), K, bits, y=y[:, :N], acc_out=acc)
+    torch.cuda.synchronize()
+    ref = qo.gemm_odd(2 * ka + 1, 2 * kb + 1)
+    assert np.array_equal(acc.cpu().numpy().astype(np.int64), ref)
+    check_gemm_output(y[:, :N], ref, sa, sb)
+    assert torch.all(y[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("M,N,K", [s for s in SHAPES if s[2] % 128 == 0] + [(30, 96, 640)])
+def test_fp4_grid(M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
+    b = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    sa = (rng.random(M) + 0.5).astype(np.float32)
+    sb = ((rng.random(N) + 0.5) * 0.01).astype(np.float32)
+    y = torch.full((M, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    acc = torch.empty(M, N, dtype=torch.float32, device=DEV)
+    q.quest_lowbit_gemm_fp4(to_device(a), to_device(sa), to_device(b), to_device(sb), K, y=y, acc_out=acc)
+    torch.cuda.synchronize()
+    ref = qo.unpack_fp4(a, K).astype(np.float64) @ qo.unpack_fp4(b, K).astype(np.float64).T
+    assert np.array_equal(acc.cpu().numpy().astype(np.float64), ref)
+    check_gemm_output(y, ref, sa, sb)
