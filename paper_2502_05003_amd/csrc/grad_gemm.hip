@@ -5,6 +5,7 @@
 //   which = 1:  out[N, K] = dy[M, N]^T * xhat_h[M, K]   (contraction over M)
 // and, with the same machinery, the weight-only forward product (Sec. 4.4):
 //   which = 2:  out[M, N] = x[M, K]    * what_h[N, K]^T (contraction over K)
+// This file: outputs of many tiles, and the choice between its kernels and those of grad_gemm_mid.hip.
 #include <algorithm>
 #include <numeric>
 #include <utility>
@@ -18,88 +19,6 @@ namespace {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-
-constexpr int kTile = 64;      // output tile is 64 x 64, one 32 x 32 quadrant per wave
-constexpr int kStep = 32;      // contraction elements per main-loop step
-constexpr int kThreads = 256;
-constexpr int kStride = 40;    // LDS row stride in bf16: 32 payload + 8 pad
-
-/*
- * TRANSPOSED = false: left operand rows are dy rows (out row = m, contraction index = n).
- * TRANSPOSED = true:  left operand rows are dy columns (out row = n, contraction index = m).
- * q is [C, K*cb/8] packed codes with one scale per contraction row; C is the contraction length.
- */
-template <bool TRANSPOSED>
-__global__ __launch_bounds__(kThreads) void grad_gemm_kernel(
-    const uint16_t *__restrict__ dy, int64_t ld_dy, const uint8_t *__restrict__ q_codes,
-    const float *__restrict__ q_scales, int levels, int cb, int C, int K,
-    uint16_t *__restrict__ out)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t left[kTile * kStride];   // [out row][c]
-    __shared__ __attribute__((aligned(16))) uint16_t right[kTile * kStride];  // [k][c]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int r0 = blockIdx.y * kTile, k0 = blockIdx.x * kTile;
-    const int64_t q_row_bytes = (int64_t)K * cb / 8;
-
-    v16f acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        acc[r] = 0.0f;
-
-    for (int c0 = 0; c0 < C; c0 += kStep) {
-        __syncthreads();
-        if constexpr (!TRANSPOSED) {
-            // 64 rows x 32 contraction elements, 16 bytes per thread, already c-contiguous
-            const int row = tid >> 2, chunk = tid & 3;
-            const uint4 v = *reinterpret_cast<const uint4 *>(dy + (int64_t)(r0 + row) * ld_dy + c0 +
-                                                             chunk * 8);
-            *reinterpret_cast<uint4 *>(left + row * kStride + chunk * 8) = v;
-        } else {
-            // 32 contraction rows x 64 output rows; transpose through LDS
-            const int crow = tid >> 3, chunk = tid & 7;
-            const uint4 v = *reinterpret_cast<const uint4 *>(dy + (int64_t)(c0 + crow) * ld_dy + r0 +
-                                                             chunk * 8);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                left[(chunk * 8 + e) * kStride + crow] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-        }
-        {
-            // 32 contraction rows x 64 k of codes: eight codes per thread, dequantized to bf16(s u)
-            const int crow = tid >> 3, chunk = tid & 7;
-            const uint8_t *src = q_codes + (int64_t)(c0 + crow) * q_row_bytes +
-                                 (int64_t)(k0 + chunk * 8) * cb / 8;
-            uint32_t bits = 0;
-            for (int byte = 0; byte < cb; ++byte)
-                bits |= (uint32_t)src[byte] << (8 * byte);
-            const float s = q_scales[c0 + crow];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int c = (int)((bits >> (e * cb)) & ((1u << cb) - 1u));
-                const float value = __fmul_rn(s, (float)(2 * c - (levels - 1)));
-                right[(chunk * 8 + e) * kStride + crow] = (uint16_t)float_to_bf16_bits(value);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < kStep / 16; ++s) {
-            const int off = s * 16 + (lane >> 5) * 8;
-            const v8bf a = *reinterpret_cast<const v8bf *>(left + (wr * 32 + (lane & 31)) * kStride + off);
-            const v8bf b = *reinterpret_cast<const v8bf *>(right + (wc * 32 + (lane & 31)) * kStride + off);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-        }
-    }
-
-    const int k = k0 + wc * 32 + (lane & 31);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = r0 + wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        out[(int64_t)row * K + k] = (uint16_t)float_to_bf16_bits(acc[r]);
-    }
-}
-
 
 // ------------------------------------------------------------------------------------------
 // Main path.  The code-packed operand is first expanded once to bf16(s u), [C, K] row-major, in
@@ -594,7 +513,8 @@ constexpr int kLds = kStages * kGStage;
 // How a call is carried out: which kernels, how the tiles are dealt out, what scratch it needs.
 struct GradGemmPlan {
     bool covered;      // some kernel handles the shape
-    bool tile_path;    // the 256 x 256 tile kernels (else the small-shape kernel, no scratch)
+    bool tile_path;    // a shape the 256 x 256 tile kernels can do (their scratch is asked for)
+    bool mid;          // the kernels of grad_gemm_mid.hip do it (always when tile_path is not set)
     bool split;        // tiles split over the CUs, partial tiles summed by the fix-up kernel
     int tiles_r, tiles_k, steps, blocks, per_block, phase_period;
     int64_t out_rows, out_cols, contraction, q_rows, ld_left;
@@ -614,7 +534,8 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
     p.tile_path = p.out_rows >= GT / 2 && p.out_cols >= GT / 2 && (p.contraction % GC) == 0 &&
                   p.out_rows * p.out_cols < ((int64_t)1 << 31) &&
                   std::max(M, N) * std::max(K, N) < ((int64_t)1 << 30);
-    p.covered = p.tile_path || !(which == 2 || fp4);   // only the tile kernels know these two forms
+    p.covered = p.tile_path || !(which == 2 || fp4);   // these two forms: outputs of 128 x 128 or more only
+    p.mid = true;
     if (!p.tile_path)
         return p;
     p.tiles_r = (int)((p.out_rows + GT - 1) / GT);
@@ -649,6 +570,16 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
         if (p.blocks % p.phase_period != 0)
             p.phase_period = p.blocks;
     }
+    // Whether the kernels that expand on the way into LDS are cheaper: theirs is their own estimate; here
+    // the expansion (read 0.5, written 2 bytes per code at 4.5 TB/s) and two or three launches come on top.
+    // A step of a whole tile takes 0.6 us, or 0.72 with all compute units busy (the chip is power-limited).
+    // Both sides measured, us: 512 x 5632 x 2048 weight-only 22 / 56; 2048 x 1792 x 640 G_x 14 / 47, G_w 16 / 47;
+    // 2048 x 5632 x 2048 G_x 59 / 76, G_w 64 / 60; 4096 x 5632 x 2048 G_x 112 / 112, G_w 123 / 98.
+    const double expand_cost = 4.0 + (double)p.q_rows * (double)K * 2.5 / 4.5e6;
+    const double busy = rounds > 0 && cus > 0 ? (double)tiles / ((double)rounds * cus) : 1.0;
+    const double tile_cost =
+        p.split ? split_cost + 0.24 * (double)((units + cus - 1) / cus) : rounds * ((0.6 + 0.12 * busy) * p.steps + 8.0) + 4.0;
+    p.mid = grad_gemm_mid_cost(p.contraction, p.out_rows, p.out_cols, cus >= 8 ? cus : 256) < expand_cost + tile_cost;
     p.expanded_bytes = ((size_t)p.q_rows * K * 2 + 255) / 256 * 256;
     p.partial_bytes = p.split ? (size_t)2 * p.blocks * kSlotQuads * sizeof(float4) : 0;
     return p;
@@ -686,57 +617,50 @@ hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)
     const GradGemmPlan p = plan_grad_gemm(a.which, a.fp4, a.M, a.N, a.K, device_compute_units());
     if (!p.covered)
         return hipErrorInvalidValue;
-    if (p.tile_path) {
-        if (a.workspace == nullptr || (size_t)a.workspace_bytes < p.expanded_bytes + p.partial_bytes)
-            return hipErrorInvalidValue;
-        hipError_t err = prepare_grad_gemm_kernels();
-        if (err != hipSuccess)
-            return err;
-        // the caller's scratch: the expanded operand, then the partial tiles
-        char *memory = static_cast<char *>(a.workspace);
-        auto *qhat = reinterpret_cast<uint16_t *>(memory);
-        auto *partial = p.split ? reinterpret_cast<float4 *>(memory + p.expanded_bytes) : nullptr;
-        const int tiles_r = p.tiles_r, tiles_k = p.tiles_k, per_block = p.per_block, phase_period = p.phase_period;
-        const int64_t ld_left = p.ld_left, contraction = p.contraction, out_rows = p.out_rows, out_cols = p.out_cols;
-
-        const int64_t groups = p.q_rows * a.K / 8;
-        hipLaunchKernelGGL(expand_codes_kernel, dim3((unsigned)((groups + 1023) / 1024)), dim3(256), 0, stream,
-                           a.q_codes, a.q_scales, levels, a.cb, (int)a.K, groups, qhat);
-        err = hipGetLastError();
-        if (err != hipSuccess)
-            return err;
-        const dim3 grid((unsigned)p.blocks), block(kGemmThreads);
-        if (a.which == 0)
-            hipLaunchKernelGGL((grad_gemm_tile_kernel<0, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
-                               a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
-                               phase_period, out, partial);
-        else if (a.which == 1)
-            hipLaunchKernelGGL((grad_gemm_tile_kernel<1, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
-                               a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
-                               phase_period, out, partial);
-        else
-            hipLaunchKernelGGL((grad_gemm_tile_kernel<2, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
-                               a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
-                               phase_period, out, partial);
-        err = hipGetLastError();
-        if (err == hipSuccess && p.split) {
-            hipLaunchKernelGGL(grad_gemm_fixup_kernel, dim3((unsigned)(tiles_r * tiles_k * 16)), dim3(256), 0, stream,
-                               partial, p.steps, per_block, phase_period, (int)out_rows, (int)out_cols, tiles_r,
-                               tiles_k, out);
-            err = hipGetLastError();
-        }
+    if (p.mid) {
+        const GradMidArgs mid = {a.which, a.fp4 ? 0 : a.bits, a.dy, p.ld_left, a.q_codes, a.K * a.cb / 8, a.q_scales,
+                                 p.contraction, p.out_rows, p.out_cols, a.out};
+        return launch_grad_gemm_mid(mid, stream);
+    }
+    if (a.workspace == nullptr || (size_t)a.workspace_bytes < p.expanded_bytes + p.partial_bytes)
+        return hipErrorInvalidValue;
+    hipError_t err = prepare_grad_gemm_kernels();
+    if (err != hipSuccess)
         return err;
+    // the caller's scratch: the expanded operand, then the partial tiles
+    char *memory = static_cast<char *>(a.workspace);
+    auto *qhat = reinterpret_cast<uint16_t *>(memory);
+    auto *partial = p.split ? reinterpret_cast<float4 *>(memory + p.expanded_bytes) : nullptr;
+    const int tiles_r = p.tiles_r, tiles_k = p.tiles_k, per_block = p.per_block, phase_period = p.phase_period;
+    const int64_t ld_left = p.ld_left, contraction = p.contraction, out_rows = p.out_rows, out_cols = p.out_cols;
+
+    const int64_t groups = p.q_rows * a.K / 8;
+    hipLaunchKernelGGL(expand_codes_kernel, dim3((unsigned)((groups + 1023) / 1024)), dim3(256), 0, stream,
+                       a.q_codes, a.q_scales, levels, a.cb, (int)a.K, groups, qhat);
+    err = hipGetLastError();
+    if (err != hipSuccess)
+        return err;
+    const dim3 grid((unsigned)p.blocks), block(kGemmThreads);
+    if (a.which == 0)
+        hipLaunchKernelGGL((grad_gemm_tile_kernel<0, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
+                           a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
+                           phase_period, out, partial);
+    else if (a.which == 1)
+        hipLaunchKernelGGL((grad_gemm_tile_kernel<1, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
+                           a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
+                           phase_period, out, partial);
+    else
+        hipLaunchKernelGGL((grad_gemm_tile_kernel<2, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
+                           a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
+                           phase_period, out, partial);
+    err = hipGetLastError();
+    if (err == hipSuccess && p.split) {
+        hipLaunchKernelGGL(grad_gemm_fixup_kernel, dim3((unsigned)(tiles_r * tiles_k * 16)), dim3(256), 0, stream,
+                           partial, p.steps, per_block, phase_period, (int)out_rows, (int)out_cols, tiles_r,
+                           tiles_k, out);
+        err = hipGetLastError();
     }
-    if (a.which == 0) {
-        const dim3 grid((unsigned)(a.K / kTile), (unsigned)(a.M / kTile));
-        hipLaunchKernelGGL(grad_gemm_kernel<false>, grid, dim3(kThreads), 0, stream, dy, a.N,
-                           a.q_codes, a.q_scales, levels, a.cb, (int)a.N, (int)a.K, out);
-    } else {
-        const dim3 grid((unsigned)(a.K / kTile), (unsigned)(a.N / kTile));
-        hipLaunchKernelGGL(grad_gemm_kernel<true>, grid, dim3(kThreads), 0, stream, dy, a.N,
-                           a.q_codes, a.q_scales, levels, a.cb, (int)a.M, (int)a.K, out);
-    }
-    return hipGetLastError();
+    return err;
 }
 
 }  // namespace quest

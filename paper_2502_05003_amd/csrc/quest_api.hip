@@ -639,6 +639,8 @@ quest_status quest_init(void)
         err = quest::prepare_trust_backward_kernels();
     if (err == hipSuccess)
         err = quest::prepare_grad_gemm_kernels();
+    if (err == hipSuccess)
+        err = quest::prepare_grad_gemm_mid_kernels();
     void *ptr = nullptr;
     if (err == hipSuccess)
         err = static_scratch_address(&ptr);

@@ -121,6 +121,24 @@ struct GradGemmArgs {
     int64_t workspace_bytes;
 };
 
+// The same products for outputs of few tiles (grad_gemm_mid.hip); needs no scratch.
+struct GradMidArgs {
+    int mode;            // as GradGemmArgs::which
+    int grid;            // 1 .. 4: bits of the Eq. 1 grid; 0: E2M1
+    const void *left;    // bf16: dy, or x for the weight-only product
+    int64_t ld_left;
+    const uint8_t *q_codes;
+    int64_t q_row_bytes;
+    const float *q_scales;
+    int64_t C, R, K;     // contraction length, output rows and columns
+    void *out;
+};
+
+// every shape of multiples of 64; E2M1 codes for modes 0 and 1 only
+hipError_t launch_grad_gemm_mid(const GradMidArgs &a, hipStream_t stream);
+// what the call is expected to take, us
+double grad_gemm_mid_cost(int64_t C, int64_t R, int64_t K, int cus);
+
 // hipErrorInvalidValue: the shape is not one the kernels cover, or the workspace is too small
 // (the entry points check both beforehand with grad_gemm_workspace_bytes).
 hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream);
@@ -142,6 +160,7 @@ hipError_t prepare_lowbit_gemm_kernels();
 hipError_t prepare_fp4_gemm_kernels();
 hipError_t prepare_trust_backward_kernels();
 hipError_t prepare_grad_gemm_kernels();
+hipError_t prepare_grad_gemm_mid_kernels();
 
 // Raise the dynamic LDS limit of `kernel` to `bytes` on the current device.  The attribute is set
 // once per (kernel, device, size) and remembered; safe to call from several host threads.
