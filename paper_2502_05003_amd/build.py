@@ -8,11 +8,14 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libquest.so")
 PROBE_LIB = os.path.join(_HERE, "libquest_probe.so")   # measurement aid of bench.py (include/quest_probe.h)
-SOURCES = ["quest_api.hip", "hadamard_quantize.hip", "hadamard_quantize_mfma.hip",
-           "lowbit_gemm.hip", "skinny_gemm.hip", "fp4_gemm.hip", "trust_backward.hip", "trust_backward_mfma.hip", "grad_gemm.hip",
+SOURCES = ["quest_api.hip", "hadamard_quantize.hip", "hadamard_quantize_mfma.hip", "hadamard_quantize_rows.hip",
+           "lowbit_gemm.hip", "skinny_gemm.hip", "fp4_gemm.hip", "trust_backward.hip", "trust_backward_mfma.hip",
+           "trust_backward_rows.hip", "grad_gemm.hip",
            "grad_gemm_mid.hip"]
 # per-source extra flags: kernels whose MFMA results are consumed by vector code keep them in VGPRs
 EXTRA_FLAGS = {"hadamard_quantize_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+               "hadamard_quantize_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+               "trust_backward_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
                "trust_backward_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

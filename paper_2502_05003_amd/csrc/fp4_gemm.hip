@@ -187,7 +187,10 @@ __global__ __launch_bounds__(kTileThreads, 2) void fp4_gemm_tile_kernel(
 
 hipError_t prepare_fp4_gemm_kernels()
 {
-    return allow_dynamic_lds(reinterpret_cast<const void *>(fp4_gemm_tile_kernel), kTileLds);
+    static OncePerDevice once;
+    return once([] {
+        return allow_dynamic_lds(reinterpret_cast<const void *>(fp4_gemm_tile_kernel), kTileLds);
+    });
 }
 
 hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream)

@@ -599,12 +599,15 @@ int64_t grad_gemm_workspace_bytes(int which, bool fp4, int64_t M, int64_t N, int
 
 hipError_t prepare_grad_gemm_kernels()
 {
-    hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<0, kStages>), kLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<1, kStages>), kLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<2, kStages>), kLds);
-    return err;
+    static OncePerDevice once;
+    return once([] {
+        hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<0, kStages>), kLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<1, kStages>), kLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<2, kStages>), kLds);
+        return err;
+    });
 }
 
 hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)

@@ -193,8 +193,11 @@ hipError_t prepare_quantize_kernels()
 hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
 {
     if (a.rows2 != 0) {
-        // two operands: one launch where the matrix-core kernel covers the shape, else one after the other
-        if (a.rows != 0 && launch_hadamard_quantize_mfma(a, stream))
+        // two operands: one launch where one matrix-core kernel takes both, else one after the other
+        const bool first_by_rows = quantize_rows_preferred(a, a.rows), second_by_rows = quantize_rows_preferred(a, a.rows2);
+        if (first_by_rows && second_by_rows)
+            return launch_hadamard_quantize_rows(a, stream);
+        if (!first_by_rows && !second_by_rows && a.rows != 0 && launch_hadamard_quantize_mfma(a, stream))
             return hipGetLastError();
         QuantizeArgs first = a, second = a;
         first.x2 = nullptr;
@@ -213,6 +216,8 @@ hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
     }
     if (a.rows == 0)
         return hipSuccess;
+    if (quantize_rows_preferred(a, a.rows))
+        return launch_hadamard_quantize_rows(a, stream);
     if (launch_hadamard_quantize_mfma(a, stream))
         return hipGetLastError();
     const int cols = (int)a.cols;

@@ -37,7 +37,6 @@
 namespace quest {
 namespace {
 
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
@@ -55,68 +54,6 @@ __device__ __forceinline__ void store_word(uint32_t *p, uint32_t v)
 {
     __builtin_nontemporal_store(v, p);
 }
-
-template <int XOR>
-__device__ __forceinline__ uint32_t swizzle_xor(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (XOR << 10) | 0x1f);
-}
-
-// Per-lane constants of the lane <-> field transposes.  In stage s a lane keeps the fields whose
-// index bit s equals its own lane bit s and takes the others from lane ^ (1 << s), moved by
-// FIELD << s bits.  Moves of 8 or 16 bits are one byte permute; smaller ones a rotate and a
-// three-input select.
-template <int STAGES, int FIELD>
-struct TransposePlan {
-    uint32_t keep[STAGES];   // bit mask of the fields kept            (sub-byte stages)
-    uint32_t rot[STAGES];    // right-rotation applied to the partner  (sub-byte stages)
-    uint32_t sel[STAGES];    // v_perm selector {own, partner}         (byte and halfword stages)
-
-    __device__ __forceinline__ void init(int lane)
-    {
-#pragma unroll
-        for (int s = 0; s < STAGES; ++s) {
-            const int sh = FIELD << s;
-            uint32_t lo = 0;  // field positions whose index has bit s clear
-#pragma unroll
-            for (int f = 0; f < (1 << STAGES); ++f)
-                if (((f >> s) & 1) == 0)
-                    lo |= ((1u << FIELD) - 1u) << (f * FIELD);
-            const bool up = (lane >> s) & 1;
-            keep[s] = up ? ~lo : lo;
-            rot[s] = up ? (uint32_t)sh : (uint32_t)(32 - sh);
-            // v_perm_b32(partner, own, sel): selector bytes 0..3 pick from own, 4..7 from partner
-            if (sh == 8)
-                sel[s] = up ? 0x03070105u : 0x06020400u;
-            else if (sh == 16)
-                sel[s] = up ? 0x03020706u : 0x05040100u;
-            else
-                sel[s] = 0;
-        }
-    }
-
-    // After the call, field i of lane a holds what field a of lane i held (lanes modulo 2^STAGES).
-    __device__ __forceinline__ uint32_t apply(uint32_t d) const
-    {
-#pragma unroll
-        for (int s = 0; s < STAGES; ++s) {
-            uint32_t partner;
-            if (s == 0) partner = swizzle_xor<1>(d);
-            else if (s == 1) partner = swizzle_xor<2>(d);
-            else if (s == 2) partner = swizzle_xor<4>(d);
-            else if (s == 3) partner = swizzle_xor<8>(d);
-            else partner = swizzle_xor<16>(d);
-            if ((FIELD << s) >= 8) {
-                d = __builtin_amdgcn_perm(partner, d, sel[s]);
-            } else {
-                const uint32_t rotated = __builtin_amdgcn_alignbit(partner, partner, rot[s]);
-                // (keep & d) | (~keep & rotated) as one three-input bit operation
-                d = __builtin_amdgcn_bitop3_b32(keep[s], d, rotated, 0xCA);
-            }
-        }
-        return d;
-    }
-};
 
 /*
  * U: row length / 128.  LOG2N: log2 of the Hadamard block when it is >= 32; 5 also stands for
@@ -386,35 +323,11 @@ void hq_mfma_kernel(
                             for (int e = 0; e < 4; ++e)
                                 f[4 * i + e] = __uint_as_float(piece[e]);
                         }
-                        // x = hi + mid + lo, each piece the top 16 bits of what the pieces before it
-                        // leave (exact: the remainders have 16 and 8 significant bits).  Remainders
-                        // come from the two-way bf16 dot product, packed piece times (1, 0) or (0, 1)
-                        // minus the value: s1 = hi - x = -(mid + lo), s2 = top16(s1) - s1 = lo.
-                        uint32_t hi[8], mid[8], lo[8];
-                        // (1, 0) and (0, 1) as bf16 pairs, held in registers the compiler cannot see through: written
-                        // as literals the pair (1, 0) reaches the instruction as (0, 1)
-                        uint32_t first_bits = 0x00003F80u, second_bits = 0x3F800000u;
-                        asm volatile("" : "+v"(first_bits), "+v"(second_bits));
-                        v2bf first, second;
-                        __builtin_memcpy(&first, &first_bits, 4);
-                        __builtin_memcpy(&second, &second_bits, 4);
+                        uint32_t hi[8], mid[8], lo[8];   // x = hi + mid + lo (see split_bf16)
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            const float a = f[2 * i], b = f[2 * i + 1];
-                            sumsq = __fmaf_rn(a, a, sumsq);
-                            sumsq = __fmaf_rn(b, b, sumsq);
-                            hi[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
-                            v2bf hp;
-                            __builtin_memcpy(&hp, &hi[i], 4);
-                            const float s1a = __builtin_amdgcn_fdot2_f32_bf16(hp, first, -a, false);
-                            const float s1b = __builtin_amdgcn_fdot2_f32_bf16(hp, second, -b, false);
-                            mid[i] = __builtin_amdgcn_perm(__float_as_uint(s1b), __float_as_uint(s1a), 0x07060302u);
-                            v2bf mp;
-                            __builtin_memcpy(&mp, &mid[i], 4);
-                            const float s2a = __builtin_amdgcn_fdot2_f32_bf16(mp, first, -s1a, false);
-                            const float s2b = __builtin_amdgcn_fdot2_f32_bf16(mp, second, -s1b, false);
-                            lo[i] = __builtin_amdgcn_perm(__float_as_uint(s2b), __float_as_uint(s2a), 0x07060302u);
-                        }
+                        for (int i = 0; i < 16; ++i)
+                            sumsq = __fmaf_rn(f[i], f[i], sumsq);
+                        split_bf16(f, hi, mid, lo);
                         v8bf p0, p1;
                         __builtin_memcpy(&p0, &lo[0], 16);      // smallest piece first
                         __builtin_memcpy(&p1, &lo[4], 16);
@@ -638,7 +551,8 @@ hipError_t prepare_quantize_mfma_kernels()
     return hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(hq_mfma_kernel<16, 11, true>));
 }
 
-// Launches the matrix-core kernel if it covers the call; returns false (nothing launched) otherwise.
+// Launches the matrix-core kernel if it covers the call; returns false (nothing launched) otherwise.  `query`:
+// only answers.
 // Covered (U = row length / 128):
 //   bf16 rows, b = 4: rows of 512, 1024, 2048, 4096, 5632 or 11008 elements with a Hadamard block of
 //     at most 32, or 128, 256 (11008 only), 512, 1024, 2048, 4096 where it divides the row; the other
@@ -647,7 +561,7 @@ hipError_t prepare_quantize_mfma_kernels()
 //   bf16 rows, b = 1, 2, 3, 8 and the E2M1 grid: rows of 1024 .. 5632 with their widest block;
 //   fp32 rows and the AbsMax scale, b = 4: rows of 512 .. 5632 with their widest block; fp32 rows
 //     also for the other model widths up to 4608.
-bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream)
+bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream, bool query)
 {
     if ((a.cols % 128) != 0)
         return false;
@@ -658,6 +572,8 @@ bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream)
             return false;
 #define QUEST_HOLD_CASE(U_, L_)                                          \
     if (u == U_ && l == L_) {                                            \
+        if (query)                                                       \
+            return true;                                                 \
         if (a.dtype == QUEST_F32 && a.mode == kQuantAbsMax)              \
             launch<U_, L_, false, 4, float, true>(a, stream);            \
         else if (a.dtype == QUEST_F32)                                   \
@@ -672,7 +588,7 @@ bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream)
         if (a.dtype == QUEST_F32 && a.mode == kQuantRms) {   // fp32 master weights of the smaller models
 #define QUEST_F32_CASE(U_, L_)                                           \
     if (u == U_ && l == L_) {                                            \
-        launch<U_, L_, false, 4, float, false>(a, stream);               \
+        if (!query) launch<U_, L_, false, 4, float, false>(a, stream);               \
         return true;                                                     \
     }
             QUEST_F32_CASE(5, 7) QUEST_F32_CASE(6, 8) QUEST_F32_CASE(10, 8) QUEST_F32_CASE(13, 7)
@@ -686,7 +602,7 @@ bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream)
             return false;
 #define QUEST_BITS_CASE(U_, L_, B_)                    \
     if (u == U_ && l == L_ && a.bits == B_) {          \
-        launch<U_, L_, false, B_>(a, stream);          \
+        if (!query) launch<U_, L_, false, B_>(a, stream);          \
         return true;                                   \
     }
 #define QUEST_BITS_CASES(U_, L_) \
@@ -699,7 +615,7 @@ bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream)
     if (a.mode == kQuantFp4) {   // the E2M1 grid
 #define QUEST_FP4_CASE(U_, L_)                    \
     if (u == U_ && l == L_) {                     \
-        launch<U_, L_, true>(a, stream);          \
+        if (!query) launch<U_, L_, true>(a, stream);          \
         return true;                              \
     }
         QUEST_FP4_CASE(8, 10) QUEST_FP4_CASE(16, 11) QUEST_FP4_CASE(32, 12) QUEST_FP4_CASE(44, 9)
@@ -708,7 +624,7 @@ bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream)
     }
 #define QUEST_CASE(U_, L_)                        \
     if (u == U_ && l == L_) {                     \
-        launch<U_, L_>(a, stream);                \
+        if (!query) launch<U_, L_>(a, stream);                \
         return true;                              \
     }
     QUEST_CASE(4, 5) QUEST_CASE(4, 7) QUEST_CASE(4, 9)

@@ -9,6 +9,7 @@
 
 namespace quest {
 
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // In-lane element index iota = b6 + 2 b7 + 4 b8 + 8 b9 + 16 tile (bN = index bit N of the
@@ -66,6 +67,16 @@ __device__ __forceinline__ void hadamard_operand(int log2n, int m, int h, v8bf (
         }
         __builtin_memcpy(&bmat[s], w, 16);
     }
+}
+
+// The same for a block size known only at run time (wave-uniform): the general form costs about 200
+// instructions, 1 us of a short launch, and is needed for blocks below 32 only.
+__device__ __forceinline__ void hadamard_operand_any(int log2n, int m, int h, v8bf (&bmat)[2])
+{
+    if (log2n >= 5)
+        hadamard_operand<true>(log2n, m, h, bmat);
+    else
+        hadamard_operand<false>(log2n, m, h, bmat);
 }
 
 // 1 / sqrt(n) and sqrt(n), correctly rounded: powers of two, times sqrt(2) for odd log2(n).
@@ -145,6 +156,173 @@ __device__ __forceinline__ void tile_stages(float (&acc)[G][16])
                 }
         }
     }
+}
+
+// Sixteen floats as three packed bf16 pieces each, x = hi + mid + lo exactly: each piece is the top 16
+// bits of what the pieces before it leave (the remainders have 16 and 8 significant bits).  Remainders
+// come from the two-way bf16 dot product, packed piece times (1, 0) or (0, 1) minus the value:
+// s1 = hi - x = -(mid + lo), s2 = top16(s1) - s1 = lo.  `mid` holds -mid.
+__device__ __forceinline__ void split_bf16(const float (&f)[16], uint32_t (&hi)[8], uint32_t (&mid)[8], uint32_t (&lo)[8])
+{
+    // (1, 0) and (0, 1) as bf16 pairs, held in registers the compiler cannot see through: written
+    // as literals the pair (1, 0) reaches the instruction as (0, 1)
+    uint32_t first_bits = 0x00003F80u, second_bits = 0x3F800000u;
+    asm volatile("" : "+v"(first_bits), "+v"(second_bits));
+    v2bf first, second;
+    __builtin_memcpy(&first, &first_bits, 4);
+    __builtin_memcpy(&second, &second_bits, 4);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float a = f[2 * i], b = f[2 * i + 1];
+        hi[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+        v2bf hp;
+        __builtin_memcpy(&hp, &hi[i], 4);
+        const float s1a = __builtin_amdgcn_fdot2_f32_bf16(hp, first, -a, false);
+        const float s1b = __builtin_amdgcn_fdot2_f32_bf16(hp, second, -b, false);
+        mid[i] = __builtin_amdgcn_perm(__float_as_uint(s1b), __float_as_uint(s1a), 0x07060302u);
+        v2bf mp;
+        __builtin_memcpy(&mp, &mid[i], 4);
+        const float s2a = __builtin_amdgcn_fdot2_f32_bf16(mp, first, -s1a, false);
+        const float s2b = __builtin_amdgcn_fdot2_f32_bf16(mp, second, -s1b, false);
+        lo[i] = __builtin_amdgcn_perm(__float_as_uint(s2b), __float_as_uint(s2a), 0x07060302u);
+    }
+}
+
+template <int XOR>
+__device__ __forceinline__ uint32_t swizzle_xor(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (XOR << 10) | 0x1f);
+}
+
+// Per-lane constants of the lane <-> field transposes.  In stage s a lane keeps the fields whose
+// index bit s equals its own lane bit s and takes the others from lane ^ (1 << s), moved by
+// FIELD << s bits.  Moves of 8 or 16 bits are one byte permute; smaller ones a rotate and a
+// three-input select.
+template <int STAGES, int FIELD>
+struct TransposePlan {
+    uint32_t keep[STAGES];   // bit mask of the fields kept            (sub-byte stages)
+    uint32_t rot[STAGES];    // right-rotation applied to the partner  (sub-byte stages)
+    uint32_t sel[STAGES];    // v_perm selector {own, partner}         (byte and halfword stages)
+
+    __device__ __forceinline__ void init(int lane)
+    {
+#pragma unroll
+        for (int s = 0; s < STAGES; ++s) {
+            const int sh = FIELD << s;
+            uint32_t lo = 0;  // field positions whose index has bit s clear
+#pragma unroll
+            for (int f = 0; f < (1 << STAGES); ++f)
+                if (((f >> s) & 1) == 0)
+                    lo |= ((1u << FIELD) - 1u) << (f * FIELD);
+            const bool up = (lane >> s) & 1;
+            keep[s] = up ? ~lo : lo;
+            rot[s] = up ? (uint32_t)sh : (uint32_t)(32 - sh);
+            // v_perm_b32(partner, own, sel): selector bytes 0..3 pick from own, 4..7 from partner
+            if (sh == 8)
+                sel[s] = up ? 0x03070105u : 0x06020400u;
+            else if (sh == 16)
+                sel[s] = up ? 0x03020706u : 0x05040100u;
+            else
+                sel[s] = 0;
+        }
+    }
+
+    // After the call, field i of lane a holds what field a of lane i held (lanes modulo 2^STAGES).
+    __device__ __forceinline__ uint32_t apply(uint32_t d) const
+    {
+#pragma unroll
+        for (int s = 0; s < STAGES; ++s) {
+            uint32_t partner;
+            if (s == 0) partner = swizzle_xor<1>(d);
+            else if (s == 1) partner = swizzle_xor<2>(d);
+            else if (s == 2) partner = swizzle_xor<4>(d);
+            else if (s == 3) partner = swizzle_xor<8>(d);
+            else partner = swizzle_xor<16>(d);
+            if ((FIELD << s) >= 8) {
+                d = __builtin_amdgcn_perm(partner, d, sel[s]);
+            } else {
+                const uint32_t rotated = __builtin_amdgcn_alignbit(partner, partner, rot[s]);
+                // (keep & d) | (~keep & rotated) as one three-input bit operation
+                d = __builtin_amdgcn_bitop3_b32(keep[s], d, rotated, 0xCA);
+            }
+        }
+        return d;
+    }
+};
+
+// tile_stages for a block size known only at run time: the stages on index bits 5 .. 9 of one tile
+// (wave-uniform branches), and the stages that pair whole tiles, bits 10 and up, of G tiles.
+__device__ __forceinline__ void one_tile_stages(int log2n, float (&acc)[16])
+{
+    if (log2n > 5) {
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+            bfly(acc[r], acc[r + 1]);
+    }
+    if (log2n > 6) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (!(r & 2))
+                bfly(acc[r], acc[r + 2]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[r]), __float_as_uint(acc[r + 1]), false, false);
+        acc[r] = __uint_as_float(sw[0]);
+        acc[r + 1] = __uint_as_float(sw[1]);
+    }
+    if (log2n > 7) {
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+            bfly(acc[r], acc[r + 1]);
+    }
+    if (log2n > 8) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (!(r & 4))
+                bfly(acc[r], acc[r + 4]);
+    }
+    if (log2n > 9) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            bfly(acc[r], acc[r + 8]);
+    }
+}
+
+template <int G>
+__device__ __forceinline__ void tile_pair_stages(int log2n, float (&acc)[G][16])
+{
+#pragma unroll
+    for (int k = 0; (1 << k) < G; ++k)
+        if (log2n > 10 + k) {
+#pragma unroll
+            for (int u = 0; u < G; ++u)
+                if (!(u & (1 << k))) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        bfly(acc[u][r], acc[u | (1 << k)][r]);
+                }
+        }
+}
+
+// ---- the inverse transform's inputs and outputs
+
+__device__ __forceinline__ uint32_t pack_bf16_pair(float lo, float hi)
+{
+    v2bf p;
+    p[0] = (__bf16)lo;
+    p[1] = (__bf16)hi;
+    uint32_t u;
+    __builtin_memcpy(&u, &p, 4);
+    return u;
+}
+
+// zero the halves of `pair` whose mask bits (bit 0: low half, bit 1: high half) are clear
+__device__ __forceinline__ uint32_t keep_trusted(uint32_t pair, uint32_t mask_bits, int first_bit)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)mask_bits, first_bit, 1);      // 0 or ~0
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)mask_bits, first_bit + 1, 1);
+    return pair & __builtin_amdgcn_perm(hi, lo, 0x07060100u);   // low half from lo, high half from hi
 }
 
 }  // namespace quest

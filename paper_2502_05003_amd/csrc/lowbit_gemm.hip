@@ -818,18 +818,21 @@ int64_t lowbit_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int bits)
 
 hipError_t prepare_lowbit_gemm_kernels()
 {
-    hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_wide_kernel<4>), kWideLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_wide_kernel<3>), kWideLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_small_kernel<4>), kSmallLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_small_kernel<3>), kSmallLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_tile_kernel<4>), kTileLds);
-    if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_tile_kernel<3>), kTileLds);
-    return err;
+    static OncePerDevice once;
+    return once([] {
+        hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_wide_kernel<4>), kWideLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_wide_kernel<3>), kWideLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_small_kernel<4>), kSmallLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_small_kernel<3>), kSmallLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_tile_kernel<4>), kTileLds);
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(lowbit_gemm_tile_kernel<3>), kTileLds);
+        return err;
+    });
 }
 
 hipError_t launch_lowbit_gemm(const GemmArgs &args, hipStream_t stream)

@@ -626,25 +626,33 @@ quest_status quest_weight_only_gemm(const void *x, const uint8_t *w_codes, const
 
 quest_status quest_init(void)
 {
-    hipError_t err = quest::prepare_quantize_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_quantize_mfma_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_trust_backward_mfma_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_lowbit_gemm_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_fp4_gemm_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_trust_backward_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_grad_gemm_kernels();
-    if (err == hipSuccess)
-        err = quest::prepare_grad_gemm_mid_kernels();
-    void *ptr = nullptr;
-    if (err == hipSuccess)
-        err = static_scratch_address(&ptr);
-    return err == hipSuccess ? QUEST_OK : QUEST_ERR_LAUNCH;
+    static quest::OncePerDevice once;
+    const hipError_t status = once([]() -> hipError_t {
+        hipError_t err = quest::prepare_quantize_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_quantize_mfma_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_quantize_rows_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_trust_backward_rows_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_trust_backward_mfma_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_lowbit_gemm_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_fp4_gemm_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_trust_backward_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_grad_gemm_kernels();
+        if (err == hipSuccess)
+            err = quest::prepare_grad_gemm_mid_kernels();
+        void *ptr = nullptr;
+        if (err == hipSuccess)
+            err = static_scratch_address(&ptr);
+        return err;
+    });
+    return status == hipSuccess ? QUEST_OK : QUEST_ERR_LAUNCH;
 }
 
 }  // extern "C"

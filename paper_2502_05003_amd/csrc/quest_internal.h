@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/quest.h"
 
 namespace quest {
@@ -37,7 +39,11 @@ struct QuantizeArgs {
 
 hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream);
 // Matrix-core kernel for the common bf16 / 4-bit shapes; false means "not covered, nothing launched".
-bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream);
+bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream, bool query = false);
+
+// Matrix-core kernel for the other row lengths and blocks (run-time sizes): whether `rows` rows of an operand go there.
+bool quantize_rows_preferred(const QuantizeArgs &a, int64_t rows);
+hipError_t launch_hadamard_quantize_rows(const QuantizeArgs &a, hipStream_t stream);
 
 struct GemmArgs {
     const uint8_t *a_codes;
@@ -108,6 +114,10 @@ hipError_t launch_trust_backward(const BackwardArgs &a, hipStream_t stream);
 // Matrix-core kernel for bf16 in / bf16 out and the common shapes; false means "not covered".
 bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream);
 
+// Matrix-core kernel for the other row lengths and blocks (run-time sizes), bf16 in.
+bool trust_backward_rows_covers(const BackwardArgs &a);
+hipError_t launch_trust_backward_rows(const BackwardArgs &a, hipStream_t stream);
+
 struct GradGemmArgs {
     int which;
     const void *dy;
@@ -155,12 +165,39 @@ int device_compute_units();
 // change a kernel attribute or load code later).
 hipError_t prepare_quantize_kernels();
 hipError_t prepare_quantize_mfma_kernels();
+hipError_t prepare_quantize_rows_kernels();
+hipError_t prepare_trust_backward_rows_kernels();
 hipError_t prepare_trust_backward_mfma_kernels();
 hipError_t prepare_lowbit_gemm_kernels();
 hipError_t prepare_fp4_gemm_kernels();
 hipError_t prepare_trust_backward_kernels();
 hipError_t prepare_grad_gemm_kernels();
 hipError_t prepare_grad_gemm_mid_kernels();
+
+// Runs a set-up step until it has succeeded once on the current device; afterwards the cost is the question
+// which device that is (a call's path through the locks and look-ups of six limits was 0.5 us).  Safe
+// from several threads: a step may run more than once, they are all idempotent.
+class OncePerDevice {
+public:
+    template <typename Step>
+    hipError_t operator()(Step &&step)
+    {
+        int device = 0;
+        hipError_t err = hipGetDevice(&device);
+        if (err != hipSuccess)
+            return err;
+        const uint64_t bit = device >= 0 && device < 64 ? uint64_t(1) << device : 0;
+        if (done_.load(std::memory_order_acquire) & bit)
+            return hipSuccess;
+        err = step();
+        if (err == hipSuccess)
+            done_.fetch_or(bit, std::memory_order_release);
+        return err;
+    }
+
+private:
+    std::atomic<uint64_t> done_{0};
+};
 
 // Raise the dynamic LDS limit of `kernel` to `bytes` on the current device.  The attribute is set
 // once per (kernel, device, size) and remembered; safe to call from several host threads.

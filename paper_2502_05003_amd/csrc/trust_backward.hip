@@ -93,6 +93,8 @@ hipError_t launch_trust_backward(const BackwardArgs &a, hipStream_t stream)
         // two gradients: one launch where the matrix-core kernel covers the shape, else one after the other
         if (a.rows != 0 && launch_trust_backward_mfma(a, stream))
             return hipGetLastError();
+        if (a.rows != 0 && trust_backward_rows_covers(a))
+            return launch_trust_backward_rows(a, stream);
         BackwardArgs first = a, second = a;
         first.g2 = nullptr;
         first.rows2 = 0;
@@ -109,6 +111,8 @@ hipError_t launch_trust_backward(const BackwardArgs &a, hipStream_t stream)
         return hipSuccess;
     if (launch_trust_backward_mfma(a, stream))
         return hipGetLastError();
+    if (trust_backward_rows_covers(a))
+        return launch_trust_backward_rows(a, stream);
     if (a.g_dtype == QUEST_BF16)
         return a.out_dtype == QUEST_BF16 ? launch_generic<uint16_t, uint16_t>(a, stream)
                                          : launch_generic<uint16_t, float>(a, stream);

@@ -20,31 +20,12 @@
 namespace quest {
 namespace {
 
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxBlocks = 1024;   // four workgroups of four waves per compute unit, each wave walking over its rows
 constexpr int kThreads = 256;
 constexpr int kRowsPerBlock = kThreads / 64;
-
-__device__ __forceinline__ uint32_t pack_bf16_pair(float lo, float hi)
-{
-    v2bf p;
-    p[0] = (__bf16)lo;
-    p[1] = (__bf16)hi;
-    uint32_t u;
-    __builtin_memcpy(&u, &p, 4);
-    return u;
-}
-
-// zero the halves of `pair` whose mask bits (bit 0: low half, bit 1: high half) are clear
-__device__ __forceinline__ uint32_t keep_trusted(uint32_t pair, uint32_t mask_bits, int first_bit)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)mask_bits, first_bit, 1);      // 0 or ~0
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)mask_bits, first_bit + 1, 1);
-    return pair & __builtin_amdgcn_perm(hi, lo, 0x07060100u);   // low half from lo, high half from hi
-}
 
 // Rows of whole 1 KiB pieces, at most 4096 elements (four workgroups' buffers fit a CU's LDS), and few
 // enough stores per row and lane for the wait on the vector-memory counter to tell them from the
@@ -288,11 +269,13 @@ hipError_t prepare_trust_backward_mfma_kernels()
 }
 
 // Launches the matrix-core kernel if it covers the call; returns false (nothing launched) otherwise.
-// Covered (U = row length / 128): bf16 in; bf16 out for rows of 512, 1024, 2048, 4096, 5632 or 11008
-// elements with a Hadamard block of at most 32, or 128, 256 (11008 only), 512, 1024, 2048, 4096 where
-// it divides the row, and for the other widths of the paper's model family (640, 768, 1280, 1664,
-// 1792, 2816, 3584, 4608) with a block of at most 32 or their widest one; fp32 out (a weight
-// gradient for an fp32 optimizer) for all of these row lengths with their widest block.
+// Covered (U = row length / 128): bf16 in; bf16 out for rows of 512, 1024, 2048 or 4096 elements with a
+// Hadamard block of at most 32, or 128, 512, 1024, 2048, 4096 where it divides the row, and for the
+// shorter of the other widths of the paper's model family (640, 768, 1280, 1664, 1792, 2816) with a block
+// of at most 32 or their widest one; fp32 out (a weight gradient for an fp32 optimizer) for all of these
+// row lengths with their widest block.  Longer rows are better off in the kernel that deals out
+// groups of tiles (trust_backward_rows.hip), measured against instantiations here: 8192 x 5632 37 us against 39,
+// 8192 x 11008 71 against 77, 333 x 5632 4.4 against 6.2; 8192 x 1792 14.3 against 13.2.
 bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
 {
     if (a.g_dtype != QUEST_BF16 || (a.cols % 128) != 0)
@@ -306,9 +289,8 @@ bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
         return true;                               \
     }
         QUEST_F32_OUT_CASE(4, 9) QUEST_F32_OUT_CASE(8, 10) QUEST_F32_OUT_CASE(16, 11) QUEST_F32_OUT_CASE(32, 12)
-        QUEST_F32_OUT_CASE(44, 9) QUEST_F32_OUT_CASE(86, 8)
         QUEST_F32_OUT_CASE(5, 7) QUEST_F32_OUT_CASE(6, 8) QUEST_F32_OUT_CASE(10, 8) QUEST_F32_OUT_CASE(13, 7)
-        QUEST_F32_OUT_CASE(14, 8) QUEST_F32_OUT_CASE(22, 8) QUEST_F32_OUT_CASE(28, 9) QUEST_F32_OUT_CASE(36, 9)
+        QUEST_F32_OUT_CASE(14, 8) QUEST_F32_OUT_CASE(22, 8)
 #undef QUEST_F32_OUT_CASE
         return false;
     }
@@ -321,12 +303,9 @@ bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
     QUEST_CASE(8, 5) QUEST_CASE(8, 7) QUEST_CASE(8, 9) QUEST_CASE(8, 10)
     QUEST_CASE(16, 5) QUEST_CASE(16, 7) QUEST_CASE(16, 9) QUEST_CASE(16, 10) QUEST_CASE(16, 11)
     QUEST_CASE(32, 5) QUEST_CASE(32, 7) QUEST_CASE(32, 9) QUEST_CASE(32, 10) QUEST_CASE(32, 11) QUEST_CASE(32, 12)
-    QUEST_CASE(44, 5) QUEST_CASE(44, 7) QUEST_CASE(44, 9)
-    QUEST_CASE(86, 5) QUEST_CASE(86, 7) QUEST_CASE(86, 8)   // 11008 = 86 x 128: ends three quarters into a tile
-    // the other widths of the paper's models (hidden 640 .. 1664, MLP 1792 .. 4608): no transform / widest block
+    // the other widths of the paper's models (hidden 640 .. 1664, MLP 1792, 2816): no transform / widest block
     QUEST_CASE(5, 5) QUEST_CASE(5, 7) QUEST_CASE(6, 5) QUEST_CASE(6, 8) QUEST_CASE(10, 5) QUEST_CASE(10, 8)
     QUEST_CASE(13, 5) QUEST_CASE(13, 7) QUEST_CASE(14, 5) QUEST_CASE(14, 8) QUEST_CASE(22, 5) QUEST_CASE(22, 8)
-    QUEST_CASE(28, 5) QUEST_CASE(28, 9) QUEST_CASE(36, 5) QUEST_CASE(36, 9)
 #undef QUEST_CASE
     return false;
 }

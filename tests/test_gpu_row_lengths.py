@@ -1,0 +1,87 @@
+"""The quantizer and the masked inverse transform at row lengths and blocks without an instantiation of
+their own (csrc/hadamard_quantize_rows.hip, csrc/trust_backward_rows.hip) against the CPU oracle: rows that
+end anywhere in a tile, every kind of block, one and several rows per wave, rows shared by a workgroup."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import quest_oracle as qo
+from paper_2502_05003_amd import binding as q
+from paper_2502_05003_amd import synth
+
+from gpu_util import BF16_HALF_ULP, DEV, compare_quantizer, compare_quantizer_fp4, gpu_quantize, to_device, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+#        rows, row length, block: one tile or less, an odd multiple of 64; ends in a tile; two and four tiles
+#        per block; more rows than resident waves (4096) or row-sharing workgroups (1024)
+#        (fewer than 256 rows: other kernels)
+SHAPES = [(256, 64, 64), (300, 192, 2), (257, 960, 64), (261, 1088, 16), (333, 2560, 512), (259, 6144, 2048),
+          (256, 8192, 4096), (1031, 3136, 64), (4201, 1536, 512), (1100, 5760, 128)]
+
+
+# b = 8: an fp32 rounding near the top of the grid is 8e-6 of a cell, so a few codes in a million differ, and the
+# bar's 1e-5 of the elements plus one needs millions of elements to be a bound and not a matter of luck.
+CASES = [(*shape, dtype, grid) for shape in SHAPES for dtype in ("bf16", "f32") for grid in (1, 2, 3, 4, 8, "fp4")
+         if grid != 8 or shape[0] * shape[1] > 3000000]
+
+
+@pytest.mark.parametrize("rows,cols,n,dtype,grid", CASES)
+def test_quantizer(rows, cols, n, dtype, grid):
+    x = synth.outlier_activations(rows, cols, 0.01, 20.0, seed=rows + cols, dtype=dtype)
+    x[rows // 2] = 0
+    if grid == "fp4":
+        got = gpu_quantize(x, n, 4, fp4=True, want_xh=False)
+        compare_quantizer_fp4(got, qo.hadamard_quantize_fp4(x, n), cols)
+    else:
+        got = gpu_quantize(x, n, grid, want_xh=(grid == 3))
+        compare_quantizer(got, qo.hadamard_quantize(x, n, grid), cols, grid)
+
+
+def test_quantizer_strided_rows_and_no_mask():
+    """A row pitch above the row length; the codes do not depend on whether the mask is asked for."""
+    x = synth.outlier_activations(270, 2560, 0.01, 20.0, seed=1, dtype="bf16")
+    with_mask, without = gpu_quantize(x, 512, 4, want_xh=False), gpu_quantize(x, 512, 4, want_xh=False, want_mask=False, ld=2568)
+    assert np.array_equal(with_mask["codes"], without["codes"])
+    assert np.array_equal(with_mask["scales"], without["scales"])
+
+
+@pytest.mark.parametrize("rows_x,rows_w", [(400, 300), (3000, 500), (3000, 40), (0, 300)])
+def test_pairs_equal_single_calls(rows_x, rows_w):
+    cols, n = 2560, 512
+    x, w = (torch.randn(r, cols, device=DEV).bfloat16() for r in (rows_x + 1, rows_w))
+    x = x[:rows_x]
+    def buffers(r):
+        return dict(codes=torch.full((r, cols // 2), 0xAA, dtype=torch.uint8, device=DEV),
+                    scales=torch.full((r,), -1.0, device=DEV), mask=torch.full((r, cols // 8), 0x55, dtype=torch.uint8, device=DEV))
+    pair, single = (buffers(rows_x), buffers(rows_w)), (buffers(rows_x), buffers(rows_w))
+    q.quest_hadamard_quantize_pair(x, w, n, 4, **{f"x_{k}": v for k, v in pair[0].items()},
+                                   **{f"w_{k}": v for k, v in pair[1].items()})
+    for t, out in ((x, single[0]), (w, single[1])):
+        if t.shape[0]:
+            q.quest_hadamard_quantize(t, n, 4, **out)
+    dx = [torch.full((r, cols), 7.0, dtype=torch.bfloat16, device=DEV) for r in (rows_x, rows_w, rows_x, rows_w)]
+    q.quest_trust_backward_pair(x, pair[0]["mask"], w, pair[1]["mask"], n, out_x=dx[0], out_w=dx[1])
+    for t, m, out in ((x, pair[0]["mask"], dx[2]), (w, pair[1]["mask"], dx[3])):
+        if t.shape[0]:
+            q.quest_trust_backward(t, m, n, out=out)
+    torch.cuda.synchronize()
+    for a, b in zip(pair, single):     # the same bits, whether a row is one wave's or shared by a workgroup
+        assert all(torch.equal(a[k], b[k]) for k in a)
+    assert torch.equal(dx[0], dx[2]) and torch.equal(dx[1], dx[3])
+
+
+@pytest.mark.parametrize("od", ["bf16", "f32"])
+@pytest.mark.parametrize("masked", [True, False])
+@pytest.mark.parametrize("rows,cols,n", SHAPES + [(3, 5632, 512), (9, 11008, 256), (5, 3584, 4), (3, 12288, 4096), (1, 64, 1)])
+def test_inverse_transform(rows, cols, n, masked, od):
+    g = synth.gaussian(rows, cols, 0.03, seed=rows + cols, dtype="bf16")
+    trust = (np.random.default_rng(cols).random((rows, cols)) < 0.9).astype(np.uint8)
+    packed = np.packbits(trust, axis=1, bitorder="little")
+    out = torch.full((rows, cols), float("nan"), dtype=torch.bfloat16 if od == "bf16" else torch.float32, device=DEV)
+    q.quest_trust_backward(to_device(g), to_device(packed) if masked else None, n, out=out)
+    torch.cuda.synchronize()
+    ref = qo.trust_backward(qo.widen(g), trust if masked else np.ones_like(trust), n)
+    scale = np.sqrt(np.mean(ref * ref, axis=1, keepdims=True))
+    rounding = BF16_HALF_ULP if od == "bf16" else 0.0
+    assert np.all(np.abs(to_host_f64(out) - ref) <= rounding * np.abs(ref) + 1e-5 * scale + 1e-30)
