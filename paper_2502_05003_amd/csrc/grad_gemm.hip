@@ -28,18 +28,35 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 //
 // 256 x 256 outputs per workgroup, four waves of 128 x 128 (sixteen 32 x 32 fp32 accumulator
 // tiles, one wave per SIMD), 32 contraction elements per step, a ring of LDS stages of 32 KiB that
-// the transfers fill several steps ahead of the step being multiplied.  An operand whose rows are
+// the transfers fill several steps ahead of the step being multiplied.  The same with tiles of 192, 128 and 64
+// rows (TI = 3, 2, 1) for outputs whose tiles of 256 would leave compute units idle or need splitting: one
+// and the same loop, fewer accumulators.  A step costs 0.78, 0.59, 0.41, 0.28 us with the chip full, so
+// the smaller tiles give away 1, 5 and 40 % per operation.  Before, whole or split tiles of 256 only, and now
+// (us per call, the expansion included; tokens x N x K):
+//   G_w 16384 x 5632 x 2048: 342 (split) -> 318 (30 x 8 tiles of 192)    G_x 4096 x 6912 x 2560: 167 (split) -> 136
+//   G_x 4096 x 5632 x 2048: 111 (split) -> 90 (tiles of 128)             weight-only 4096 x 5632 x 2048: 133 -> 107
+//   G_w 4096 x 6912 x 2560: 184 (split) -> 147                           G_w 16384 x 1664 x 1664: 169 -> 146 (64)  An operand whose rows are
 // contraction rows in memory ([c][k]: the expanded operand, and dy for which = 1) is staged as it
 // is and read with the transposing LDS load, which hands each lane four contraction elements of
 // one column; an operand whose rows are output rows (dy for which = 0) is read with 128-bit loads.
 // ------------------------------------------------------------------------------------------
 
-constexpr int GT = 256;                        // tile edge
+constexpr int GT = 256;                        // tile columns, and rows of the largest tile
 constexpr int GC = 32;                         // contraction elements per step
 constexpr int kGemmThreads = 256;
-constexpr int kOperandBytes = GT * GC * 2;     // 16 KiB per operand and step
-constexpr int kGStage = 2 * kOperandBytes;     // left operand, then right operand
-constexpr int kParkBytes = 4 * 32768;          // epilogue: 32 KiB per wave
+constexpr int kRightBytes = GT * GC * 2;       // right operand of one step
+
+// TI: accumulator tiles of a wave along the rows: tiles of 64 TI rows
+template <int TI>
+struct TileSizes {
+    static constexpr int kRows = 64 * TI;
+    static constexpr int kLeftBytes = kRows * GC * 2;
+    static constexpr int kStage = kLeftBytes + kRightBytes;   // left operand, then right operand
+    static constexpr int kStages = 160 * 1024 / kStage;       // ring of stages: 5 (TI = 4, 3), 6, 8
+    static constexpr int kLds = kStages * kStage;
+    static constexpr int kParkBytes = 4 * (32 * TI) * 256;    // epilogue: 32 TI rows of 256 bytes per wave
+    static_assert(kParkBytes <= kLds && kLds <= 160 * 1024, "the epilogue reuses the stages");
+};
 
 typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 
@@ -49,16 +66,28 @@ struct ReadOp {
     bool left;
     int idx, half;
 };
-// right fragment j feeds matrix instructions j, 4 + j, ..., left fragment i instructions 4 i .. 4 i + 3
-constexpr ReadOp kReadsTransposed[16] = {{false, 0, 0}, {false, 0, 1}, {true, 0, 0},  {true, 0, 1},
-                                         {false, 1, 0}, {false, 1, 1}, {false, 2, 0}, {false, 2, 1},
-                                         {false, 3, 0}, {false, 3, 1}, {true, 1, 0},  {true, 1, 1},
-                                         {true, 2, 0},  {true, 2, 1},  {true, 3, 0},  {true, 3, 1}};
-constexpr ReadOp kReadsRows[8] = {{false, 0, -1}, {true, 0, -1}, {false, 1, -1}, {false, 2, -1},
-                                  {false, 3, -1}, {true, 1, -1},  {true, 2, -1},  {true, 3, -1}};
-constexpr ReadOp kReadsPlain[12] = {{false, 0, 0}, {false, 0, 1}, {true, 0, -1}, {false, 1, 0},
-                                    {false, 1, 1}, {false, 2, 0}, {false, 2, 1}, {false, 3, 0},
-                                    {false, 3, 1}, {true, 1, -1}, {true, 2, -1}, {true, 3, -1}};
+// The reads of one k-step in the order the matrix instructions want them: right fragment j feeds
+// instructions j, 4 + j, .., left fragment i instructions 4 i .. 4 i + 3.
+template <int MODE, int TI>
+struct ReadOrder {
+    static constexpr bool kLeftHalves = MODE == 1, kRightHalves = MODE != 2;   // transposing reads come in halves
+    static constexpr int kCount = TI * (kLeftHalves ? 2 : 1) + 4 * (kRightHalves ? 2 : 1);
+    ReadOp op[kCount];
+    constexpr ReadOrder() : op{}
+    {
+        int n = 0;
+        for (int f = 0; f < TI + 4; ++f) {   // R0 L0 R1 R2 R3 L1 ..
+            const bool left = f == 1 || f > 4;
+            const int idx = left ? (f == 1 ? 0 : f - 4) : (f == 0 ? 0 : f - 1);
+            if (left ? kLeftHalves : kRightHalves) {
+                op[n++] = {left, idx, 0};
+                op[n++] = {left, idx, 1};
+            } else {
+                op[n++] = {left, idx, -1};
+            }
+        }
+    }
+};
 
 // Expands packed codes to bf16(fp32(s * u)), u = 2 c - (L - 1): eight elements per thread.
 // levels = 0 stands for E2M1 codes (Sec. 4.4): u is then the signed E2M1 value of the code.
@@ -123,15 +152,15 @@ __global__ __launch_bounds__(256) void expand_codes_kernel(const uint8_t *__rest
 // that they share the fetch through that XCD's L2.  phase_period = 0: whole tiles, all in phase.
 constexpr int kSlotQuads = 4 * 64 * 64;   // float4 per partial tile (256 KiB)
 
-__device__ __forceinline__ void tile_origin(int tile, int tiles_r, int tiles_k, int phase_period, int &r0,
+__device__ __forceinline__ void tile_origin(int tile, int tile_rows, int tiles_r, int tiles_k, int phase_period, int &r0,
                                             int &k0)
 {
     if (phase_period != 0) {   // split tiles: plain order along the longer side of the tile grid
         if (tiles_k > tiles_r) {
-            r0 = (tile / tiles_k) * GT;
+            r0 = (tile / tiles_k) * tile_rows;
             k0 = (tile % tiles_k) * GT;
         } else {
-            r0 = (tile % tiles_r) * GT;
+            r0 = (tile % tiles_r) * tile_rows;
             k0 = (tile / tiles_r) * GT;
         }
         return;
@@ -140,7 +169,7 @@ __device__ __forceinline__ void tile_origin(int tile, int tiles_r, int tiles_k, 
     const int band = tile / (4 * tiles_k);
     const int band_rows = min(4, tiles_r - band * 4);
     const int in_band = tile - band * 4 * tiles_k;
-    r0 = (band * 4 + in_band % band_rows) * GT;
+    r0 = (band * 4 + in_band % band_rows) * tile_rows;
     k0 = (in_band / band_rows) * GT;
 }
 
@@ -150,7 +179,7 @@ __device__ __forceinline__ void tile_origin(int tile, int tiles_r, int tiles_k, 
  *             c ^ ((r >> 2) & 3).  Lane l of a 128-bit fragment read takes row l % 32 and chunk
  *             2 ks + l / 32 of k-step ks.
  *   column form [32 contraction rows][32 chunks of 8 columns]: chunk c of contraction row q sits at
- *             chunk c ^ ((q & 3) << 2).  A transposing 64-bit read works on 16 lanes: lanes 4 a ..
+ *             chunk c ^ column_swz(q).  A transposing 64-bit read works on 16 lanes: lanes 4 a ..
  *             4 a + 3 point at contraction row a of a block of four, sixteen columns wide, and lane
  *             i receives column i of it (four contraction elements).  Two such reads give a lane
  *             its eight contraction elements of one matrix-instruction operand.
@@ -166,9 +195,18 @@ __device__ __forceinline__ void tile_origin(int tile, int tiles_r, int tiles_k, 
  * R and K need not be whole tiles: the transfers of an edge tile fetch the last rows or columns
  * that exist in place of those that do not (results of those positions are never stored).
  */
+template <int EDGE>
+__device__ __forceinline__ int column_swz(int crow)
+{
+    // rows of 512 or 256 bytes all start at the same bank: four contraction rows apart by 64 bytes; rows of
+    // 384 or 128 bytes alternate between two starts 128 bytes apart: the second pair moves by 64
+    static_assert(EDGE == 64 || EDGE == 128 || EDGE == 192 || EDGE == 256, "tile edge");
+    return EDGE % 128 != 0 ? ((crow >> 1) & 1) << 2 : (crow & 3) << 2;
+}
+
 constexpr int kSpreadModes = 5;   // bit m: MODE m spreads its transfers over the whole step (measured, see below)
 
-template <int MODE, int STAGES>
+template <int MODE, int TI>
 __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     const uint16_t *__restrict__ dy, int64_t ld_dy, const uint16_t *__restrict__ qhat, int64_t ld_right,
     int C, int R, int K, int tiles_r, int tiles_k, int per_block, int phase_period, uint16_t *__restrict__ out,
@@ -177,7 +215,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     constexpr bool TRANSPOSED = MODE == 1;   // left operand in column form
     constexpr bool RIGHT_ROWS = MODE == 2;   // right operand in row form
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    static_assert(STAGES * kGStage >= kParkBytes, "the epilogue reuses the stages");
+    typedef TileSizes<TI> Sizes;
+    constexpr int STAGES = Sizes::kStages, kGStage = Sizes::kStage, kLeftBytes = Sizes::kLeftBytes;
+    constexpr int kTransfers = TI + 4;        // per wave and step
+    constexpr int kHalf = 4 * TI;             // matrix instructions per k-step
 
     const int steps = C / GC;
     const int64_t total_units = (int64_t)tiles_r * tiles_k * steps;
@@ -208,29 +249,29 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     //   column form, fragment j, k-step ks, half t:  col_off[j] + 512 (16 ks + 4 t)
     // (column form: lane group g = l / 16 covers columns 16 (g % 2) .. + 16 and contraction rows
     //  8 (g / 2) .. of the k-step; lane i of the group points at row i / 4, columns 4 (i % 4) ..)
-    auto column_offsets = [&](int w, uint32_t (&off)[4]) {
+    auto column_offsets = [&](auto edge, int w, auto &off) {   // wave w's fragments of 32 columns
+        constexpr int kEdge = decltype(edge)::value, kFragments = kEdge / 64;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < kFragments; ++j) {
             const int crow = 8 * (lg >> 1) + (l16 >> 2);
-            const int chunk = ((4 * w + (j ^ (l16 >> 2))) << 2) + 2 * (lg & 1) + ((l16 >> 1) & 1);
-            off[j] = (uint32_t)(crow * 512 + chunk * 16 + 8 * (l16 & 1));
+            const int chunk = (4 * (kFragments * w + j) + 2 * (lg & 1) + ((l16 >> 1) & 1)) ^ column_swz<kEdge>(l16 >> 2);
+            off[j] = (uint32_t)(crow * 2 * kEdge + chunk * 16 + 8 * (l16 & 1));
         }
     };
-    auto row_offsets = [&](int w, uint32_t (&off)[4]) {
+    auto row_offsets = [&](int first_row, auto &off) {
         const int x = (lm >> 2) & 3;
-        off[0] = (uint32_t)((w * 128 + lm) * 64 + ((lh ^ x) << 4));
-        off[1] = (uint32_t)((w * 128 + lm) * 64 + (((2 + lh) ^ x) << 4));
-        off[2] = off[3] = 0;
+        off[0] = (uint32_t)((first_row + lm) * 64 + ((lh ^ x) << 4));
+        off[1] = (uint32_t)((first_row + lm) * 64 + (((2 + lh) ^ x) << 4));
     };
     uint32_t left_off[4], right_off[4];
-    if (RIGHT_ROWS)
-        row_offsets(wc, right_off);
+    if constexpr (RIGHT_ROWS)
+        row_offsets(wc * 128, right_off);
     else
-        column_offsets(wc, right_off);
-    if (TRANSPOSED)
-        column_offsets(wr, left_off);
+        column_offsets(std::integral_constant<int, GT>{}, wc, right_off);
+    if constexpr (TRANSPOSED)
+        column_offsets(std::integral_constant<int, 64 * TI>{}, wr, left_off);
     else
-        row_offsets(wr, left_off);
+        row_offsets(wr * 32 * TI, left_off);
 
     for (int64_t unit = unit_begin; unit < unit_end;) {
     const int tile = (int)(unit / steps);
@@ -238,70 +279,74 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     const int s_end = (int)min((int64_t)steps, unit_end - (int64_t)tile * steps);
     unit += s_end - s_begin;
     int r0, k0;
-    tile_origin(tile, tiles_r, tiles_k, phase_period, r0, k0);
-    // Transfers: piece q (0..3) of an operand is the 1 KiB at offset (4 q + wave) KiB.  Per-lane
-    // byte offsets from the operand's position of the step:
+    tile_origin(tile, Sizes::kRows, tiles_r, tiles_k, phase_period, r0, k0);
+    // Transfers: piece q of an operand is the 1 KiB at offset (4 q + wave) KiB; lane l of it lands at 16 l.
+    // Per-lane byte offsets from the operand's position of the step:
     //   row form:    row 16 (4 q + wave) + l / 4, chunk (l % 4) ^ ((l / 16) & 3)
-    //   column form: contraction row 2 (4 q + wave) + l / 32, chunk (l % 32) ^ ((2 wave + l / 32) & 3) << 2
+    //   column form: the (64 (4 q + wave) + l)-th chunk of the step: contraction row and slot by the row length
     // with rows and columns beyond the output's edge replaced by the last ones inside it.
-    uint32_t left_voff[4], right_voff[4];
+    uint32_t left_voff[TI], right_voff[4];
     {
         const int rows_left = R - r0, cols_left = K - k0;   // what exists of this tile: >= 64, multiples of 8
+        const uint32_t row_form_chunk = (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+        auto column_form = [&](auto edge, int piece, int64_t ld, int exists) {
+            constexpr int kEdge = decltype(edge)::value;
+            const int at = 64 * piece + lane, crow = at / (kEdge / 8), slot = at % (kEdge / 8);
+            const int column = (slot ^ column_swz<kEdge>(crow)) * 8;    // first of the chunk's eight columns
+            return (uint32_t)crow * (uint32_t)ld * 2u + (uint32_t)min(column, exists - 8) * 2u;
+        };
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int piece = 4 * q + wave;
-            const int crow = 2 * piece + lh;
-            const int column = ((lane & 31) ^ ((crow & 3) << 2)) * 8;    // first of the chunk's eight columns
-            const int row_form_row = 16 * piece + (lane >> 2);
-            const uint32_t row_form_chunk = (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
-            right_voff[q] = RIGHT_ROWS ? (uint32_t)min(row_form_row, cols_left - 1) * (uint32_t)ld_right * 2u + row_form_chunk
-                                       : (uint32_t)crow * (uint32_t)ld_right * 2u + (uint32_t)min(column, cols_left - 8) * 2u;
-            left_voff[q] = TRANSPOSED ? (uint32_t)crow * (uint32_t)ld_dy * 2u + (uint32_t)min(column, rows_left - 8) * 2u
-                                      : (uint32_t)min(row_form_row, rows_left - 1) * (uint32_t)ld_dy * 2u + row_form_chunk;
+            const int piece = 4 * q + wave, row = 16 * piece + (lane >> 2);
+            right_voff[q] = RIGHT_ROWS ? (uint32_t)min(row, cols_left - 1) * (uint32_t)ld_right * 2u + row_form_chunk
+                                       : column_form(std::integral_constant<int, GT>{}, piece, ld_right, cols_left);
+            if (q < TI)
+                left_voff[q] = TRANSPOSED ? column_form(std::integral_constant<int, 64 * TI>{}, piece, ld_dy, rows_left)
+                                          : (uint32_t)min(row, rows_left - 1) * (uint32_t)ld_dy * 2u + row_form_chunk;
         }
     }
     // operand positions of contraction step 0 (wave-uniform)
     const char *left_base = reinterpret_cast<const char *>(TRANSPOSED ? dy + r0 : dy + (int64_t)r0 * ld_dy);
     const char *right_base = reinterpret_cast<const char *>(RIGHT_ROWS ? qhat + (int64_t)k0 * ld_right : qhat + k0);
 
-    v16f acc[4][4];
+    v16f acc[TI][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = 0.0f;
 
-    // eight transfers per wave fill the stage at LDS byte address `stage` with contraction step `step`
+    // TI + 4 transfers per wave fill the stage at LDS byte address `stage` with contraction step `step`
     auto transfer = [&](auto pc, uint32_t stage, int step) {
         constexpr int p = decltype(pc)::value;
         const int at = min(step, s_end - 1);   // past the end: a valid step again, never used
-        if constexpr (p < 4)
+        if constexpr (p < TI)
             lds_dma16(left_base + at * left_step, left_voff[p], stage + (4 * p + wave_u) * 1024);
         else
-            lds_dma16(right_base + at * right_step, right_voff[p - 4],
-                      stage + kOperandBytes + (4 * (p - 4) + wave_u) * 1024);
+            lds_dma16(right_base + at * right_step, right_voff[p - TI],
+                      stage + kLeftBytes + (4 * (p - TI) + wave_u) * 1024);
     };
 
     // the same from operand positions that the caller keeps up to date
     // (`wave_stage`: LDS byte address of the stage plus 1024 * wave)
     auto transfer_from = [&](auto pc, uint32_t wave_stage, const char *left_at, const char *right_at) {
         constexpr int p = decltype(pc)::value;
-        if constexpr (p < 4)
+        if constexpr (p < TI)
             lds_dma16_at<4096 * p>(left_at, left_voff[p], wave_stage);
         else
-            lds_dma16_at<kOperandBytes + 4096 * (p - 4)>(right_at, right_voff[p - 4], wave_stage);
+            lds_dma16_at<kLeftBytes + 4096 * (p - TI)>(right_at, right_voff[p - TI], wave_stage);
     };
 
     // fragments as halves of four contraction elements: [k-step][fragment][half]
-    v4bf lf[2][4][2], rf[2][4][2];
+    v4bf lf[2][TI][2], rf[2][4][2];
     // read number n of k-step ks out of `stage`, in the order the matrix instructions want them
     auto load_frag = [&](auto nc, const uint8_t *stage, auto ksc) {
         constexpr int ks = decltype(ksc)::value;
-        constexpr ReadOp op = (MODE == 1 ? kReadsTransposed : MODE == 0 ? kReadsPlain : kReadsRows)[decltype(nc)::value];
+        constexpr ReadOp op = ReadOrder<MODE, TI>().op[decltype(nc)::value];
         if constexpr (op.half < 0) {
-            const uint32_t off = (op.left ? left_off[ks] : kOperandBytes + right_off[ks]) + 2048 * op.idx;
+            const uint32_t off = (op.left ? left_off[ks] : kLeftBytes + right_off[ks]) + 2048 * op.idx;
             const v8bf v = *reinterpret_cast<const v8bf *>(stage + off);
             if constexpr (op.left) {
                 lf[ks][op.idx][0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
@@ -311,8 +356,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
                 rf[ks][op.idx][1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
             }
         } else {
-            const uint32_t off = (op.left ? left_off[op.idx] : kOperandBytes + right_off[op.idx]) +
-                                 512 * (16 * ks + 4 * op.half);
+            const uint32_t off = (op.left ? left_off[op.idx] : kLeftBytes + right_off[op.idx]) +
+                                 2 * (op.left ? Sizes::kRows : GT) * (16 * ks + 4 * op.half);
             const v4bf v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
                 (__attribute__((address_space(3))) v4bf *)(stage + off));
             if constexpr (op.left)
@@ -321,7 +366,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
                 rf[ks][op.idx][op.half] = v;
         }
     };
-    constexpr int kReads = MODE == 1 ? 16 : MODE == 0 ? 12 : 8;
+    constexpr int kReads = ReadOrder<MODE, TI>::kCount;
+    // read numbers [reads_before(k), reads_before(k + 1)) of a k-step go behind its k-th matrix instruction
+    auto reads_before = [](int k) constexpr { return kReads <= kHalf ? (k < kReads ? k : kReads) : k * kReads / kHalf; };
 
     // Ring of STAGES stages: while step s is multiplied out of stage s % STAGES, the transfers of the
     // next steps are in flight or done.  Two ways to refill:
@@ -334,12 +381,19 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     // one box, 334 instead of 338 on another) and 0-1 % slower when both operands are in column form.
     constexpr bool kSpread = kSpreadModes & (1 << MODE);
     constexpr int kAhead = kSpread ? STAGES - 2 : STAGES - 1;   // steps in flight beyond the current one
+    // the matrix instruction behind which transfer p is issued
+    auto transfer_slot = [](int p) constexpr {
+        return kSpread ? p * 2 * kHalf / kTransfers : kHalf + p * kHalf / kTransfers;
+    };
+    constexpr int kIssuedAtWait = kSpread ? (kTransfers + 1) / 2 : 0;   // transfers of this step before its wait
+    static_assert(transfer_slot(kIssuedAtWait) >= kHalf && (kIssuedAtWait == 0 || transfer_slot(kIssuedAtWait - 1) < kHalf),
+                  "the wait counts the transfers issued before it");
     static_for<kAhead>([&](auto sc) {
-        static_for<8>([&](auto pc) {
+        static_for<kTransfers>([&](auto pc) {
             transfer(pc, smem_addr + decltype(sc)::value * kGStage, s_begin + decltype(sc)::value);
         });
     });
-    wait_vmcnt<8 * (kAhead - 1)>();
+    wait_vmcnt<kTransfers * (kAhead - 1)>();
     __builtin_amdgcn_s_barrier();
     static_for<kReads>([&](auto nc) { load_frag(nc, smem, std::integral_constant<int, 0>{}); });
 
@@ -357,36 +411,39 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
         const int nxt_off = cur_off + kGStage == kRing ? 0 : cur_off + kGStage;
         const uint8_t *nxt_stage = smem + nxt_off;
         const uint32_t refill = smem_addr + refill_off + wave_u * 1024;
-        // 32 matrix instructions; each is followed by one slice of the other work, pinned in place:
+        // 8 TI matrix instructions; each is followed by one slice of the other work, pinned in place
+        // (figures for TI = 4):
         //    0..15  fragment reads of the step's second k-step
         //   15      transfers of step + 1 have landed (all but the newer groups), barrier
         //   16..31  fragment reads of the next step's first k-step
         //   16, 18, .. 30 (late) or 0, 4, .. 28 (spread)  transfers of a later step (never back to back:
         //           a wave issues in order, and a transfer that finds the memory pipeline's queue full
         //           holds up the MFMAs behind it)
-        static_for<32>([&](auto kc) {
+        static_for<2 * kHalf>([&](auto kc) {
             constexpr int k = decltype(kc)::value;
-            constexpr int ks = k >> 4, i = (k >> 2) & 3, j = k & 3;
+            constexpr int ks = k / kHalf, i = (k % kHalf) >> 2, j = k & 3;
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                 __builtin_shufflevector(rf[ks][j][0], rf[ks][j][1], 0, 1, 2, 3, 4, 5, 6, 7),
                 __builtin_shufflevector(lf[ks][i][0], lf[ks][i][1], 0, 1, 2, 3, 4, 5, 6, 7), acc[i][j], 0, 0, 0);
-            if constexpr (kSpread && (k & 3) == 0)
-                transfer_from(std::integral_constant<int, k / 4>{}, refill, left_fetch, right_fetch);
-            if constexpr (k < 16) {
-                if constexpr (k < kReads)
-                    load_frag(std::integral_constant<int, k>{}, cur_stage, std::integral_constant<int, 1>{});
-                if constexpr (k == 15) {
-                    // all transfers of step + 1 have landed: what may still be in flight are the groups of
-                    // the steps after it and, when spread, the four transfers this step has issued so far
-                    wait_vmcnt<8 * (kAhead - 2) + (kSpread ? 4 : 0)>();
-                    __builtin_amdgcn_s_barrier();
-                }
-            } else {
-                if constexpr (k - 16 < kReads)
-                    load_frag(std::integral_constant<int, k - 16>{}, nxt_stage, std::integral_constant<int, 0>{});
-                if constexpr (!kSpread && (k & 1) == 0)
-                    transfer_from(std::integral_constant<int, (k - 16) / 2>{}, refill, left_fetch, right_fetch);
+            static_for<kTransfers>([&](auto pc) {
+                if constexpr (kSpread && transfer_slot(decltype(pc)::value) == k)
+                    transfer_from(pc, refill, left_fetch, right_fetch);
+            });
+            constexpr int first = reads_before(k % kHalf), count = reads_before(k % kHalf + 1) - first;
+            static_for<count>([&](auto nc) {
+                load_frag(std::integral_constant<int, first + decltype(nc)::value>{}, ks == 0 ? cur_stage : nxt_stage,
+                          std::integral_constant<int, 1 - ks>{});
+            });
+            if constexpr (k == kHalf - 1) {
+                // all transfers of step + 1 have landed: what may still be in flight are the groups of
+                // the steps after it and, when spread, the transfers this step has issued so far
+                wait_vmcnt<kTransfers * (kAhead - 2) + kIssuedAtWait>();
+                __builtin_amdgcn_s_barrier();
             }
+            static_for<kTransfers>([&](auto pc) {
+                if constexpr (!kSpread && transfer_slot(decltype(pc)::value) == k)
+                    transfer_from(pc, refill, left_fetch, right_fetch);
+            });
             __builtin_amdgcn_sched_barrier(0);
         });
         cur_off = nxt_off;
@@ -400,10 +457,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
 
     // Epilogue.  A segment that is not a whole tile leaves its accumulators as they are, in fp32.
     __syncthreads();
-    if (s_begin != 0 || s_end != steps) {
+    if (TI == 4 && (s_begin != 0 || s_end != steps)) {   // (only tiles of 256 rows are ever split)
         float4 *slot = partial + ((int64_t)(2 * block + (s_begin == 0 ? 1 : 0)) * 4 + wave) * (64 * 64) + lane;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -415,11 +472,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     }
     // Each accumulator tile is a transposed output tile: lane l holds output row l % 32
     // and, in register r, output column 8 (r / 4) + 4 (l / 32) + r % 4.  Each wave parks its
-    // 128 x 128 block as bf16 in its own 32 KiB of LDS (chunks swizzled by row) and writes it out as
+    // 32 TI x 128 block as bf16 in LDS of its own (chunks swizzled by row) and writes it out as
     // 256-byte row segments.
-    uint8_t *park = smem + wave * 32768;
+    uint8_t *park = smem + wave * (Sizes::kParkBytes / 4);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < TI; ++i) {
         const int row = i * 32 + lm;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -433,13 +490,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
             }
         }
     }
-    uint16_t *out_base = out + (int64_t)(r0 + wr * 128) * K + k0 + wc * 128;
+    const int block_row = r0 + wr * 32 * TI;
+    uint16_t *out_base = out + (int64_t)block_row * K + k0 + wc * 128;
 #pragma unroll 4
-    for (int pass = 0; pass < 32; ++pass) {
+    for (int pass = 0; pass < 8 * TI; ++pass) {
         const int row = pass * 4 + (lane >> 4);
         const int c = lane & 15;
         const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 256 + ((c ^ (row & 15)) << 4));
-        if (r0 + wr * 128 + row < R && k0 + wc * 128 + c * 8 < K)
+        if (block_row + row < R && k0 + wc * 128 + c * 8 < K)
             *reinterpret_cast<uint4 *>(out_base + (int64_t)row * K + c * 8) = v;
     }
     __syncthreads();   // the next segment's first stage overwrites the parked block
@@ -491,7 +549,7 @@ __global__ __launch_bounds__(256) void grad_gemm_fixup_kernel(const float4 *__re
     }
     __syncthreads();
     int r0, k0;
-    tile_origin(tile, tiles_r, tiles_k, phase_period, r0, k0);
+    tile_origin(tile, GT, tiles_r, tiles_k, phase_period, r0, k0);
     const int row0 = r0 + (quadrant >> 1) * 128 + i * 32, col0 = k0 + (quadrant & 1) * 128 + j * 32;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -507,15 +565,13 @@ __global__ __launch_bounds__(256) void grad_gemm_fixup_kernel(const float4 *__re
 
 namespace {
 
-constexpr int kStages = 5;
-constexpr int kLds = kStages * kGStage;
-
 // How a call is carried out: which kernels, how the tiles are dealt out, what scratch it needs.
 struct GradGemmPlan {
     bool covered;      // some kernel handles the shape
     bool tile_path;    // a shape the 256 x 256 tile kernels can do (their scratch is asked for)
     bool mid;          // the kernels of grad_gemm_mid.hip do it (always when tile_path is not set)
     bool split;        // tiles split over the CUs, partial tiles summed by the fix-up kernel
+    int ti;            // tiles of 64 ti rows
     int tiles_r, tiles_k, steps, blocks, per_block, phase_period;
     int64_t out_rows, out_cols, contraction, q_rows, ld_left;
     size_t expanded_bytes, partial_bytes;
@@ -538,48 +594,70 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
     p.mid = true;
     if (!p.tile_path)
         return p;
-    p.tiles_r = (int)((p.out_rows + GT - 1) / GT);
     p.tiles_k = (int)((p.out_cols + GT - 1) / GT);
     p.steps = (int)(p.contraction / GC);
-    const int tiles = p.tiles_r * p.tiles_k;
-    // One workgroup per CU at a time.  When rounds of whole tiles would leave CUs idle, every CU
-    // can get the same share of (tile, step) units instead, the split tiles being summed by a
-    // second, small kernel.  That pays when the steps saved outweigh the partial tiles written
-    // and read back (two 256 KiB slots per workgroup at most, one per tile at least).
-    const int rounds = cus > 0 ? (tiles + cus - 1) / cus : 0;
+    auto tiles_of = [&](int ti) { return (int)((p.out_rows + 64 * ti - 1) / (64 * ti)) * p.tiles_k; };
+    // One workgroup per CU at a time.  Two ways to deal out the work: rounds of whole tiles of 256, 192, 128 or
+    // 64 rows (whichever costs least), or, when rounds would leave too many CUs idle, every CU gets
+    // the same share of (tile, step) units of the largest tiles and the split tiles are summed by a
+    // second, small kernel.
+    const int tiles = tiles_of(4);
     const int64_t units = (int64_t)tiles * p.steps;
-    // measured on this kernel: 0.6 us per step, 0.08 us per partial tile written and read, 10 us for the second launch
-    const double whole_cost = 0.6 * rounds * p.steps;
-    const double split_cost = cus > 0 ? 0.6 * (double)((units + cus - 1) / cus) + 0.08 * (cus + tiles) + 10.0 : 0.0;
-    p.split = cus >= 8 && split_cost < whole_cost && units >= 4 * (int64_t)cus;
-    p.blocks = (tiles + 7) / 8 * 8;
+    // What a step of 32 contraction elements takes, us, with a share `busy` of the CUs at work (the chip is
+    // power-limited: the more of them, the slower each), and what a tile's two ends take.  Fitted to
+    // 30 products with 49 .. 2816 tiles and 64 .. 512 steps, most of which are met within 5 %.  The weight-only
+    // form reads half lines of both operands, which the smaller tiles feel.
+    constexpr double kStepUs[5] = {0.0, 0.20, 0.25, 0.30, 0.46}, kBusyUs[5] = {0.0, 0.08, 0.16, 0.29, 0.32};
+    constexpr double kEndsUs[5] = {0.0, 5.0, 7.0, 9.5, 13.5};
+    auto whole_cost = [&](int ti) {
+        const int n = tiles_of(ti), rounds = (n + cus - 1) / cus;
+        const double busy = (double)n / ((double)rounds * cus);
+        const double step = (kStepUs[ti] + kBusyUs[ti] * busy * busy) * (which == 2 && ti < 4 ? 1.15 : 1.0);
+        return rounds * (step * p.steps + kEndsUs[ti]);
+    };
+    // split: a share of the units, partial tiles written and read back (0.08 us each), the second launch;
+    // a step costs more when no other workgroup is at the same contraction position (see phase_period)
+    const int share = cus >= 8 ? (int)((units + cus - 1) / cus) : 0;
+    const int period = cus >= 8 ? p.steps / std::gcd(share, p.steps) : 0;
+    const double split_cost = cus >= 8 && units >= 4 * (int64_t)cus
+                                  ? (period <= 32 ? 0.78 : 1.0) * share + 0.08 * (cus + tiles) + 8.0
+                                  : 1e30;
+    p.ti = 4;
+    double cost = cus > 0 ? whole_cost(4) : 0.0;
+    for (int ti = 3; cus > 0 && ti >= 1; --ti)
+        if (whole_cost(ti) < cost) {
+            cost = whole_cost(ti);
+            p.ti = ti;
+        }
+    p.split = split_cost < cost;
+    if (p.split) {
+        cost = split_cost;
+        p.ti = 4;
+    }
+    p.tiles_r = (int)((p.out_rows + 64 * p.ti - 1) / (64 * p.ti));
+    const int chosen = tiles_of(p.ti);
+    p.blocks = (chosen + 7) / 8 * 8;
     p.per_block = p.steps;
     p.phase_period = 0;
-    if (!p.split && cus >= 8 && tiles > cus) {
+    if (!p.split && cus >= 8 && chosen > cus) {
         // more whole tiles than compute units: one workgroup per unit walks over several tiles, so that
         // no tile after the first waits for a workgroup to be dispatched (7 us per tile here)
-        p.blocks = cus;
-        p.per_block = (tiles + cus - 1) / cus * p.steps;
+        const int rounds = (chosen + cus - 1) / cus;
+        p.blocks = ((chosen + rounds - 1) / rounds + 7) / 8 * 8;   // the same number on every XCD
+        p.per_block = rounds * p.steps;
     }
     if (p.split) {
         p.blocks = cus;
-        p.per_block = (int)((units + p.blocks - 1) / p.blocks);
+        p.per_block = share;
         // workgroups b and b + period are at the same contraction position at all times
-        const int period = p.steps / std::gcd(p.per_block, p.steps);
         p.phase_period = (period % 8 == 0 && p.blocks % period == 0) ? period : 8;
         if (p.blocks % p.phase_period != 0)
             p.phase_period = p.blocks;
     }
     // Whether the kernels that expand on the way into LDS are cheaper: theirs is their own estimate; here
     // the expansion (read 0.5, written 2 bytes per code at 4.5 TB/s) and two or three launches come on top.
-    // A step of a whole tile takes 0.6 us, or 0.72 with all compute units busy (the chip is power-limited).
-    // Both sides measured, us: 512 x 5632 x 2048 weight-only 22 / 56; 2048 x 1792 x 640 G_x 14 / 47, G_w 16 / 47;
-    // 2048 x 5632 x 2048 G_x 59 / 76, G_w 64 / 60; 4096 x 5632 x 2048 G_x 112 / 112, G_w 123 / 98.
-    const double expand_cost = 4.0 + (double)p.q_rows * (double)K * 2.5 / 4.5e6;
-    const double busy = rounds > 0 && cus > 0 ? (double)tiles / ((double)rounds * cus) : 1.0;
-    const double tile_cost =
-        p.split ? split_cost + 0.24 * (double)((units + cus - 1) / cus) : rounds * ((0.6 + 0.12 * busy) * p.steps + 8.0) + 4.0;
-    p.mid = grad_gemm_mid_cost(p.contraction, p.out_rows, p.out_cols, cus >= 8 ? cus : 256) < expand_cost + tile_cost;
+    const double expand_cost = 3.0 + (double)p.q_rows * (double)K * 2.5 / 4.5e6;
+    p.mid = grad_gemm_mid_cost(p.contraction, p.out_rows, p.out_cols, cus >= 8 ? cus : 256) < expand_cost + cost;
     p.expanded_bytes = ((size_t)p.q_rows * K * 2 + 255) / 256 * 256;
     p.partial_bytes = p.split ? (size_t)2 * p.blocks * kSlotQuads * sizeof(float4) : 0;
     return p;
@@ -597,15 +675,52 @@ int64_t grad_gemm_workspace_bytes(int which, bool fp4, int64_t M, int64_t N, int
     return p.tile_path ? (int64_t)(p.expanded_bytes + p.partial_bytes) : 0;
 }
 
+namespace {
+
+template <int MODE, int TI>
+hipError_t launch_tiles(const GradGemmPlan &p, const uint16_t *left, const uint16_t *qhat, int64_t ld_right, uint16_t *out,
+                        float4 *partial, hipStream_t stream)
+{
+    hipLaunchKernelGGL((grad_gemm_tile_kernel<MODE, TI>), dim3((unsigned)p.blocks), dim3(kGemmThreads), TileSizes<TI>::kLds,
+                       stream, left, p.ld_left, qhat, ld_right, (int)p.contraction, (int)p.out_rows, (int)p.out_cols,
+                       p.tiles_r, p.tiles_k, p.per_block, p.phase_period, out, partial);
+    return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t launch_mode(const GradGemmPlan &p, const uint16_t *left, const uint16_t *qhat, int64_t ld_right, uint16_t *out,
+                       float4 *partial, hipStream_t stream)
+{
+    return p.ti == 4   ? launch_tiles<MODE, 4>(p, left, qhat, ld_right, out, partial, stream)
+           : p.ti == 3 ? launch_tiles<MODE, 3>(p, left, qhat, ld_right, out, partial, stream)
+           : p.ti == 2 ? launch_tiles<MODE, 2>(p, left, qhat, ld_right, out, partial, stream)
+                       : launch_tiles<MODE, 1>(p, left, qhat, ld_right, out, partial, stream);
+}
+
+template <int MODE>
+hipError_t prepare_mode()
+{
+    hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 4>), TileSizes<4>::kLds);
+    if (err == hipSuccess)
+        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 3>), TileSizes<3>::kLds);
+    if (err == hipSuccess)
+        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 2>), TileSizes<2>::kLds);
+    if (err == hipSuccess)
+        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 1>), TileSizes<1>::kLds);
+    return err;
+}
+
+}  // namespace
+
 hipError_t prepare_grad_gemm_kernels()
 {
     static OncePerDevice once;
     return once([] {
-        hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<0, kStages>), kLds);
+        hipError_t err = prepare_mode<0>();
         if (err == hipSuccess)
-            err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<1, kStages>), kLds);
+            err = prepare_mode<1>();
         if (err == hipSuccess)
-            err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<2, kStages>), kLds);
+            err = prepare_mode<2>();
         return err;
     });
 }
@@ -634,8 +749,6 @@ hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)
     char *memory = static_cast<char *>(a.workspace);
     auto *qhat = reinterpret_cast<uint16_t *>(memory);
     auto *partial = p.split ? reinterpret_cast<float4 *>(memory + p.expanded_bytes) : nullptr;
-    const int tiles_r = p.tiles_r, tiles_k = p.tiles_k, per_block = p.per_block, phase_period = p.phase_period;
-    const int64_t ld_left = p.ld_left, contraction = p.contraction, out_rows = p.out_rows, out_cols = p.out_cols;
 
     const int64_t groups = p.q_rows * a.K / 8;
     hipLaunchKernelGGL(expand_codes_kernel, dim3((unsigned)((groups + 1023) / 1024)), dim3(256), 0, stream,
@@ -643,24 +756,13 @@ hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)
     err = hipGetLastError();
     if (err != hipSuccess)
         return err;
-    const dim3 grid((unsigned)p.blocks), block(kGemmThreads);
-    if (a.which == 0)
-        hipLaunchKernelGGL((grad_gemm_tile_kernel<0, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
-                           a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
-                           phase_period, out, partial);
-    else if (a.which == 1)
-        hipLaunchKernelGGL((grad_gemm_tile_kernel<1, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
-                           a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
-                           phase_period, out, partial);
-    else
-        hipLaunchKernelGGL((grad_gemm_tile_kernel<2, kStages>), grid, block, kLds, stream, dy, ld_left, qhat,
-                           a.K, (int)contraction, (int)out_rows, (int)out_cols, tiles_r, tiles_k, per_block,
-                           phase_period, out, partial);
-    err = hipGetLastError();
+    err = a.which == 0   ? launch_mode<0>(p, dy, qhat, a.K, out, partial, stream)
+          : a.which == 1 ? launch_mode<1>(p, dy, qhat, a.K, out, partial, stream)
+                         : launch_mode<2>(p, dy, qhat, a.K, out, partial, stream);
     if (err == hipSuccess && p.split) {
-        hipLaunchKernelGGL(grad_gemm_fixup_kernel, dim3((unsigned)(tiles_r * tiles_k * 16)), dim3(256), 0, stream,
-                           partial, p.steps, per_block, phase_period, (int)out_rows, (int)out_cols, tiles_r,
-                           tiles_k, out);
+        hipLaunchKernelGGL(grad_gemm_fixup_kernel, dim3((unsigned)(p.tiles_r * p.tiles_k * 16)), dim3(256), 0, stream,
+                           partial, p.steps, p.per_block, p.phase_period, (int)p.out_rows, (int)p.out_cols, p.tiles_r,
+                           p.tiles_k, out);
         err = hipGetLastError();
     }
     return err;

@@ -374,7 +374,7 @@ struct Shape {
     double alone, shared;
 };
 constexpr Shape kShapes[] = {{1, 1, 2, 0.56, 0.44}, {1, 1, 4, 1.00, 1.00}, {1, 2, 1, 0.53, 0.39},
-                             {1, 2, 2, 0.79, 0.79}, {2, 2, 1, 0.74, 0.64}, {2, 2, 2, 1.25, 1.25}};
+                             {1, 2, 2, 0.79, 0.79}, {2, 2, 1, 0.74, 0.64}, {2, 2, 2, 1.30, 1.30}};
 
 double shape_cost(const Shape &s, int64_t C, int64_t R, int64_t K, int cus)
 {
