@@ -37,7 +37,7 @@ typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;   // of one group: four waves
 constexpr int GC = 64;          // contraction elements per step
-constexpr int PF = 2;           // steps a group's loads are ahead in registers (4 measured the same)
+constexpr int PF = 2;           // register sets for a group's loads, one step each (4 measured the same)
 
 template <int T>
 __device__ __forceinline__ int column_swz(int crow)
@@ -68,39 +68,41 @@ struct PackedCodes {
         }
     }
 
-    // elements 8 g .. 8 g + 7 as bf16(fp32(s u)) (E2M1: s v), one 16-byte chunk
-    __device__ __forceinline__ v4u expand(int g, float s) const
+    // elements 2 p, 2 p + 1 as bf16(fp32(s u)) (E2M1: s v); `scaled` is scale(s)
+    static __device__ __forceinline__ float scale(float s)
     {
-        float v[8];
-        if constexpr (GRID == 0) {
-            const uint32_t word = w[g];
-            const v2f p0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 0);
-            const v2f p1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 1);
-            const v2f p2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 2);
-            const v2f p3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 3);
-            v[0] = __fmul_rn(s, p0[0]); v[1] = __fmul_rn(s, p0[1]);
-            v[2] = __fmul_rn(s, p1[0]); v[3] = __fmul_rn(s, p1[1]);
-            v[4] = __fmul_rn(s, p2[0]); v[5] = __fmul_rn(s, p2[1]);
-            v[6] = __fmul_rn(s, p3[0]); v[7] = __fmul_rn(s, p3[1]);
-        } else {
-            // code at the top of its byte, top bit inverted, the bit below the code set: the signed byte
-            // 2^(7 - b) u, whose power of two goes into the scale (a product by a power of two is exact)
+        return GRID == 0 ? s : s * (1.0f / (float)(1 << (GRID == 0 ? 0 : 7 - GRID)));
+    }
+    static constexpr int kPerByte = 8 / kContainer;
+    // The eight codes of group g as signed bytes: bytes[d] holds, in byte i, element kPerByte i + d of the group as
+    // 2^(7 - b) u: the code at the top of its byte, top bit inverted, the bit below the code set.  (The power of
+    // two goes into the scale; a product by it is exact.)
+    template <int g, bool WHOLE>
+    __device__ __forceinline__ void to_bytes(uint32_t (&bytes)[8]) const
+    {
+        if constexpr (GRID != 0) {
             constexpr uint32_t field = ((0xffu << (8 - GRID)) & 0xffu) * 0x01010101u;
             constexpr uint32_t flip = (0x80u | (0x80u >> GRID)) * 0x01010101u;
-            constexpr int kPerByte = 8 / kContainer;
-            const float scaled = s * (1.0f / (float)(1 << (7 - GRID)));
             const uint32_t word = kContainer == 4 ? w[g] : w[g * kContainer / 4] >> (8 * ((g * kContainer) & 3));
-            uint32_t bytes[kPerByte];   // bytes[d] holds, in byte i, element kPerByte i + d
-#pragma unroll
-            for (int d = 0; d < kPerByte; ++d) {
-                const int up = 8 - GRID - d * kContainer;
-                bytes[d] = ((up >= 0 ? word << up : word >> -up) & field) ^ flip;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                v[e] = __fmul_rn((float)(int8_t)(bytes[e % kPerByte] >> (8 * (e / kPerByte))), scaled);
+            static_for<kPerByte>([&](auto d) {
+                constexpr int up = 8 - GRID - decltype(d)::value * kContainer;
+                bytes[decltype(d)::value] = ((up >= 0 ? word << (up & 31) : word >> (-up & 31)) & field) ^ flip;
+                if constexpr (WHOLE)   // computed here as a word, not byte by byte at each use
+                    asm("" : "+v"(bytes[decltype(d)::value]));
+            });
         }
-        return v4u{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+    }
+    template <int P>
+    __device__ __forceinline__ uint32_t expand_pair(const uint32_t (&bytes)[8], float scaled) const
+    {
+        if constexpr (GRID == 0) {
+            const v2f v = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[P / 4], 1.0f, P % 4);
+            return pack_bf16(__fmul_rn(scaled, v[0]), __fmul_rn(scaled, v[1]));
+        } else {
+            constexpr int e = 2 * P % 8;
+            return pack_bf16(__fmul_rn((float)(int8_t)(bytes[e % kPerByte] >> (8 * (e / kPerByte))), scaled),
+                             __fmul_rn((float)(int8_t)(bytes[(e + 1) % kPerByte] >> (8 * ((e + 1) / kPerByte))), scaled));
+        }
     }
 };
 
@@ -189,27 +191,66 @@ __global__ __launch_bounds__(kThreads * GROUPS, GROUPS == 1 ? 2 : 1) void grad_g
     v4u left_reg[PF][kLeftChunks];
     Packed code_reg[PF];
     float scale_reg[PF];
-    auto fetch = [&](auto set, int round) {   // past the end: the last step again, not used
-        constexpr int p = decltype(set)::value;
+    // operand positions of the round being fetched (past the end: the last step again, not used)
+    const char *left_at = left_base, *scale_at = scale_base;
+    const uint8_t *code_at = code_base;
+    auto position = [&](int round) {
         const int at = min(round * GROUPS + group, steps - 1);
-        const char *left_at = left_base + at * left_step;
-        const uint8_t *code_at = code_base + at * code_step;
-        const char *scale_at = scale_base + at * scale_step;
-        static_for<kLeftChunks>([&](auto i) {
-            left_reg[p][decltype(i)::value] = *reinterpret_cast<const v4u *>(left_at + left_src[decltype(i)::value]);
-        });
-        code_reg[p].load(code_at + code_src);
-        scale_reg[p] = *reinterpret_cast<const float *>(scale_at + scale_src);
+        left_at = left_base + at * left_step;
+        code_at = code_base + at * code_step;
+        scale_at = scale_base + at * scale_step;
     };
-    auto stage_in = [&](auto set, uint8_t *stage) {
-        constexpr int p = decltype(set)::value;
-        static_for<kLeftChunks>([&](auto i) {
-            *reinterpret_cast<v4u *>(stage + left_dst[decltype(i)::value]) = left_reg[p][decltype(i)::value];
-        });
-        static_for<NE / 8>([&](auto g) {
-            *reinterpret_cast<v4u *>(stage + right_dst[decltype(g)::value]) =
-                code_reg[p].expand(decltype(g)::value, scale_reg[p]);
-        });
+    auto fetch_left = [&](auto set, auto i) {
+        left_reg[decltype(set)::value][decltype(i)::value] =
+            *reinterpret_cast<const v4u *>(left_at + left_src[decltype(i)::value]);
+    };
+    auto fetch_codes = [&](auto set) {
+        code_reg[decltype(set)::value].load(code_at + code_src);
+        scale_reg[decltype(set)::value] = *reinterpret_cast<const float *>(scale_at + scale_src);
+    };
+    auto fetch = [&](auto set, int round) {
+        position(round);
+        static_for<kLeftChunks>([&](auto i) { fetch_left(set, i); });
+        fetch_codes(set);
+    };
+    // Blocks of 128 x 128 pin the staging of the next round between a round's matrix instructions: a wave
+    // that multiplies first and expands afterwards leaves the matrix unit and the vector unit idle in turn,
+    // and two waves on a SIMD, in step by the barriers, do little about it (weight-only 512 x 5632 x 2048
+    // 23.1 -> 20.7 us, 2560 x 1024 x 2816 28.2 -> 24.5; G_w 2688 x 384 x 5632 28.5 -> 24.7).  Smaller blocks have
+    // half or a quarter of the matrix instructions per expanded code; there the order is left to the
+    // compiler, with all loads issued ahead of the multiplication (G_w 2048 x 1792 x 640 16.6 us, pinned 17.9).
+    constexpr bool kPinned = WI * WJ == 4;
+    // The staging of a round in kSlices slices: slice e expands pair e of the codes and, with a chunk's last
+    // pair, writes the chunk; the left operand's chunks go in between, each replaced at once by the load of
+    // the same chunk for two rounds later, if REFILL (`position` says which).
+    constexpr int kSlices = NE / 2;
+    v4u chunk;
+    uint32_t bytes[8];
+    auto stage_slice = [&](auto set, uint8_t *stage, auto slice, auto refill) __attribute__((always_inline)) {
+        constexpr int p = decltype(set)::value, e = decltype(slice)::value;
+        if constexpr (e % 4 == 0)
+            code_reg[p].template to_bytes<e / 4, kPinned>(bytes);
+        chunk[e % 4] = code_reg[p].template expand_pair<e>(bytes, Packed::scale(scale_reg[p]));
+        if constexpr (e % 4 == 3)
+            *reinterpret_cast<v4u *>(stage + right_dst[e / 4]) = chunk;
+        if constexpr (kPinned && e % 4 == 1)
+            static_for<kLeftChunks>([&](auto i) {
+                if constexpr (decltype(i)::value * (kSlices / 4) / kLeftChunks == e / 4) {
+                    *reinterpret_cast<v4u *>(stage + left_dst[decltype(i)::value]) = left_reg[p][decltype(i)::value];
+                    if constexpr (decltype(refill)::value)
+                        fetch_left(set, i);
+                }
+            });
+        if constexpr (e == kSlices - 1 && decltype(refill)::value)
+            fetch_codes(set);
+    };
+    auto stage_in = [&](auto set, uint8_t *stage, auto refill) {
+        if constexpr (!kPinned)
+            static_for<kLeftChunks>([&](auto i) {
+                *reinterpret_cast<v4u *>(stage + left_dst[decltype(i)::value]) =
+                    left_reg[decltype(set)::value][decltype(i)::value];
+            });
+        static_for<kSlices>([&](auto e) { stage_slice(set, stage, e, refill); });
     };
 
     // ---- fragment reads
@@ -217,7 +258,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, GROUPS == 1 ? 2 : 1) void grad_g
         const int row = row0 + lm;
         return *reinterpret_cast<const v8bf *>(operand + row * 128 + (((2 * ks + lh) ^ ((row >> 1) & 7)) << 4));
     };
-    auto column_fragment = [&](auto edge, const uint8_t *operand, int col0, int ks) {
+    auto column_fragment = [&](auto edge, const uint8_t *operand, int col0, int ks) __attribute__((always_inline)) {
         constexpr int T = decltype(edge)::value;
         const int col = col0 + 16 * (lg & 1) + 4 * (l16 & 3), row = 8 * (lg >> 1) + (l16 >> 2);
         auto at = [&](int more) {   // contraction row of the k-step: row + more (swz has period 16)
@@ -238,57 +279,110 @@ __global__ __launch_bounds__(kThreads * GROUPS, GROUPS == 1 ? 2 : 1) void grad_g
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = 0.0f;
-    auto multiply = [&](const uint8_t *stage) {
-#pragma unroll
-        for (int ks = 0; ks < GC / 16; ++ks) {
-            v8bf lf[WI], rf[WJ];
-#pragma unroll
-            for (int i = 0; i < WI; ++i) {
-                if constexpr (kLeftColumns)
-                    lf[i] = column_fragment(std::integral_constant<int, TR>{}, stage, wr * 32 * WI + 32 * i, ks);
-                else
-                    lf[i] = row_fragment(stage, wr * 32 * WI + 32 * i, ks);
-            }
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) {
-                if constexpr (kRightRows)
-                    rf[j] = row_fragment(stage + kLeftBytes, wc * 32 * WJ + 32 * j, ks);
-                else
-                    rf[j] = column_fragment(std::integral_constant<int, TC>{}, stage + kLeftBytes,
-                                            wc * 32 * WJ + 32 * j, ks);
-            }
-#pragma unroll
-            for (int i = 0; i < WI; ++i)
-#pragma unroll
-                for (int j = 0; j < WJ; ++j)   // right fragment as the row operand: transposed accumulator tiles
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[j], lf[i], acc[i][j], 0, 0, 0);
+    // Fragments of k-step ks in set ks % 2; read number n of a k-step (transposing reads come in pairs).
+    v8bf lf[2][WI], rf[2][WJ];
+    constexpr int kFragments = WI + WJ, kBlocks = WI * WJ, kMatrix = (GC / 16) * kBlocks;
+    auto read_fragment = [&](const uint8_t *stage, auto ksc, auto fc) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ksc)::value, f = decltype(fc)::value;   // R0 L0 then the others
+        constexpr bool is_left = f == 1 || f > WJ;
+        constexpr int i = is_left ? (f == 1 ? 0 : f - WJ) : (f == 0 ? 0 : f - 1);
+        if constexpr (is_left) {
+            if constexpr (kLeftColumns)
+                lf[ks & 1][i] = column_fragment(std::integral_constant<int, TR>{}, stage, wr * 32 * WI + 32 * i, ks);
+            else
+                lf[ks & 1][i] = row_fragment(stage, wr * 32 * WI + 32 * i, ks);
+        } else {
+            if constexpr (kRightRows)
+                rf[ks & 1][i] = row_fragment(stage + kLeftBytes, wc * 32 * WJ + 32 * i, ks);
+            else
+                rf[ks & 1][i] = column_fragment(std::integral_constant<int, TC>{}, stage + kLeftBytes,
+                                                wc * 32 * WJ + 32 * i, ks);
         }
     };
+    // The matrix instructions of a round out of `stage`.  Pinned: each is followed by its share of the next
+    // k-step's fragment reads and, if STAGING, of the next round's staging.  (Right fragment as the row
+    // operand: transposed accumulator tiles.)
+    auto multiply = [&](auto staging, auto refill, const uint8_t *stage, auto next_set, uint8_t *next_stage)
+                        __attribute__((always_inline)) {
+        static_for<GC / 16>([&](auto ksc) {
+            constexpr int ks = decltype(ksc)::value;
+            typedef std::integral_constant<int, ks + 1> NextStep;
+            if constexpr (ks == 0 || !kPinned)
+                static_for<kFragments>([&](auto f) { read_fragment(stage, ksc, f); });
+            static_for<kBlocks>([&](auto bc) {
+                constexpr int b = decltype(bc)::value, i = b / WJ, j = b % WJ;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ks & 1][j], lf[ks & 1][i], acc[i][j], 0, 0, 0);
+                if constexpr (kPinned) {
+                    if constexpr (ks + 1 < GC / 16)
+                        static_for<kFragments>([&](auto f) {
+                            if constexpr (decltype(f)::value * kBlocks / kFragments == b)
+                                read_fragment(stage, NextStep{}, f);
+                        });
+                    if constexpr (decltype(staging)::value)
+                        static_for<kSlices>([&](auto e) {
+                            if constexpr (decltype(e)::value * kMatrix / kSlices == ks * kBlocks + b)
+                                stage_slice(next_set, next_stage, e, refill);
+                        });
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        });
+    };
 
-    // Round s: into stage s % 2 (last read in round s - 2, which every wave had left when it passed the
-    // barrier of round s - 1), loads of round s + PF, barrier, multiply.
+    typedef std::integral_constant<int, 0> Set0;
+    typedef std::integral_constant<int, 1> Set1;
     static_for<PF>([&](auto p) { fetch(p, decltype(p)::value); });
     int s = 0;
-    for (; s + PF < rounds; s += PF) {
-        static_for<PF>([&](auto p) {
-            uint8_t *const stage = stages + (decltype(p)::value & 1) * kStage;
-            stage_in(p, stage);
-            fetch(p, s + decltype(p)::value + PF);
-            // the next round's expansion may move up to here, not above the loads: its wait would cover them
-            __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPinned) {
+        // Round s reads stage s % 2 and stages round s + 1 in the other one (last read in round s - 1, which
+        // every wave had left when it passed the barrier of round s).
+        position(PF);
+        stage_in(Set0{}, stages, std::true_type{});
+        for (; s + PF < rounds; s += PF) {
+            static_for<PF>([&](auto p) {
+                constexpr int now = decltype(p)::value;
+                typedef std::integral_constant<int, 1 - now> Next;
+                __syncthreads();
+                position(s + now + 1 + PF);
+                multiply(std::true_type{}, std::true_type{}, stages + now * kStage, Next{}, stages + (1 - now) * kStage);
+            });
+        }
+        // the last one or two rounds
+        __syncthreads();
+        const bool second = s + 1 < rounds;
+        if (second)   // (then every group has this round)
+            multiply(std::true_type{}, std::false_type{}, stages, Set1{}, stages + kStage);
+        else if (GROUPS == 1 || s * GROUPS + group < steps)
+            multiply(std::false_type{}, std::false_type{}, stages, Set1{}, stages + kStage);
+        if (second) {
             __syncthreads();
-            multiply(stage);
+            if (GROUPS == 1 || (s + 1) * GROUPS + group < steps)
+                multiply(std::false_type{}, std::false_type{}, stages + kStage, Set0{}, stages);
+        }
+    } else {
+        // Round s: into stage s % 2 (last read in round s - 2, which every wave had left when it passed the
+        // barrier of round s - 1), loads of round s + PF, barrier, multiply.
+        for (; s + PF < rounds; s += PF) {
+            static_for<PF>([&](auto p) {
+                uint8_t *const stage = stages + decltype(p)::value * kStage;
+                stage_in(p, stage, std::false_type{});
+                fetch(p, s + decltype(p)::value + PF);
+                // the next round's expansion may move up to here, not above the loads: its wait would cover them
+                __builtin_amdgcn_sched_barrier(0);
+                __syncthreads();
+                multiply(std::false_type{}, std::false_type{}, stage, p, stage);
+            });
+        }
+        static_for<PF>([&](auto p) {
+            if (s + decltype(p)::value < rounds) {
+                uint8_t *const stage = stages + decltype(p)::value * kStage;
+                stage_in(p, stage, std::false_type{});
+                __syncthreads();
+                if (GROUPS == 1 || (s + decltype(p)::value) * GROUPS + group < steps)
+                    multiply(std::false_type{}, std::false_type{}, stage, p, stage);
+            }
         });
     }
-    static_for<PF>([&](auto p) {
-        if (s + decltype(p)::value < rounds) {
-            uint8_t *const stage = stages + (decltype(p)::value & 1) * kStage;
-            stage_in(p, stage);
-            __syncthreads();
-            if (GROUPS == 1 || (s + decltype(p)::value) * GROUPS + group < steps)
-                multiply(stage);
-        }
-    });
 
     // the groups' sums meet in the first group, in order
     if constexpr (GROUPS > 1) {
@@ -374,7 +468,7 @@ struct Shape {
     double alone, shared;
 };
 constexpr Shape kShapes[] = {{1, 1, 2, 0.56, 0.44}, {1, 1, 4, 1.00, 1.00}, {1, 2, 1, 0.53, 0.39},
-                             {1, 2, 2, 0.79, 0.79}, {2, 2, 1, 0.74, 0.64}, {2, 2, 2, 1.30, 1.30}};
+                             {1, 2, 2, 0.79, 0.79}, {2, 2, 1, 0.74, 0.64}, {2, 2, 2, 1.08, 1.30}};
 
 double shape_cost(const Shape &s, int64_t C, int64_t R, int64_t K, int cus)
 {
