@@ -95,26 +95,44 @@ __device__ __forceinline__ void store_wave_block(const Vec (&acc)[AF][2], const 
             }
         }
     }
-    // each pass: 8 rows of 128 bytes, lane l takes 16-byte chunk l % 8 of row l / 8
     uint16_t *y_base = y + (int64_t)row0 * ld_y + col0;
-    const bool vector_ok = ((ld_y & 7) == 0) && ((reinterpret_cast<uintptr_t>(y) & 15) == 0) && (col0 + 64 <= N);
+    if (((ld_y & 7) == 0) && ((reinterpret_cast<uintptr_t>(y) & 15) == 0) && (col0 + 64 <= N)) {
+        // each pass: 8 rows of 128 bytes, lane l takes 16-byte chunk l % 8 of row l / 8
 #pragma unroll 4
-    for (int pass = 0; pass < 4 * AF; ++pass) {
-        const int row = pass * 8 + (lane >> 3);
-        const int c = lane & 7;
-        const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 128 + ((c ^ (row & 7)) << 4));
-        if (row0 + row >= M)
-            continue;
-        uint16_t *dst = y_base + (int64_t)row * ld_y + c * 8;
-        if (vector_ok) {
-            *reinterpret_cast<uint4 *>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (col0 + c * 8 + e < N)
-                    dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        for (int pass = 0; pass < 4 * AF; ++pass) {
+            const int row = pass * 8 + (lane >> 3);
+            const int c = lane & 7;
+            const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 128 + ((c ^ (row & 7)) << 4));
+            if (row0 + row < M)
+                *reinterpret_cast<uint4 *>(y_base + (int64_t)row * ld_y + c * 8) = v;
         }
+        return;
+    }
+    // Rows that 16-byte stores do not fit (a row pitch that is no multiple of 8, or the last columns): the lanes
+    // of a store write consecutive columns, two at a time where the rows start on whole dwords.  A lane
+    // writing its chunk of eight columns one by one scatters each store over 8 rows (us, that / this: E2M1
+    // 5000 x 2100 x 768 31.4 / 14.5; 4 bits 5000 x 2101 x 768 30.8 / 19.8, 9000 x 1421 x 2048 50.5 / 39.6).
+    if ((ld_y & 1) == 0 && (reinterpret_cast<uintptr_t>(y) & 3) == 0) {
+        const int c = 2 * (lane & 31);
+#pragma unroll 4
+        for (int pass = 0; pass < 16 * AF; ++pass) {
+            const int row = pass * 2 + (lane >> 5);
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(park + row * 128 + (((c >> 3) ^ (row & 7)) << 4) + (c & 7) * 2);
+            if (row0 + row >= M || col0 + c >= N)
+                continue;
+            uint16_t *dst = y_base + (int64_t)row * ld_y + c;
+            if (col0 + c + 1 < N)
+                *reinterpret_cast<uint32_t *>(dst) = v;
+            else
+                *dst = (uint16_t)v;
+        }
+        return;
+    }
+#pragma unroll 4
+    for (int row = 0; row < 32 * AF; ++row) {
+        const uint16_t v = *reinterpret_cast<const uint16_t *>(park + row * 128 + (((lane >> 3) ^ (row & 7)) << 4) + (lane & 7) * 2);
+        if (row0 + row < M && col0 + lane < N)
+            y_base[(int64_t)row * ld_y + lane] = v;
     }
 }
 
