@@ -147,6 +147,10 @@ __global__ __launch_bounds__(kTileThreads, AF == 4 ? 2 : 3) void fp4_gemm_tile_k
     //   s = 11..15  load the fragments of pair 0 of step + 1
     //   AF = 2: transfers at s = 0..3, fragments of pair 1 two each at 0 and 1, wait and barrier at 4,
     //   fragments of pair 0 two each at 5 and 6
+    // The barrier lets the other waves refill the stage that is being read, one step later, so a wave has all
+    // of its reads back before it: the instructions up to s = 9 use every fragment of pair 1 (AF = 4);
+    // with AF = 2 the second fragments are used behind the barrier, so those are read first, the first ones,
+    // which s = 4 waits for, last, and the wait is spelled out.
     constexpr int kWaitAt = AF == 4 ? 10 : 4;
     const int one = 0x7f7f7f7f;   // block scales 2^0 (the codes carry no block scale)
     auto operand = [](const uint4 &f) { return v8i{(int)f.x, (int)f.y, (int)f.z, (int)f.w, 0, 0, 0, 0}; };
@@ -166,10 +170,12 @@ __global__ __launch_bounds__(kTileThreads, AF == 4 ? 2 : 3) void fp4_gemm_tile_k
             if constexpr (AF == 4 && s >= 1 && s <= 6)
                 load_frag(cur, 1, s - 1);
             if constexpr (AF == 2 && s < 2) {
-                load_frag(cur, 1, s == 0 ? 0 : 1);
-                load_frag(cur, 1, s == 0 ? AF : AF + 1);
+                load_frag(cur, 1, s == 0 ? 1 : 0);
+                load_frag(cur, 1, s == 0 ? AF + 1 : AF);
             }
             if constexpr (s == kWaitAt) {
+                if constexpr (AF == 2)
+                    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
                 wait_vmcnt<kTransfers>();
                 __builtin_amdgcn_s_barrier();
             }
