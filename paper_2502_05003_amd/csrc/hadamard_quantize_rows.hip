@@ -16,6 +16,7 @@
 // 2048 elements, do not show.
 #include "hadamard_tile.h"
 #include "quest_internal.h"
+#include "row_staging.h"
 
 namespace quest {
 namespace {
@@ -49,18 +50,13 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
     const uint8_t *const buffer = row_buffers + (shared_row ? 0 : wave * row_buffer);
     const uint32_t buffer_addr = lds_address(row_buffers) + (uint32_t)(shared_row ? 0 : wave * row_buffer);
 
-    // A transfer fills 1 KiB: bf16, sixteen tile rows of 64 bytes, chunk c of tile row r in slot c ^ ((r >> 2) & 3);
-    // fp32, eight of 128 bytes, in slot c ^ ((r >> 1) & 7).  Beyond the row's end: its last chunk again.
+    typedef RowStaging<(int)sizeof(In)> Staging;
     auto request_row = [&](int64_t row_of_launch) {
         const bool from_b = row_of_launch >= rows_a;
         const char *base = reinterpret_cast<const char *>(from_b ? x_b + (row_of_launch - rows_a) * ld_b
                                                                  : x_a + row_of_launch * ld_a);
-        const int off = kF32 ? 128 * (lane >> 3) + 16 * ((lane & 7) ^ (lane >> 4))
-                             : 64 * (lane >> 2) + 16 * ((lane & 3) ^ ((lane >> 4) & 3));
-        for (int at = 1024 * part; at < row_bytes; at += 1024 * parts) {
-            const int flip = kF32 ? (at & 1024) >> 4 : 0;   // fp32, odd pieces: (r >> 1) & 4 is set
-            lds_dma16_stream(base, (uint32_t)min(at + (off ^ flip), row_bytes - 16), buffer_addr + (uint32_t)at);
-        }
+        for (int at = 1024 * part; at < row_bytes; at += 1024 * parts)
+            lds_dma16_stream(base, (uint32_t)Staging::source(at, lane, row_bytes), buffer_addr + (uint32_t)at);
     };
     const int64_t row_stride = shared_row ? gridDim.x : (int64_t)gridDim.x * waves;
     int64_t row_of_launch = shared_row ? blockIdx.x : (int64_t)blockIdx.x * waves + wave;
@@ -94,9 +90,8 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
 
     // This lane's share of a tile: 16 consecutive elements of tile row m (zeros beyond the row's end)
     auto read_bf16 = [&](int t, uint32_t (&w)[8]) {
-        const int slot0 = (2 * h) ^ ((m >> 2) & 3), slot1 = (2 * h + 1) ^ ((m >> 2) & 3);
-        const v4u a = *reinterpret_cast<const v4u *>(buffer + 2048 * t + 64 * m + 16 * slot0);
-        const v4u b = *reinterpret_cast<const v4u *>(buffer + 2048 * t + 64 * m + 16 * slot1);
+        const v4u a = *reinterpret_cast<const v4u *>(buffer + Staging::read(t, m, h, 0, row_buffer));
+        const v4u b = *reinterpret_cast<const v4u *>(buffer + Staging::read(t, m, h, 1, row_buffer));
         const bool there = 1024 * t + 32 * m < cols;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -108,7 +103,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
         const bool there = 1024 * t + 32 * m < cols;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const v4u v = *reinterpret_cast<const v4u *>(buffer + 4096 * t + 128 * m + 16 * ((4 * h + i) ^ ((m >> 1) & 7)));
+            const v4u v = *reinterpret_cast<const v4u *>(buffer + Staging::read(t, m, h, i, row_buffer));
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 f[4 * i + e] = there ? __uint_as_float(v[e]) : 0.0f;
@@ -337,18 +332,11 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
     }
 }
 
-// LDS per row: whole transfers
-int row_buffer_bytes(const QuantizeArgs &a)
-{
-    const int row_bytes = (int)a.cols * (a.dtype == QUEST_F32 ? 4 : 2);
-    return (row_bytes + 1023) / 1024 * 1024;
-}
-
 template <int GRID, typename In, int G>
 hipError_t launch(const QuantizeArgs &a, hipStream_t stream)
 {
     auto kernel = hq_rows_kernel<GRID, In, G>;
-    const int buffer = row_buffer_bytes(a), groups = (int)((a.cols + 1024 * G - 1) / (1024 * G));
+    const int buffer = RowStaging<(int)sizeof(In)>::buffer_bytes((int)a.cols), groups = (int)((a.cols + 1024 * G - 1) / (1024 * G));
     const int64_t rows = a.rows + a.rows2;
     // A workgroup shares a row when there are few rows, and when sixteen waves' rows would not fit a compute
     // unit's LDS (us, a row per wave / shared: 333 x 5120 8.8 / 5.8, 1400 x 2560 7.3 / 7.7,
