@@ -157,8 +157,10 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
         }
         // per-row constants as in the general kernel, every operation correctly rounded
         const float rms = sqrtf(__fdiv_rn(total, (float)cols));
-        const float clip = __fmul_rn(alpha, rms), trust_raw = __fmul_rn(__fmul_rn(trust_edge, rms), sqrt_n);
+        const float clip = __fmul_rn(alpha, rms);
+        // scale 0, code k = 0 (E2M1: +0) and all trusted, also where the entries are not zero but their squares are
         const bool zero_row = !(rms > 0.0f);
+        const float trust_raw = zero_row ? __builtin_inff() : __fmul_rn(__fmul_rn(trust_edge, rms), sqrt_n);
         // raw -> 2^(8-b) * (position in grid cells), so that the code ends up in the top b bits of a byte;
         // E2M1: raw -> units of the format
         const float inv_step = zero_row ? 0.0f : kFp4 ? __fdiv_rn(6.0f, clip) : __fdiv_rn((float)(kLevels - 1), __fmul_rn(2.0f, clip));
@@ -239,7 +241,8 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                     if (8 * dd < count_i) {
                         uint32_t packed;
                         if (kFp4) {
-                            auto scaled = [&](int i) { return __fmul_rn(elem(8 * dd + i), to_e2m1); };
+                            // (+ 0: the zero row's products are -0 for negative entries)
+                            auto scaled = [&](int i) { return __fmaf_rn(elem(8 * dd + i), to_e2m1, 0.0f); };
                             packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, scaled(0), scaled(1), 1.0f, 0);
                             packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, scaled(2), scaled(3), 1.0f, 1);
                             packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, scaled(4), scaled(5), 1.0f, 2);
@@ -307,7 +310,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
 #pragma unroll
                         for (int i = 31; i >= 0; --i)
                             negative = __builtin_amdgcn_alignbit(negative, __float_as_uint(elem(32 * cc + i)), 31);
-                        const uint32_t code = bit_plan.apply(~negative);
+                        const uint32_t code = bit_plan.apply(zero_row ? ~0u : ~negative);
                         if (mine)
                             store(code_row + at, code);
                     }

@@ -38,6 +38,22 @@ def test_quantizer(rows, cols, n, dtype, grid):
         compare_quantizer(got, qo.hadamard_quantize(x, n, grid), cols, grid)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("grid", [1, 2, 3, 4, 8, "fp4"])
+def test_rows_whose_squares_underflow_are_zero_rows(grid, dtype):
+    """Entries of about 2^-80 of both signs: the row's sum of squares is 0 in fp32, so the row is quantized like
+    an all-zero one, scale 0, code k = 0 (E2M1: +0) and every element trusted."""
+    rows, cols = 300, 1536
+    x = synth.gaussian(rows, cols, 1.0, 3, "f32") * np.float32(2.0 ** -80)
+    x = synth.to_bf16_bits(x) if dtype == "bf16" else x
+    got = gpu_quantize(x, 512, 4 if grid == "fp4" else grid, fp4=grid == "fp4", want_xh=False)
+    assert np.all(got["scales"] == 0.0) and np.all(got["mask"] == 0xFF)
+    if grid == "fp4":
+        assert np.all(got["codes"] == 0)
+    else:
+        assert np.all(qo.unpack_odd(got["codes"], cols, grid) == 1)
+
+
 def test_quantizer_strided_rows_and_no_mask():
     """A row pitch above the row length; the codes do not depend on whether the mask is asked for."""
     x = synth.outlier_activations(270, 2560, 0.01, 20.0, seed=1, dtype="bf16")
