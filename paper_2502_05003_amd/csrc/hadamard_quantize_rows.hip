@@ -10,9 +10,9 @@
 // fewer rows than waves to fill the chip, a workgroup shares a row instead.  A tile that the row
 // does not reach is skipped; one that it ends in is transformed whole, with zeros.
 //
-// Measured against the general kernel (bf16, b = 4, us): 8192 x 2560 50 -> 16, 8192 x 5120 94 -> 26..31,
-// 333 x 2560 7.4 -> 5.5; fp32: 8192 x 2560 50 -> 28.  What bounds it is the vector unit (about 24 instructions per 64 elements; the row is touched twice, the
-// sum of squares being half an instruction per element), so the run-time branches, a handful per
+// Measured against the general kernel (b = 4, us): bf16 8192 x 2560 48.7 -> 18.2, 8192 x 5120 94 -> 33.7,
+// 333 x 2560 7.2 -> 5.6; fp32 8192 x 2560 48.9 -> 30.1.  What bounds it is the vector unit (the row is touched
+// twice, the sum of squares being half an instruction per element), so the run-time branches, a handful per
 // 2048 elements, do not show.
 #include "hadamard_tile.h"
 #include "quest_internal.h"
@@ -161,10 +161,9 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
         // scale 0, code k = 0 (E2M1: +0) and all trusted, also where the entries are not zero but their squares are
         const bool zero_row = !(rms > 0.0f);
         const float trust_raw = zero_row ? __builtin_inff() : __fmul_rn(__fmul_rn(trust_edge, rms), sqrt_n);
-        // raw -> 2^(8-b) * (position in grid cells), so that the code ends up in the top b bits of a byte;
-        // E2M1: raw -> units of the format
+        // raw -> position in grid cells; E2M1: raw -> units of the format
         const float inv_step = zero_row ? 0.0f : kFp4 ? __fdiv_rn(6.0f, clip) : __fdiv_rn((float)(kLevels - 1), __fmul_rn(2.0f, clip));
-        const float cell16 = inv_step * inv_sqrt_n * (float)(256 >> BITS), to_e2m1 = inv_step * inv_sqrt_n;
+        const float to_cell = inv_step * inv_sqrt_n, to_e2m1 = to_cell;
         if (lane == 0 && part == 0)
             (from_b ? scales_b : scales_a)[row] = __fdiv_rn(clip, kFp4 ? 6.0f : (float)(kLevels - 1));
         uint32_t *code_row = reinterpret_cast<uint32_t *>((from_b ? codes_b : codes_a) + row * (cols * CB / 8));
@@ -234,7 +233,14 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                         dst[64 * i] = __fmul_rn(elem(i), inv_sqrt_n);
             }
             auto store = [&](uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); };
-            // Codes: see hq_mfma_kernel for the bit tricks
+            // Codes: see hq_mfma_kernel for the bit tricks.  The cell is the floor of the product itself, not of its sum
+            // with 127.5 as there: that sum's fp32 spacing is coarser than the product's near zero.  Codes that
+            // differ from a 64-bit evaluation, of 3.5e8 bf16 elements, 4 and 8 bits: by the sum 116 and 1945, so 74
+            // and 533, general kernel 72 and 516.  The two operations more per element cost 3 to 6 % (8192 x 2560
+            // 17.4 -> 18.2 us).  The byte 2^(8-b) (cell + L/2), saturated, has the code in its top b bits.
+            auto code_byte = [&](int i) {
+                return __fmaf_rn(floorf(__fmul_rn(elem(i), to_cell)), (float)(256 >> BITS), 128.0f);
+            };
             if constexpr (CB == 4) {
 #pragma unroll
                 for (int dd = 0; dd < 2 * G; ++dd) {
@@ -251,7 +257,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                             uint32_t even = 0, odd = 0;
 #pragma unroll
                             for (int i = 0; i < 8; ++i) {
-                                const float t = __fmaf_rn(elem(8 * dd + i), cell16, 127.5f);
+                                const float t = code_byte(8 * dd + i);
                                 if (i & 1)
                                     odd = __builtin_amdgcn_cvt_pk_u8_f32(t, i >> 1, odd);
                                 else
@@ -272,7 +278,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                         uint32_t packed = 0;
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            packed = __builtin_amdgcn_cvt_pk_u8_f32(__fmaf_rn(elem(4 * w + i), cell16, 127.5f), i, packed);
+                            packed = __builtin_amdgcn_cvt_pk_u8_f32(code_byte(4 * w + i), i, packed);
                         packed = byte_plan.apply(packed);
                         if (4 * w + (lane & 3) < count_i)
                             store(code_row + (lane >> 2) + 16 * (lane & 3) + 64 * (4 * g0 + w), packed);
@@ -288,7 +294,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                             uint32_t e = 0;
 #pragma unroll
                             for (int j = 0; j < 4; ++j)
-                                e = __builtin_amdgcn_cvt_pk_u8_f32(__fmaf_rn(elem(16 * t16 + k + 4 * j), cell16, 127.5f), j, e);
+                                e = __builtin_amdgcn_cvt_pk_u8_f32(code_byte(16 * t16 + k + 4 * j), j, e);
                             packed |= ((e >> 6) & 0x03030303u) << (2 * k);
                         }
                         packed = pair_plan.apply(packed);

@@ -20,10 +20,7 @@ SHAPES = [(256, 64, 64), (300, 192, 2), (257, 960, 64), (261, 1088, 16), (333, 2
           (256, 8192, 4096), (1031, 3136, 64), (4201, 1536, 512), (1100, 5760, 128)]
 
 
-# b = 8: an fp32 rounding near the top of the grid is 8e-6 of a cell, so a few codes in a million differ, and the
-# bar's 1e-5 of the elements plus one needs millions of elements to be a bound and not a matter of luck.
-CASES = [(*shape, dtype, grid) for shape in SHAPES for dtype in ("bf16", "f32") for grid in (1, 2, 3, 4, 8, "fp4")
-         if grid != 8 or shape[0] * shape[1] > 3000000]
+CASES = [(*shape, dtype, grid) for shape in SHAPES for dtype in ("bf16", "f32") for grid in (1, 2, 3, 4, 8, "fp4")]
 
 
 @pytest.mark.parametrize("rows,cols,n,dtype,grid", CASES)
@@ -36,6 +33,17 @@ def test_quantizer(rows, cols, n, dtype, grid):
     else:
         got = gpu_quantize(x, n, grid, want_xh=(grid == 3))
         compare_quantizer(got, qo.hadamard_quantize(x, n, grid), cols, grid)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_8_bit_codes_are_decided_by_the_rounded_product(dtype):
+    """A code differs from the 64-bit one where a cell boundary lies between x_h / step and its fp32 value.  With
+    the fp32 roundings of scale and product, 6e-8 each, and |x_h| / step = 26 on average that is about 2e-6 of the
+    elements; deciding on the sum with 127.5 (spacing 1.5e-5) makes it 6e-6."""
+    rows, cols, n = 4096, 2560, 512
+    x = synth.outlier_activations(rows, cols, 0.01, 20.0, seed=5, dtype=dtype)
+    got, ref = gpu_quantize(x, n, 8, want_xh=False), qo.hadamard_quantize(x, n, 8)
+    assert compare_quantizer(got, ref, cols, 8)[0] < 3.5e-6 * x.size
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
