@@ -83,6 +83,7 @@ typedef enum { QUEST_F32 = 0, QUEST_BF16 = 1 } quest_dtype;
  *   scales      out [rows] fp32, s = alpha rms / (L - 1)
  *   mask        out [rows, cols/8] bitmap, or NULL when no backward pass will follow
  *   xh_out      out [rows, cols] fp32 Hadamard-domain values x_h, or NULL (NULL in production)
+ * A row's outputs depend on that row alone, not on the number of rows of the call or its place among them.
  * Rows whose entries are all zero give s = 0, c = L/2 everywhere and an all-ones mask.  A row that
  * holds an infinity or a NaN gets a non-finite scale and unspecified codes and mask bits; other
  * rows are not affected (the paper defines the projection for finite inputs only; the row's sum of

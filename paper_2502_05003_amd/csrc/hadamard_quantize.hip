@@ -193,11 +193,10 @@ hipError_t prepare_quantize_kernels()
 hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
 {
     if (a.rows2 != 0) {
-        // two operands: one launch where one matrix-core kernel takes both, else one after the other
-        const bool first_by_rows = quantize_rows_preferred(a, a.rows), second_by_rows = quantize_rows_preferred(a, a.rows2);
-        if (first_by_rows && second_by_rows)
+        // two operands: one launch where a matrix-core kernel covers the shape, else one after the other
+        if (quantize_rows_preferred(a, a.rows + a.rows2))
             return launch_hadamard_quantize_rows(a, stream);
-        if (!first_by_rows && !second_by_rows && a.rows != 0 && launch_hadamard_quantize_mfma(a, stream))
+        if (a.rows != 0 && launch_hadamard_quantize_mfma(a, stream))
             return hipGetLastError();
         QuantizeArgs first = a, second = a;
         first.x2 = nullptr;

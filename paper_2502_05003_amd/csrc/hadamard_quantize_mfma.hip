@@ -105,6 +105,10 @@ void hq_mfma_kernel(
     constexpr int kSpan = LOG2N > 10 ? (1 << (LOG2N - 10)) : 1;
     constexpr int G = kHoldAll ? T : (kSpan >= T ? T : (kSpan >= 2 ? kSpan : (T >= 2 ? 2 : 1)));
     constexpr int kLevels = 1 << BITS;
+    // fp32 rows that hq_rows_kernel takes when there are many of them: sum of squares, row constants and codes
+    // are made as they are there
+    constexpr bool kAsRows = kF32 && !ABSMAX && U >= 8;
+    constexpr int kSums = kAsRows ? partial_sums_of_row(T, LOG2N > 11 ? 4 : 2) : 1;
     constexpr int CB = BITS == 3 ? 4 : BITS;   // container bits
     static_assert(!FP4 || BITS == 4, "the E2M1 grid has 4-bit codes");
     static_assert((U % 4) == 0 || (BITS == 3 || BITS == 4), "rows that do not end on half a tile: nibble codes only");
@@ -256,15 +260,26 @@ void hq_mfma_kernel(
         // Per-row constants in the un-normalised domain (x_h = raw / sqrt(n)).  The reciprocal and
         // the square root are the hardware approximations (1 ulp): the codes are decided on
         // raw * raw_to_cell, and a relative error of 1e-7 there is the size of one fp32 rounding.
-        float cell16 = 0.0f, to_e2m1 = 0.0f, trust_raw = 0.0f;
+        float cell16 = 0.0f, to_e2m1 = 0.0f, trust_raw = 0.0f;   // (kAsRows: cell16 is raw -> cells)
         // `sumsq`: this lane's share of the row's sum of squares; `raw_max`: the row's largest |raw|
-        auto set_row_constants = [&](float sumsq, float raw_max) {
+        auto set_row_constants = [&](const float (&sumsq)[kSums], float raw_max) {
+            if constexpr (kAsRows) {
+                float total = wave_sum_dpp(sumsq[0]);
+#pragma unroll
+                for (int c = 1; c < kSums; ++c)
+                    total += wave_sum_dpp(sumsq[c]);
+                const RowConstants row_is = row_constants<kLevels, false>(total, cols, alpha, trust_edge, inv_sqrt_n, sqrt_n);
+                cell16 = row_is.to_cell;
+                trust_raw = row_is.trust_raw;
+                emit_if(lane == 0, reinterpret_cast<uint32_t *>(scales + row), __float_as_uint(row_is.scale));
+                return;
+            }
             float clip;   // half-width of the grid in x_h units
             if constexpr (ABSMAX) {
                 clip = __fmul_rn(raw_max, inv_sqrt_n);
                 trust_raw = raw_max;
             } else {
-                const float rms = __builtin_amdgcn_sqrtf(wave_sum_dpp(sumsq) * (1.0f / (float)cols));
+                const float rms = __builtin_amdgcn_sqrtf(wave_sum_dpp(sumsq[0]) * (1.0f / (float)cols));
                 clip = alpha * rms;
                 trust_raw = trust_edge * rms * sqrt_n;
             }
@@ -276,7 +291,10 @@ void hq_mfma_kernel(
             emit_if(lane == 0, reinterpret_cast<uint32_t *>(scales + row),
                     __float_as_uint(clip * (FP4 ? 1.0f / 6.0f : 1.0f / (float)(kLevels - 1))));
         };
-        float sumsq = 0.0f;
+        float sumsq[kSums];
+#pragma unroll
+        for (int c = 0; c < kSums; ++c)
+            sumsq[c] = 0.0f;
         if constexpr (!kF32) {
             // sum of squares from the packed inputs (the block transform is orthonormal)
 #pragma unroll
@@ -287,7 +305,7 @@ void hq_mfma_kernel(
                 for (int i = 0; i < 8; ++i) {
                     v2bf pair;
                     __builtin_memcpy(&pair, &w[i], 4);
-                    sumsq = __builtin_amdgcn_fdot2_f32_bf16(pair, pair, sumsq, false);
+                    sumsq[0] = __builtin_amdgcn_fdot2_f32_bf16(pair, pair, sumsq[0], false);
                 }
             }
         }
@@ -326,7 +344,7 @@ void hq_mfma_kernel(
                         uint32_t hi[8], mid[8], lo[8];   // x = hi + mid + lo (see split_bf16)
 #pragma unroll
                         for (int i = 0; i < 16; ++i)
-                            sumsq = __fmaf_rn(f[i], f[i], sumsq);
+                            sumsq[t % kSums] = __fmaf_rn(f[i], f[i], sumsq[t % kSums]);
                         split_bf16(f, hi, mid, lo);
                         v8bf p0, p1;
                         __builtin_memcpy(&p0, &lo[0], 16);      // smallest piece first
@@ -418,7 +436,8 @@ void hq_mfma_kernel(
                             uint32_t even = 0, odd = 0;
 #pragma unroll
                             for (int i = 0; i < 8; ++i) {
-                                const float t = __fmaf_rn(elem(8 * dd + i), cell16, 127.5f);
+                                const float t = kAsRows ? cell_byte<BITS>(elem(8 * dd + i), cell16)
+                                                        : __fmaf_rn(elem(8 * dd + i), cell16, 127.5f);
                                 if (i & 1)
                                     odd = __builtin_amdgcn_cvt_pk_u8_f32(t, i >> 1, odd);
                                 else

@@ -45,7 +45,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
     const int tiles = (cols + 1023) >> 10, per_lane = cols >> 6;   // elements per lane
     // A row is one wave's, or (shared_row, wave-uniform like everything that follows from it) its
     // workgroup's: the waves then take transfers and groups of tiles in turn.
-    const int sums = min((tiles + G - 1) / G, 4);
+    const int sums = partial_sums_of_row(tiles, G);
     const int part = shared_row ? wave : 0, parts = shared_row ? waves : 1;
     const uint8_t *const buffer = row_buffers + (shared_row ? 0 : wave * row_buffer);
     const uint32_t buffer_addr = lds_address(row_buffers) + (uint32_t)(shared_row ? 0 : wave * row_buffer);
@@ -119,8 +119,8 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
         if (shared_row)
             __syncthreads();
 
-        // The block transform is orthonormal: the sum of squares of the inputs.  It is made of as many partial
-        // sums as a shared row has waves, added in order, so that it does not depend on who makes them.
+        // The block transform is orthonormal: the sum of squares of the inputs, in as many partial sums as a shared
+        // row has waves (see partial_sums_of_row)
         auto partial_sum = [&](int c) {
             float sumsq = 0.0f;
             for (int t = c; t < tiles; t += sums) {
@@ -155,17 +155,11 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
             for (int c = 1; c < sums; ++c)
                 total += partial_sum(c);
         }
-        // per-row constants as in the general kernel, every operation correctly rounded
-        const float rms = sqrtf(__fdiv_rn(total, (float)cols));
-        const float clip = __fmul_rn(alpha, rms);
-        // scale 0, code k = 0 (E2M1: +0) and all trusted, also where the entries are not zero but their squares are
-        const bool zero_row = !(rms > 0.0f);
-        const float trust_raw = zero_row ? __builtin_inff() : __fmul_rn(__fmul_rn(trust_edge, rms), sqrt_n);
-        // raw -> position in grid cells; E2M1: raw -> units of the format
-        const float inv_step = zero_row ? 0.0f : kFp4 ? __fdiv_rn(6.0f, clip) : __fdiv_rn((float)(kLevels - 1), __fmul_rn(2.0f, clip));
-        const float to_cell = inv_step * inv_sqrt_n, to_e2m1 = to_cell;
+        const RowConstants row_is = row_constants<kLevels, kFp4>(total, cols, alpha, trust_edge, inv_sqrt_n, sqrt_n);
+        const float to_cell = row_is.to_cell, trust_raw = row_is.trust_raw;
+        const bool zero_row = row_is.zero_row;
         if (lane == 0 && part == 0)
-            (from_b ? scales_b : scales_a)[row] = __fdiv_rn(clip, kFp4 ? 6.0f : (float)(kLevels - 1));
+            (from_b ? scales_b : scales_a)[row] = row_is.scale;
         uint32_t *code_row = reinterpret_cast<uint32_t *>((from_b ? codes_b : codes_a) + row * (cols * CB / 8));
         uint32_t *mask_row = reinterpret_cast<uint32_t *>(mask + row * (cols / 8));
 
@@ -233,14 +227,8 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                         dst[64 * i] = __fmul_rn(elem(i), inv_sqrt_n);
             }
             auto store = [&](uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); };
-            // Codes: see hq_mfma_kernel for the bit tricks.  The cell is the floor of the product itself, not of its sum
-            // with 127.5 as there: that sum's fp32 spacing is coarser than the product's near zero.  Codes that
-            // differ from a 64-bit evaluation, of 3.5e8 bf16 elements, 4 and 8 bits: by the sum 116 and 1945, so 74
-            // and 533, general kernel 72 and 516.  The two operations more per element cost 3 to 6 % (8192 x 2560
-            // 17.4 -> 18.2 us).  The byte 2^(8-b) (cell + L/2), saturated, has the code in its top b bits.
-            auto code_byte = [&](int i) {
-                return __fmaf_rn(floorf(__fmul_rn(elem(i), to_cell)), (float)(256 >> BITS), 128.0f);
-            };
+            // Codes: see hq_mfma_kernel for the bit tricks
+            auto code_byte = [&](int i) { return cell_byte<BITS>(elem(i), to_cell); };
             if constexpr (CB == 4) {
 #pragma unroll
                 for (int dd = 0; dd < 2 * G; ++dd) {
@@ -248,7 +236,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                         uint32_t packed;
                         if (kFp4) {
                             // (+ 0: the zero row's products are -0 for negative entries)
-                            auto scaled = [&](int i) { return __fmaf_rn(elem(8 * dd + i), to_e2m1, 0.0f); };
+                            auto scaled = [&](int i) { return __fmaf_rn(elem(8 * dd + i), to_cell, 0.0f); };
                             packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, scaled(0), scaled(1), 1.0f, 0);
                             packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, scaled(2), scaled(3), 1.0f, 1);
                             packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, scaled(4), scaled(5), 1.0f, 2);
@@ -408,21 +396,20 @@ hipError_t prepare_quantize_rows_kernels()
     return err;
 }
 
-// Which rows come here: at least 256 of them (fewer stay with the kernels that had them, the instantiated one
-// or the general one: those launches are short and mostly latency, 24 rows of 2560 take 5.1 us here
-// and 6.8 there, and the general kernel adds a row's squares up in an order of its own that a
-// fp32 evaluation elsewhere reproduces bit for bit), of a shape without an instantiation in
-// hadamard_quantize_mfma.hip, or fp32 rows of 1024 elements or more, which that file holds in registers as a whole
-// (us, here / there: 8192 x 1024 11.5 / 13.5, 8192 x 4096 41 / 53, 333 x 3584 6.8 / 8.3), or very long bf16
-// rows (11008: 8192 rows 56 / 58, 1400 rows 15 / 16, 333 rows 8.3 / 10.3).  The choice is made operand by
-// operand, so that a pair call gives the bits of two single calls.
+// Which calls come here (`rows`: of both operands).  Everything that hadamard_quantize_mfma.hip has no instantiation
+// for, up to blocks of 4096: faster than the general kernel at every number of rows (us, here / there, 24 rows:
+// 2560 elements 4.7 / 6.6, 5120 4.9 / 11.0, 64 3.4 / 4.3).  Of the fp32 shapes that it has, which it holds in registers as
+// a whole: long rows, and many rows (here / there: 24 rows of 2816 5.8 / 5.1, 3584 5.9 / 6.9, 5632 6.1 / 9.1;
+// 1024 x 2048 6.9 / 6.7, 2048 x 2048 8.5 / 8.9, 8192 x 2048 19.2 / 24.6; blocks of 4096, 24 rows 9.2 / 6.1,
+// 2048 rows 15.4 / 15.0, 8192 rows 43.9 / 51.7).  Both kernels make the same bits of these rows, so the number
+// of rows may decide; for bf16 rows they do not, and the shape alone does.
 bool quantize_rows_preferred(const QuantizeArgs &a, int64_t rows)
 {
-    if (rows < 256 || a.cols % 64 != 0 || a.log2n > 12 || a.mode == kQuantAbsMax)
+    if (a.cols % 64 != 0 || a.log2n > 12 || a.mode == kQuantAbsMax)
         return false;
-    if (a.dtype == QUEST_F32 ? a.cols >= 1024 : a.cols > 5632)
+    if (!launch_hadamard_quantize_mfma(a, nullptr, true))
         return true;
-    return !launch_hadamard_quantize_mfma(a, nullptr, true);
+    return a.dtype == QUEST_F32 && a.cols >= 1024 && (rows >= 2048 || (a.cols > 2816 && a.log2n < 12));
 }
 
 hipError_t launch_hadamard_quantize_rows(const QuantizeArgs &a, hipStream_t stream)

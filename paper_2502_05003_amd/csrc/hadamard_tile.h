@@ -90,6 +90,49 @@ __device__ __forceinline__ float sqrt_pow2(int log2n)
     return (log2n & 1) ? 1.41421356237309504880f * (float)(1 << (log2n >> 1)) : (float)(1 << (log2n >> 1));
 }
 
+// Per-row constants of the projection from the row's sum of squares, in the un-normalised domain
+// (x_h = raw / sqrt(n)), every operation correctly rounded.
+struct RowConstants {
+    float scale;       // alpha rms / (L - 1); E2M1: alpha rms / 6
+    float to_cell;     // raw -> position in grid cells; E2M1: raw -> units of the format
+    float trust_raw;   // trusted iff |raw| <= trust_raw
+    bool zero_row;     // scale 0, code k = 0 (E2M1: +0), all trusted, also where the entries are not zero but their squares are
+};
+
+template <int LEVELS, bool FP4>
+__device__ __forceinline__ RowConstants row_constants(float total, int cols, float alpha, float trust_edge,
+                                                      float inv_sqrt_n, float sqrt_n)
+{
+    RowConstants c;
+    const float rms = sqrtf(__fdiv_rn(total, (float)cols));
+    const float clip = __fmul_rn(alpha, rms);
+    c.zero_row = !(rms > 0.0f);
+    c.trust_raw = c.zero_row ? __builtin_inff() : __fmul_rn(__fmul_rn(trust_edge, rms), sqrt_n);
+    const float inv_step = c.zero_row ? 0.0f : FP4 ? __fdiv_rn(6.0f, clip) : __fdiv_rn((float)(LEVELS - 1), __fmul_rn(2.0f, clip));
+    c.to_cell = __fmul_rn(inv_step, inv_sqrt_n);
+    c.scale = __fdiv_rn(clip, FP4 ? 6.0f : (float)(LEVELS - 1));
+    return c;
+}
+
+// The code of one element in the top BITS bits of a byte (before its saturation to 0 .. 255): 2^(8-b) (cell + L/2), the cell
+// being the floor of the product itself.  By the sum of product and 127.5, whose fp32 spacing is coarser than
+// the product's near zero, more codes differ from a 64-bit evaluation (of 3.5e8 bf16 elements, 4 and 8
+// bits: by the sum 116 and 1945, by the product 74 and 533; the general kernel 72 and 516).
+template <int BITS>
+__device__ __forceinline__ float cell_byte(float raw, float to_cell)
+{
+    return __fmaf_rn(floorf(__fmul_rn(raw, to_cell)), (float)(256 >> BITS), 128.0f);
+}
+
+// How a row's sum of squares is made up, the same in every kernel that may get a shape, so that a row's scale
+// and codes do not depend on the number of rows: partial sum c is that of tiles c, c + n, .. (a fused multiply-add
+// per element in order, then wave_sum_dpp), and the n partial sums are added in order.
+__host__ __device__ constexpr int partial_sums_of_row(int tiles, int tiles_per_group)
+{
+    const int groups = (tiles + tiles_per_group - 1) / tiles_per_group;
+    return groups < 4 ? groups : 4;
+}
+
 // The stages on index bits 5 .. LOG2N - 1 of G tiles held as MFMA accumulators: bits 5, 6, 8, 9 are
 // register-to-register, bit 7 is the half-wave index and is swapped with register bit 0 first
 // (after which h holds bit 5; the swap is made for every block size so that the element order of

@@ -41,7 +41,7 @@ hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream);
 // Matrix-core kernel for the common bf16 / 4-bit shapes; false means "not covered, nothing launched".
 bool launch_hadamard_quantize_mfma(const QuantizeArgs &a, hipStream_t stream, bool query = false);
 
-// Matrix-core kernel for the other row lengths and blocks (run-time sizes): whether `rows` rows of an operand go there.
+// Matrix-core kernel for the other row lengths and blocks (run-time sizes): whether a call of `rows` rows goes there.
 bool quantize_rows_preferred(const QuantizeArgs &a, int64_t rows);
 hipError_t launch_hadamard_quantize_rows(const QuantizeArgs &a, hipStream_t stream);
 

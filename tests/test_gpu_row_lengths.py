@@ -15,7 +15,6 @@ pytestmark = pytest.mark.gpu
 
 #        rows, row length, block: one tile or less, an odd multiple of 64; ends in a tile; two and four tiles
 #        per block; more rows than resident waves (4096) or row-sharing workgroups (1024)
-#        (fewer than 256 rows: other kernels)
 SHAPES = [(256, 64, 64), (300, 192, 2), (257, 960, 64), (261, 1088, 16), (333, 2560, 512), (259, 6144, 2048),
           (256, 8192, 4096), (1031, 3136, 64), (4201, 1536, 512), (1100, 5760, 128)]
 
@@ -60,6 +59,26 @@ def test_rows_whose_squares_underflow_are_zero_rows(grid, dtype):
         assert np.all(got["codes"] == 0)
     else:
         assert np.all(qo.unpack_odd(got["codes"], cols, grid) == 1)
+
+
+# a shape without an instantiation, each grid; one wave per row and shared rows (up to 1024) on the larger side
+COUNTS = [(1100, 2560, 512, "bf16", grid) for grid in (1, 2, 3, 4, 8, "fp4")] + \
+         [(300, 1088, 16, "f32", 4), (1100, 2560, 512, "f32", 3), (300, 8192, 4096, "bf16", 4)] + \
+         [(2100, cols, n, "f32", 4) for cols, n in ((1024, 1024), (1280, 256), (1664, 128), (1792, 256), (2048, 2048),
+                                                    (2816, 256), (3584, 512), (4096, 4096), (4608, 512), (5632, 512))] + \
+         [(300, 11008, 256, "bf16", 4), (300, 5632, 512, "bf16", 4)]
+
+
+@pytest.mark.parametrize("rows,cols,n,dtype,grid", COUNTS)
+def test_a_row_does_not_depend_on_the_number_of_rows(rows, cols, n, dtype, grid):
+    """A token quantized alone, in a short call and in a long one gets the same bytes, whatever kernel takes the call."""
+    x = synth.outlier_activations(rows, cols, 0.01, 20.0, seed=cols, dtype=dtype)
+    args = dict(bits=4, fp4=True) if grid == "fp4" else dict(bits=grid)
+    whole = gpu_quantize(x, n, want_xh=False, **args)
+    for rows_of_call in (slice(0, 1), slice(7, 31), slice(0, 255), slice(1, 299)):
+        part = gpu_quantize(x[rows_of_call], n, want_xh=False, **args)
+        for name in ("codes", "scales", "mask"):
+            assert np.array_equal(part[name].view(np.uint8), whole[name][rows_of_call].view(np.uint8)), (name, rows_of_call)
 
 
 def test_quantizer_strided_rows_and_no_mask():

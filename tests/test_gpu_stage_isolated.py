@@ -6,9 +6,10 @@ isolated instead: the kernel's own Hadamard-domain values (`xh_out`) go through 
 written in NumPy, of the row RMS (Sec. 3.1), the clip-and-round projection onto the grid of Eq. 1,
 the scale and the trust mask (Sec. 3.2), operation by operation in the kernel's precision and
 order, and every scale, packed code byte and mask byte must be identical.  This holds for the
-general kernel, whose per-row constants are correctly rounded divisions and square roots; the
-matrix-core kernel takes those two per-row operations from the hardware's approximate
-instructions and is covered by the end-to-end bar only.
+general kernel and for the matrix-core kernel of any row length, whose per-row constants are
+correctly rounded divisions and square roots; the instantiated matrix-core kernel takes those two
+per-row operations from the hardware's approximate instructions (for bf16 rows) and is covered by the
+end-to-end bar only.
 """
 import numpy as np
 import pytest
@@ -98,10 +99,10 @@ def mirror_projection(xh, bits, alpha, outer_trust=1.0):
     return scale, codes, mask
 
 
-# shapes and widths the general kernel serves (the matrix-core kernel takes none of them)
-CASES = [(96, 1536, 512, 4, "f32"), (64, 1536, 512, 3, "bf16"), (33, 768, 256, 2, "bf16"),
-         (40, 2048, 2048, 8, "f32"), (57, 3072, 1024, 1, "bf16"), (19, 24, 8, 4, "f32"),
-         (200, 64, 64, 8, "f32"), (31, 6144, 2048, 4, "bf16")]
+# shapes the general kernel serves: rows that are no multiple of 64, blocks above 4096
+CASES = [(96, 1544, 8, 4, "f32"), (64, 1560, 8, 3, "bf16"), (33, 776, 8, 2, "bf16"),
+         (40, 8192, 8192, 8, "f32"), (57, 3080, 8, 1, "bf16"), (19, 24, 8, 4, "f32"),
+         (200, 72, 8, 8, "f32"), (31, 16384, 8192, 4, "bf16")]
 
 
 @pytest.mark.parametrize("rows,cols,block,bits,dtype", CASES)
@@ -125,11 +126,81 @@ def test_rounding_stages_match_the_fp32_mirror_bit_for_bit(rows, cols, block, bi
 
 def test_outer_trust_width_in_the_mirror():
     """The 1-bit mask at the narrower outer trust region (Sec. 3.3, the 1-bit case) through the same mirror."""
-    x = synth.student_t_activations(48, 1536, 3.0, seed=5, dtype="bf16")
+    x = synth.student_t_activations(48, 1544, 3.0, seed=5, dtype="bf16")
     from paper_2502_05003_amd import binding as q
     alpha = float(F32(q.quest_alpha_star(1)))
-    got = gpu_quantize(x, 512, 1, alpha=alpha, outer_trust=0.30)
+    got = gpu_quantize(x, 8, 1, alpha=alpha, outer_trust=0.30)
     scale, codes, mask = mirror_projection(got["xh"], 1, alpha, outer_trust=0.30)
     assert np.array_equal(got["scales"].view(np.uint32), scale.view(np.uint32))
     assert np.array_equal(got["codes"], codes) and np.array_equal(got["mask"], mask)
-    assert 0.2 < 1.0 - qo.unpack_mask(got["mask"], 1536).mean() < 0.4
+    assert 0.2 < 1.0 - qo.unpack_mask(got["mask"], 1544).mean() < 0.4
+
+
+# ---- the matrix-core kernel of any row length (csrc/hadamard_quantize_rows.hip)
+
+def mirror_sum_of_squares_by_tiles(x, dtype, block):
+    """Sum of squares of each row in that kernel's order, from the inputs: of a tile of 1024 elements lane
+    m + 32 h has elements 32 m + 16 h .. + 15; partial sum c is that of tiles c, c + n, .. (a fused
+    multiply-add per element; bf16: a dot product of two, whose rounding is not specified, so those inputs are
+    whole numbers whose sums are exact), added up over the lanes in quads, eights, rows of sixteen and
+    the four rows, and the n partial sums in order."""
+    rows, cols = x.shape
+    tiles = (cols + 1023) // 1024
+    v = np.zeros((rows, tiles * 1024), dtype=F32)
+    v[:, :cols] = (qo.widen(x) if dtype == "bf16" else x).astype(F32)
+    v = v.reshape(rows, tiles, 64, 16)                     # [row][tile][2 m + h][element]
+    group = 2 if block <= 2048 else 4
+    n = min((tiles + group - 1) // group, 4)
+    total = np.zeros(rows, dtype=F32)
+    for c in range(n):
+        lane = np.zeros((rows, 64), dtype=F32)
+        for t in range(c, tiles, n):
+            for e in range(16):
+                lane = fma32(v[:, t, :, e], v[:, t, :, e], lane)
+        lane = np.concatenate([lane[:, 0::2], lane[:, 1::2]], axis=1)      # lane m + 32 h
+        for _ in range(4):                                 # neighbours, pairs, quads, eights
+            lane = (lane[:, 0::2] + lane[:, 1::2]).astype(F32)
+        part = ((lane[:, 3] + lane[:, 2]).astype(F32) + (lane[:, 1] + lane[:, 0]).astype(F32)).astype(F32)
+        total = part if c == 0 else (total + part).astype(F32)
+    return total
+
+
+# blocks that are powers of four: 1 / sqrt(block) is a power of two, so that the mirror has the kernel's values before
+# that factor, exactly.  One wave per row and four, one tile and many, rows that end inside a tile.
+TILE_CASES = [(96, 1536, 256, 4, "f32"), (64, 1536, 256, 3, "bf16"), (33, 768, 64, 2, "bf16"), (40, 2048, 1024, 8, "f32"),
+              (57, 3072, 1024, 1, "bf16"), (200, 64, 64, 8, "f32"), (31, 12288, 4096, 4, "bf16"), (20, 1088, 16, 4, "f32"),
+              (9, 5120, 1024, 4, "f32"), (5, 16384, 4096, 8, "f32"), (1100, 2560, 256, 4, "bf16")]
+
+
+@pytest.mark.parametrize("rows,cols,block,bits,dtype", TILE_CASES)
+def test_rounding_stages_of_any_row_length_match_the_fp32_mirror_bit_for_bit(rows, cols, block, bits, dtype):
+    if dtype == "f32":
+        x = synth.outlier_activations(rows, cols, 0.01, 20.0, seed=rows + cols + bits, dtype=dtype)
+    else:   # whole numbers, a column in a hundred eight times as large: sums of squares below 2^24
+        rng = np.random.default_rng(rows + cols + bits)
+        x = synth.to_bf16_bits((rng.integers(-9, 10, size=(rows, cols)) * np.where(rng.random(cols) < 0.01, 8, 1)).astype(F32))
+    x[3] = 0
+    from oracle.quest_oracle import _load, _ptr
+    from paper_2502_05003_amd import binding as q
+    alpha = F32(q.quest_alpha_star(bits))
+    got = gpu_quantize(x, block, bits, alpha=float(alpha))
+    levels, root = 1 << bits, F32(np.sqrt(block))
+    rms = np.sqrt(mirror_sum_of_squares_by_tiles(x, dtype, block) / F32(cols), dtype=F32)
+    clip, zero = (alpha * rms).astype(F32), ~(rms > 0)
+    with np.errstate(divide="ignore"):
+        inv_step = np.where(zero, F32(0), F32(levels - 1) / (F32(2) * clip).astype(F32)).astype(F32)
+    raw = (got["xh"] * root).astype(F32)                   # exact
+    cell = np.floor((raw * (inv_step / root)[:, None]).astype(F32))
+    k = np.where(zero[:, None], 0, np.clip(cell, -(levels // 2), levels // 2 - 1)).astype(np.int32)
+    if bits == 1:
+        k = np.where(zero[:, None] | ~np.signbit(raw), 0, -1).astype(np.int32)
+    edge = F32(float(alpha) * (1.0 + 1.0 / (levels - 1)))
+    trusted = (zero[:, None] | (np.abs(raw) <= ((edge * rms).astype(F32) * root).astype(F32)[:, None])).astype(np.uint8)
+    codes = np.empty((rows, cols * qo.container_bits(bits) // 8), dtype=np.uint8)
+    mask = np.empty((rows, cols // 8), dtype=np.uint8)
+    _load().qo_pack_codes(_ptr(np.ascontiguousarray(k)), rows, cols, bits, _ptr(codes))
+    _load().qo_pack_mask(_ptr(np.ascontiguousarray(trusted)), rows, cols, _ptr(mask))
+    scale = (clip / F32(levels - 1)).astype(F32)
+    assert np.array_equal(got["scales"].view(np.uint32), scale.view(np.uint32)), "scales differ in some bit"
+    assert np.array_equal(got["codes"], codes), f"{int((got['codes'] != codes).sum())} code bytes differ"
+    assert np.array_equal(got["mask"], mask), f"{int((got['mask'] != mask).sum())} mask bytes differ"
