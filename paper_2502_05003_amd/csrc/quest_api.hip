@@ -640,6 +640,8 @@ quest_status quest_init(void)
         if (err == hipSuccess)
             err = quest::prepare_lowbit_gemm_kernels();
         if (err == hipSuccess)
+            err = quest::prepare_skinny_gemm_kernels();
+        if (err == hipSuccess)
             err = quest::prepare_fp4_gemm_kernels();
         if (err == hipSuccess)
             err = quest::prepare_trust_backward_kernels();

@@ -169,6 +169,7 @@ hipError_t prepare_quantize_rows_kernels();
 hipError_t prepare_trust_backward_rows_kernels();
 hipError_t prepare_trust_backward_mfma_kernels();
 hipError_t prepare_lowbit_gemm_kernels();
+hipError_t prepare_skinny_gemm_kernels();
 hipError_t prepare_fp4_gemm_kernels();
 hipError_t prepare_trust_backward_kernels();
 hipError_t prepare_grad_gemm_kernels();

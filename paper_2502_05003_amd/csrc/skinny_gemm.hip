@@ -335,6 +335,14 @@ bool skinny_gemm_preferred(int64_t M, int64_t N, int64_t K, int grid)
     return block_count(M, N, 4, 4) <= (!tiles ? 2048 : grid == 1 || grid == 2 ? 768 : 256);
 }
 
+// Makes the runtime load this file's code object now (a query of one kernel's attributes does), so
+// that the first launch, which may be under graph capture, does not.
+hipError_t prepare_skinny_gemm_kernels()
+{
+    hipFuncAttributes attr;
+    return hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(skinny_gemm_kernel<4, 1, 1, 2>));
+}
+
 hipError_t launch_skinny_gemm(const SkinnyGemmArgs &a, hipStream_t stream)
 {
     switch (a.grid) {

@@ -58,3 +58,35 @@ def test_fp4_grid(M, N, K):
     ref = qo.unpack_fp4(a, K).astype(np.float64) @ qo.unpack_fp4(b, K).astype(np.float64).T
     assert np.array_equal(acc.cpu().numpy().astype(np.float64), ref)
     check_gemm_output(y, ref, sa, sb)
+
+
+def test_a_captured_decode_step_replays_on_new_inputs():
+    """Quantizer and product of a decode step captured with no call of either before it in this stream (only
+    quest_init): every replay gives the bytes of eager calls on the same inputs."""
+    M, N, K, n, bits = 24, 2048, 2560, 512, 4
+    q.quest_init()
+    x = torch.empty(M, K, dtype=torch.bfloat16, device=DEV)
+    w_codes = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV)
+    w_scales = torch.rand(N, device=DEV) * 0.01 + 0.005
+
+    def step():
+        codes = torch.empty(M, K // 2, dtype=torch.uint8, device=DEV)
+        scales = torch.empty(M, device=DEV)
+        y = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
+        q.quest_hadamard_quantize(x, n, bits, codes=codes, scales=scales)
+        q.quest_lowbit_gemm(codes, scales, w_codes, w_scales, K, bits, y=y)
+        return codes, scales, y
+
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            captured = step()
+    for seed in range(3):
+        x.copy_(torch.randn(M, K, generator=torch.Generator().manual_seed(seed)).bfloat16())
+        eager = step()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(captured, eager):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), seed

@@ -91,3 +91,20 @@ def test_binding_has_no_fallback_when_the_library_is_missing(tmp_path, monkeypat
     monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "libquest.so"))
     with pytest.raises(FileNotFoundError):
         binding.quest_alpha_star(4)
+
+
+def test_quest_init_prepares_every_file_that_launches_kernels():
+    """The first launch of a kernel makes the runtime load its file's code object, which a capture must not:
+    each source file with launches has one set-up function, and quest_init calls them all."""
+    import re
+    csrc = os.path.join(ROOT, "paper_2502_05003_amd", "csrc")
+    init = open(os.path.join(csrc, "quest_api.hip")).read().split("quest_status quest_init(void)")[1]
+    called = set(re.findall(r"quest::(prepare_\w+)\(\)", init))
+    defined = set()
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        if name.endswith(".hip") and "hipLaunchKernelGGL" in text and name != "peak_probe.hip":
+            own = re.findall(r"^hipError_t (prepare_\w+_kernels)\(\)", text, flags=re.M)
+            assert len(own) == 1, f"{name}: set-up functions {own}"
+            defined.update(own)
+    assert called == defined
