@@ -237,11 +237,20 @@ hipError_t prepare_fp4_gemm_kernels()
     });
 }
 
+quest_plan plan_fp4_gemm(int64_t M, int64_t N, int64_t K)
+{
+    if (skinny_gemm_preferred(M, N, K, 0))
+        return {QUEST_PLAN_FEW, 0, 0, 0};
+    const int64_t big_tiles = ((M + Tile<4>::kRows - 1) / Tile<4>::kRows) * ((N + TN - 1) / TN);
+    return {QUEST_PLAN_TILES, big_tiles < kFewTiles ? Tile<2>::kRows : Tile<4>::kRows, TN, 0};
+}
+
 hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream)
 {
     if (a.M == 0 || a.N == 0)
         return hipSuccess;
-    if (skinny_gemm_preferred(a.M, a.N, a.K, 0)) {
+    const quest_plan plan = plan_fp4_gemm(a.M, a.N, a.K);
+    if (plan.kernel == QUEST_PLAN_FEW) {
         const SkinnyGemmArgs few = {a.a_codes, a.a_scales, a.b_codes, a.b_scales, a.M, a.N,
                                     a.K, 0, a.y, a.ld_y, a.acc_out};
         return launch_skinny_gemm(few, stream);
@@ -249,8 +258,7 @@ hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream)
     const hipError_t attr_err = prepare_fp4_gemm_kernels();
     if (attr_err != hipSuccess)
         return attr_err;
-    const int64_t big_tiles = ((a.M + Tile<4>::kRows - 1) / Tile<4>::kRows) * ((a.N + TN - 1) / TN);
-    return big_tiles < kFewTiles ? launch<2>(a, stream) : launch<4>(a, stream);
+    return plan.block_rows == Tile<2>::kRows ? launch<2>(a, stream) : launch<4>(a, stream);
 }
 
 }  // namespace quest

@@ -789,3 +789,13 @@ hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)
 }
 
 }  // namespace quest
+
+quest_plan quest_plan_grad_gemm(int32_t form, int32_t fp4, int64_t M, int64_t N, int64_t K, int32_t cus)
+{
+    const quest::GradGemmPlan p = quest::plan_grad_gemm(form, fp4 != 0, M, N, K, cus);
+    if (!p.covered)
+        return {QUEST_PLAN_NONE, 0, 0, 0};
+    if (p.mid)
+        return quest::grad_gemm_mid_plan(p.contraction, p.out_rows, p.out_cols, cus);
+    return {p.split ? QUEST_PLAN_SPLIT : QUEST_PLAN_TILES, 64 * p.ti, quest::GT, p.split ? 1 : p.per_block / p.steps};
+}

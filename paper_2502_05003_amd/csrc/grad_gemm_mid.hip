@@ -548,6 +548,12 @@ hipError_t prepare_mode()
 
 }  // namespace
 
+quest_plan grad_gemm_mid_plan(int64_t C, int64_t R, int64_t K, int cus)
+{
+    const Shape &s = kShapes[cheapest_shape(C, R, K, cus)];
+    return {QUEST_PLAN_MID, 64 * s.wi, 64 * s.wj, s.groups};
+}
+
 double grad_gemm_mid_cost(int64_t C, int64_t R, int64_t K, int cus)
 {
     return shape_cost(kShapes[cheapest_shape(C, R, K, cus)], C, R, K, cus);

@@ -190,13 +190,26 @@ hipError_t prepare_quantize_kernels()
     return err;
 }
 
+namespace {
+
+// the kernel for a call of `rows` rows (of both operands)
+int kernel_for(const QuantizeArgs &a, int64_t rows)
+{
+    if (quantize_rows_preferred(a, rows))
+        return QUEST_PLAN_ROWS;
+    return launch_hadamard_quantize_mfma(a, nullptr, true) ? QUEST_PLAN_INSTANCE : QUEST_PLAN_GENERAL;
+}
+
+}  // namespace
+
 hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
 {
     if (a.rows2 != 0) {
         // two operands: one launch where a matrix-core kernel covers the shape, else one after the other
-        if (quantize_rows_preferred(a, a.rows + a.rows2))
+        const int kernel = kernel_for(a, a.rows + a.rows2);
+        if (kernel == QUEST_PLAN_ROWS)
             return launch_hadamard_quantize_rows(a, stream);
-        if (a.rows != 0 && launch_hadamard_quantize_mfma(a, stream))
+        if (kernel == QUEST_PLAN_INSTANCE && a.rows != 0 && launch_hadamard_quantize_mfma(a, stream))
             return hipGetLastError();
         QuantizeArgs first = a, second = a;
         first.x2 = nullptr;
@@ -215,9 +228,10 @@ hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
     }
     if (a.rows == 0)
         return hipSuccess;
-    if (quantize_rows_preferred(a, a.rows))
+    const int kernel = kernel_for(a, a.rows);
+    if (kernel == QUEST_PLAN_ROWS)
         return launch_hadamard_quantize_rows(a, stream);
-    if (launch_hadamard_quantize_mfma(a, stream))
+    if (kernel == QUEST_PLAN_INSTANCE && launch_hadamard_quantize_mfma(a, stream))
         return hipGetLastError();
     const int cols = (int)a.cols;
     const size_t lds_bytes = (size_t)(cols + (cols >> 5) + 1) * sizeof(float);
@@ -226,21 +240,21 @@ hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
     const dim3 block(kGenericThreads);
     hipError_t err = hipSuccess;
     if (a.dtype == QUEST_BF16) {
-        auto kernel = hq_generic_kernel<uint16_t>;
+        auto general = hq_generic_kernel<uint16_t>;
         if (lds_bytes > 48 * 1024)
-            err = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), (int)lds_bytes);
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(general), (int)lds_bytes);
         if (err != hipSuccess)
             return err;
-        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, stream,
+        hipLaunchKernelGGL(general, grid, block, lds_bytes, stream,
                            static_cast<const uint16_t *>(a.x), a.rows, cols, a.ld, a.log2n, a.bits,
                            a.cb, a.alpha, a.trust_edge, a.mode, a.codes, a.scales, a.mask, a.xh_out);
     } else {
-        auto kernel = hq_generic_kernel<float>;
+        auto general = hq_generic_kernel<float>;
         if (lds_bytes > 48 * 1024)
-            err = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), (int)lds_bytes);
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(general), (int)lds_bytes);
         if (err != hipSuccess)
             return err;
-        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, stream,
+        hipLaunchKernelGGL(general, grid, block, lds_bytes, stream,
                            static_cast<const float *>(a.x), a.rows, cols, a.ld, a.log2n, a.bits,
                            a.cb, a.alpha, a.trust_edge, a.mode, a.codes, a.scales, a.mask, a.xh_out);
     }
@@ -248,3 +262,15 @@ hipError_t launch_hadamard_quantize(const QuantizeArgs &a, hipStream_t stream)
 }
 
 }  // namespace quest
+
+quest_plan quest_plan_quantize(int32_t mode, int32_t f32, int64_t rows, int64_t cols, int32_t had_block, int32_t bits)
+{
+    quest::QuantizeArgs a = {};
+    a.dtype = f32 ? QUEST_F32 : QUEST_BF16;
+    a.mode = mode;
+    a.bits = bits;
+    a.cols = cols;
+    while ((1 << a.log2n) < had_block)
+        ++a.log2n;
+    return {quest::kernel_for(a, rows), 0, 0, 0};
+}

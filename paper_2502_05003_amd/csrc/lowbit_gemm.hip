@@ -835,19 +835,60 @@ hipError_t prepare_lowbit_gemm_kernels()
     });
 }
 
+quest_plan plan_lowbit_gemm(int64_t M, int64_t N, int64_t K, int bits, bool with_workspace)
+{
+    if (skinny_gemm_preferred(M, N, K, bits))
+        return {QUEST_PLAN_FEW, 0, 0, 0};
+    // 1 and 2 bits with scratch from the caller: re-code, then the 4-bit tile kernels.  Without
+    // scratch the general kernel multiplies the narrow containers directly (slower).
+    const int recodes = recode_path(M, N, K, bits) && with_workspace ? 2 : 0;
+    if (recodes == 0 && bits <= 2)
+        return {QUEST_PLAN_GENERAL, BM, BN, 0};
+    // the wide kernel runs one workgroup per CU: it needs about a round of 256 x 256 tiles to fill the chip
+    const int64_t wide_tiles = ((M + WTM - 1) / WTM) * ((N + WTN - 1) / WTN);
+    if ((K % WTK) == 0 && K >= 4096 && M >= 512 && N >= 512 && wide_tiles >= 192)
+        return {QUEST_PLAN_TILES, WTM, WTN, recodes};
+    // fewer 256 x 128 tiles than three quarters of the chip's slots (two per CU): 128 x 128 tiles
+    const int64_t big_tiles = ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
+    if ((K % TK) == 0 && M > 64 && N >= 128 && big_tiles < 384)
+        return {QUEST_PLAN_TILES, STM, STN, recodes};
+    if ((K % TK) == 0 && M >= 512 && N >= 256)
+        return {QUEST_PLAN_TILES, TM, TN, recodes};
+    return {QUEST_PLAN_GENERAL, BM, BN, recodes};
+}
+
+namespace {
+
+// a tile kernel: one workgroup per tile, every XCD the same number
+template <typename Kernel>
+hipError_t launch_tiles(Kernel kernel, const quest_plan &plan, int threads, int lds, const GemmArgs &a, hipStream_t stream)
+{
+    const int tiles_m = (int)((a.M + plan.block_rows - 1) / plan.block_rows);
+    const int tiles_n = (int)((a.N + plan.block_cols - 1) / plan.block_cols);
+    const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+    const hipError_t err = prepare_lowbit_gemm_kernels();
+    if (err != hipSuccess)
+        return err;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * 8)), dim3((unsigned)threads), lds, stream, a.a_codes, a.a_scales,
+                       a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n,
+                       static_cast<uint16_t *>(a.y), a.ld_y, a.acc_out);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_lowbit_gemm(const GemmArgs &args, hipStream_t stream)
 {
     if (args.M == 0 || args.N == 0)
         return hipSuccess;
-    if (skinny_gemm_preferred(args.M, args.N, args.K, args.bits)) {
+    const quest_plan plan = plan_lowbit_gemm(args.M, args.N, args.K, args.bits, args.workspace != nullptr);
+    if (plan.kernel == QUEST_PLAN_FEW) {
         const SkinnyGemmArgs few = {args.a_codes, args.a_scales, args.b_codes, args.b_scales, args.M, args.N,
                                     args.K, args.bits, args.y, args.ld_y, args.acc_out};
         return launch_skinny_gemm(few, stream);
     }
     GemmArgs a = args;
-    // 1 and 2 bits with scratch from the caller: re-code, then the 4-bit tile kernels.  Without
-    // scratch the general kernel below multiplies the narrow containers directly (slower).
-    if (recode_path(a.M, a.N, a.K, a.bits) && a.workspace != nullptr) {
+    if (plan.count != 0) {
         if (a.workspace_bytes < lowbit_gemm_workspace_bytes(a.M, a.N, a.K, a.bits))
             return hipErrorInvalidValue;
         uint8_t *a_nibbles = static_cast<uint8_t *>(a.workspace);
@@ -862,64 +903,18 @@ hipError_t launch_lowbit_gemm(const GemmArgs &args, hipStream_t stream)
         a.bits = 4;
         a.cb = 4;
     }
+    if (plan.kernel == QUEST_PLAN_TILES) {
+        if (plan.block_cols == WTN)
+            return a.bits == 4 ? launch_tiles(lowbit_gemm_wide_kernel<4>, plan, kWideThreads, kWideLds, a, stream)
+                               : launch_tiles(lowbit_gemm_wide_kernel<3>, plan, kWideThreads, kWideLds, a, stream);
+        if (plan.block_rows == STM)
+            return a.bits == 4 ? launch_tiles(lowbit_gemm_small_kernel<4>, plan, kTileThreads, kSmallLds, a, stream)
+                               : launch_tiles(lowbit_gemm_small_kernel<3>, plan, kTileThreads, kSmallLds, a, stream);
+        return a.bits == 4 ? launch_tiles(lowbit_gemm_tile_kernel<4>, plan, kTileThreads, kTileLds, a, stream)
+                           : launch_tiles(lowbit_gemm_tile_kernel<3>, plan, kTileThreads, kTileLds, a, stream);
+    }
     const int levels = 1 << a.bits;
     auto *y = static_cast<uint16_t *>(a.y);
-    // the wide kernel runs one workgroup per CU: it needs about a round of 256 x 256 tiles to fill the chip
-    const int64_t wide_tiles = ((a.M + WTM - 1) / WTM) * ((a.N + WTN - 1) / WTN);
-    if ((a.bits == 4 || a.bits == 3) && (a.K % WTK) == 0 && a.K >= 4096 && a.M >= 512 && a.N >= 512 &&
-        wide_tiles >= 192) {
-        const int tiles_m = (int)((a.M + WTM - 1) / WTM), tiles_n = (int)((a.N + WTN - 1) / WTN);
-        const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-        const hipError_t err = prepare_lowbit_gemm_kernels();
-        if (err != hipSuccess)
-            return err;
-        const dim3 grid((unsigned)(per_xcd * 8)), block(kWideThreads);
-        if (a.bits == 4)
-            hipLaunchKernelGGL(lowbit_gemm_wide_kernel<4>, grid, block, kWideLds, stream, a.a_codes, a.a_scales,
-                               a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, y, a.ld_y,
-                               a.acc_out);
-        else
-            hipLaunchKernelGGL(lowbit_gemm_wide_kernel<3>, grid, block, kWideLds, stream, a.a_codes, a.a_scales,
-                               a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, y, a.ld_y,
-                               a.acc_out);
-        return hipGetLastError();
-    }
-    // fewer 256 x 128 tiles than three quarters of the chip's slots (two per CU): 128 x 128 tiles
-    const int64_t big_tiles = ((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
-    if ((a.bits == 4 || a.bits == 3) && (a.K % TK) == 0 && a.M > 64 && a.N >= 128 && big_tiles < 384) {
-        const int tiles_m = (int)((a.M + STM - 1) / STM), tiles_n = (int)((a.N + STN - 1) / STN);
-        const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-        const hipError_t err = prepare_lowbit_gemm_kernels();
-        if (err != hipSuccess)
-            return err;
-        const dim3 grid((unsigned)(per_xcd * 8)), block(kTileThreads);
-        if (a.bits == 4)
-            hipLaunchKernelGGL(lowbit_gemm_small_kernel<4>, grid, block, kSmallLds, stream, a.a_codes, a.a_scales,
-                               a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, y, a.ld_y,
-                               a.acc_out);
-        else
-            hipLaunchKernelGGL(lowbit_gemm_small_kernel<3>, grid, block, kSmallLds, stream, a.a_codes, a.a_scales,
-                               a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, y, a.ld_y,
-                               a.acc_out);
-        return hipGetLastError();
-    }
-    if ((a.bits == 4 || a.bits == 3) && (a.K % TK) == 0 && a.M >= 512 && a.N >= 256) {
-        const int tiles_m = (int)((a.M + TM - 1) / TM), tiles_n = (int)((a.N + TN - 1) / TN);
-        const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-        const hipError_t err = prepare_lowbit_gemm_kernels();
-        if (err != hipSuccess)
-            return err;
-        const dim3 grid((unsigned)(per_xcd * 8)), block(kTileThreads);
-        if (a.bits == 4)
-            hipLaunchKernelGGL(lowbit_gemm_tile_kernel<4>, grid, block, kTileLds, stream, a.a_codes, a.a_scales,
-                               a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, y, a.ld_y,
-                               a.acc_out);
-        else
-            hipLaunchKernelGGL(lowbit_gemm_tile_kernel<3>, grid, block, kTileLds, stream, a.a_codes, a.a_scales,
-                               a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, y, a.ld_y,
-                               a.acc_out);
-        return hipGetLastError();
-    }
     const dim3 grid((unsigned)((a.N + BN - 1) / BN), (unsigned)((a.M + BM - 1) / BM));
     const dim3 block(kThreads);
     switch (a.cb) {

@@ -624,6 +624,11 @@ quest_status quest_weight_only_gemm(const void *x, const uint8_t *w_codes, const
                              stream);
 }
 
+quest_plan quest_plan_forward(int32_t bits, int64_t M, int64_t N, int64_t K, int32_t with_workspace)
+{
+    return bits == 0 ? quest::plan_fp4_gemm(M, N, K) : quest::plan_lowbit_gemm(M, N, K, bits, with_workspace != 0);
+}
+
 quest_status quest_init(void)
 {
     static quest::OncePerDevice once;

@@ -8,6 +8,7 @@
 #include <atomic>
 
 #include "../../include/quest.h"
+#include "../../include/quest_plan.h"
 
 namespace quest {
 
@@ -60,6 +61,7 @@ struct GemmArgs {
 };
 
 hipError_t launch_lowbit_gemm(const GemmArgs &a, hipStream_t stream);
+quest_plan plan_lowbit_gemm(int64_t M, int64_t N, int64_t K, int bits, bool with_workspace);
 // Scratch the fast path of a 1- or 2-bit product needs (both operands re-coded as nibbles); 0 when the
 // shape or the bit width does not take that path.
 int64_t lowbit_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int bits);
@@ -76,6 +78,7 @@ struct Fp4GemmArgs {
 };
 
 hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream);
+quest_plan plan_fp4_gemm(int64_t M, int64_t N, int64_t K);
 
 // The forward product for few activation rows, on either grid.
 struct SkinnyGemmArgs {
@@ -146,6 +149,8 @@ struct GradMidArgs {
 
 // every shape of multiples of 64; E2M1 codes for modes 0 and 1 only
 hipError_t launch_grad_gemm_mid(const GradMidArgs &a, hipStream_t stream);
+// the block of the kernel the call gets (kernel, block_rows, block_cols, count)
+quest_plan grad_gemm_mid_plan(int64_t C, int64_t R, int64_t K, int cus);
 // what the call is expected to take, us
 double grad_gemm_mid_cost(int64_t C, int64_t R, int64_t K, int cus);
 

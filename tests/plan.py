@@ -1,0 +1,39 @@
+"""Which kernel a call runs, asked of the library (include/quest_plan.h): for tests that must reach a certain one.
+No GPU needed."""
+import ctypes
+from collections import namedtuple
+
+from paper_2502_05003_amd import binding as q
+
+CUS = 256                                                      # compute units of an MI355X
+GENERAL, INSTANCE, ROWS, FEW, TILES, SPLIT, MID = range(7)     # quest_plan_kernel
+Plan = namedtuple("Plan", "kernel rows cols count")
+
+
+class _Plan(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int32) for name in ("kernel", "block_rows", "block_cols", "count")]
+
+
+def _ask(name, *args):
+    function = getattr(q.load(), name)
+    function.restype = _Plan
+    p = function(*args)
+    return Plan(p.kernel, p.block_rows, p.block_cols, p.count)
+
+
+def _i64(*values):
+    return [ctypes.c_int64(v) for v in values]
+
+
+def grad_gemm(form, M, N, K, fp4=False):
+    return _ask("quest_plan_grad_gemm", form, int(fp4), *_i64(M, N, K), CUS)
+
+
+def forward(M, N, K, bits, workspace=True):
+    """bits = 0: E2M1 codes"""
+    return _ask("quest_plan_forward", bits, *_i64(M, N, K), int(workspace))
+
+
+def quantize(rows, cols, block, bits, dtype, absmax=False, fp4=False):
+    return _ask("quest_plan_quantize", 1 if absmax else 2 if fp4 else 0, int(dtype == "f32"), *_i64(rows, cols), block,
+                bits).kernel

@@ -12,11 +12,15 @@ from gpu_util import DEV, check_gemm_output, to_device
 
 pytestmark = pytest.mark.gpu
 
-# M, N, K, extra output pitch.  All beyond the few-rows kernel (more than 256 blocks of 64 x 64).  Row pitches of
-# every kind (odd, even, multiple of 8), last tiles of 1, 3, 4 and 128 rows and of 1, 2, 6, 8 and 72 columns, one
-# to nine contraction steps; the last shape has enough tiles of 256 rows for those.
+# M, N, K, extra output pitch.  All beyond the few-rows kernel (more than 256 blocks of 64 x 64 at 3 and 4 bits and
+# E2M1).  Row pitches of every kind (odd, even, multiple of 8), last tiles of 1, 3, 4 and 128 rows and of 1, 2, 6, 8
+# and 72 columns, one to nine contraction steps, one tile row that is not full; (6145, 2050) has enough tiles of
+# 256 rows for those.
 SHAPES = [(1025, 1153, 128, 0), (1027, 1154, 256, 0), (1280, 1032, 384, 0), (1092, 1224, 1152, 3),
-          (1025, 1158, 128, 2), (2049, 520, 384, 1), (6145, 2050, 128, 0)]
+          (1025, 1158, 128, 2), (2049, 520, 384, 1), (6145, 2050, 128, 0), (65, 8321, 128, 0), (127, 8200, 384, 2)]
+# 2 bits, re-coded: more than 768 blocks
+RECODED = [(2049, 1601, 128, 0), (1793, 1858, 256, 0), (3073, 1032, 384, 1)]
+INTEGER_CASES = [(*shape, bits) for shape in SHAPES for bits in (3, 4)] + [(*shape, 2) for shape in RECODED]
 
 
 def _scales(rng, M, N):
@@ -39,8 +43,7 @@ def test_fp4_grid(M, N, K, pad):
     assert torch.all(y[:, N:] == 7.0)
 
 
-@pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("M,N,K,pad", SHAPES)
+@pytest.mark.parametrize("M,N,K,pad,bits", INTEGER_CASES)
 def test_integer_grids(M, N, K, pad, bits):
     rng = np.random.default_rng(M + N + K + bits)
     L, cb = 1 << bits, qo.container_bits(bits)

@@ -9,6 +9,7 @@ from oracle import quest_oracle as qo
 from paper_2502_05003_amd import binding as q
 from paper_2502_05003_amd import synth
 
+import plan
 from gpu_util import (BF16_HALF_ULP, DEV, check_gemm_output, compare_quantizer, compare_quantizer_fp4, gpu_quantize,
                       grad_ws, lowbit_ws, to_device, to_host_f64, weight_only_ws)
 
@@ -385,9 +386,12 @@ GEMM_CASES = [(256, 512, 512, 4), (130, 200, 1024, 4), (1, 1, 64, 4), (257, 129,
               (4096, 4090, 256, 4), (4096, 4096, 128, 4), (4000, 4100, 384, 4),
               # b = 3 on the tile kernels (one more shift in the widening, products carry 256)
               (700, 600, 512, 3), (768, 512, 5632, 3), (513, 1025, 1024, 3),
-              # b = 1, 2 re-coded to nibbles for the tile kernels (and for the wide one at K = 5632)
-              (700, 600, 512, 2), (513, 1025, 1024, 1), (768, 512, 5632, 2), (768, 512, 5632, 1),
-              (4000, 4100, 384, 1), (512, 256, 128, 2),
+              # b = 1, 2 as they are, by the kernel for few rows
+              (700, 600, 512, 2), (513, 1025, 1024, 1), (768, 512, 5632, 2), (768, 512, 5632, 1), (512, 256, 128, 2),
+              # b = 1, 2 re-coded to nibbles for the tile kernels, or without scratch by the general kernel
+              (4000, 4100, 384, 1), (2000, 2100, 384, 2),
+              # an odd number of half steps on the general kernel
+              (2944, 2945, 192, 4), (2944, 2945, 64, 3),
               # more 256 x 128 tiles than the chip's workgroup slots, with a remainder and a ragged last tile row
               (4090, 5000, 256, 4), (4090, 5000, 128, 3)]
 
@@ -450,12 +454,15 @@ def test_gemm_full_size_sampled_rows():
     assert np.linalg.norm(got - exact) / np.linalg.norm(exact) < 0.25
 
 
-@pytest.mark.parametrize("M,N,K,bits", [(4000, 4100, 384, 3),      # 256 x 128 tiles, ragged edges
-                                        (4090, 3100, 4096, 3), (4090, 3100, 4352, 4),   # 256 x 256 tiles
-                                        (3000, 1100, 640, 4), (3000, 1100, 640, 3)])    # 128 x 128 tiles
-def test_gemm_kernel_variants_sampled_rows(M, N, K, bits):
-    """Every tile size of the matmul at b = 3 and b = 4, ragged last tiles, random codes with extreme
-    rows: accumulators of sampled rows (first, last, rows around tile edges) against the oracle."""
+@pytest.mark.parametrize("M,N,K,bits,tile", [(4000, 4100, 384, 3, 256),      # 256 x 128 tiles, ragged edges
+                                             (4090, 3100, 4096, 3, 512), (4090, 3100, 4352, 4, 512),   # 256 x 256 tiles
+                                             (4090, 3100, 4352, 2, 512), (4090, 3100, 4096, 1, 512),   # re-coded
+                                             (3000, 1100, 640, 4, 128), (3000, 1100, 640, 3, 128)])    # 128 x 128 tiles
+def test_gemm_kernel_variants_sampled_rows(M, N, K, bits, tile):
+    """Every tile size of the matmul at b = 3 and b = 4, the wide one also re-coded from b = 1 and 2, ragged last
+    tiles, random codes with extreme rows: accumulators of sampled rows (first, last, rows around tile edges)
+    against the oracle."""
+    assert plan.forward(M, N, K, bits) == (plan.TILES, min(tile, 256), 256 if tile == 512 else 128, 2 if bits < 3 else 0)
     rng = np.random.default_rng(M + N + K + bits)
     L = 1 << bits
     ka = rng.integers(-L // 2, L // 2, size=(M, K), dtype=np.int32)
@@ -464,15 +471,17 @@ def test_gemm_kernel_variants_sampled_rows(M, N, K, bits):
     kb[0] = L // 2 - 1
     kb[N - 1] = -L // 2
     from oracle.quest_oracle import _load, _ptr
-    a_codes = np.empty((M, K // 2), dtype=np.uint8)
-    b_codes = np.empty((N, K // 2), dtype=np.uint8)
+    cb = qo.container_bits(bits)
+    a_codes = np.empty((M, K * cb // 8), dtype=np.uint8)
+    b_codes = np.empty((N, K * cb // 8), dtype=np.uint8)
     _load().qo_pack_codes(_ptr(ka), M, K, bits, _ptr(a_codes))
     _load().qo_pack_codes(_ptr(kb), N, K, bits, _ptr(b_codes))
     sa = (rng.random(M) + 0.5).astype(np.float32)
     sb = ((rng.random(N) + 0.5) * 0.01).astype(np.float32)
     y = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
     acc = torch.empty(M, N, dtype=torch.int32, device=DEV)
-    q.quest_lowbit_gemm(to_device(a_codes), to_device(sa), to_device(b_codes), to_device(sb), K, bits, y=y, acc_out=acc)
+    q.quest_lowbit_gemm(to_device(a_codes), to_device(sa), to_device(b_codes), to_device(sb), K, bits, y=y, acc_out=acc,
+                        workspace=lowbit_ws(M, N, K, bits))
     torch.cuda.synchronize()
     rows = np.unique(np.concatenate([[0, 1, 127, 128, 255, 256, M - 257, M - 129, M - 2, M - 1],
                                      rng.choice(M, size=24, replace=False)]))
@@ -648,18 +657,17 @@ def test_trust_backward_full_size_headline_shape():
 
 
 @pytest.mark.parametrize("M,N,K", [(192, 128, 256), (512, 256, 512), (768, 512, 256),
-                                   # few tiles, long contraction: tiles split between workgroups,
-                                   # evenly (12 steps over 4) and unevenly (128 steps in threes)
-                                   (768, 8192, 512), (8192, 768, 512),
-                                   # more tiles than CUs, two steps each: whole tiles and halves mixed
+                                   # few tiles, long contraction: which = 0 of the first and which = 1 of the
+                                   # second split tiles between workgroups
+                                   (576, 12288, 128), (16384, 576, 320), (768, 8192, 512), (8192, 768, 512),
+                                   # more blocks than CUs, two steps each
                                    (5120, 128, 3840), (128, 5120, 3840),
                                    # outputs that end inside a tile (hidden 640 and 1664 of the paper's models)
                                    (640, 1664, 384), (1664, 640, 896), (320, 192, 448), (4096, 640, 1664)])
 @pytest.mark.parametrize("which", [0, 1])
 def test_grad_gemm_matches_oracle(which, M, N, K):
-    """Small shapes run the 64x64 kernel; outputs of at least half a 256x256 tile each way run the
-    main kernel (edge tiles may be partial), which splits tiles between workgroups when whole tiles
-    would leave CUs idle."""
+    """Small shapes run the kernels that expand the codes on the way into LDS; larger ones the main kernel (edge
+    tiles may be partial), which splits tiles between workgroups when whole tiles would leave CUs idle."""
     bits, n = 4, min(256, K & -K)
     x = synth.gaussian(M, K, 1.0, 11, "bf16")
     w = synth.gaussian(N, K, 0.02, 12, "bf16")
@@ -690,8 +698,8 @@ def test_grad_gemm_matches_oracle(which, M, N, K):
 
 
 def test_grad_gemm_full_size_sampled_rows():
-    """Both gradient matmuls at M=16384, N=5632, K=2048 (the launch shapes the benchmark times, the
-    weight gradient with its tiles split over the CUs); sampled output rows against the oracle."""
+    """Both gradient matmuls at M=16384, N=5632, K=2048 (the launch shapes the benchmark times);
+    sampled output rows against the oracle."""
     x, w, cfg = synth.make_config("mlp_up_1p6b", seed=0)
     K, bits, n = cfg["K"], cfg["bits"], cfg["had_block"]
     M, N = x.shape[0], w.shape[0]
@@ -861,7 +869,8 @@ def test_7b_layers_whole_step_sampled(name):
 
 @pytest.mark.parametrize("M,N,K,bits", [(256, 256, 64, 4), (512, 256, 2048, 4), (256, 768, 320, 2),
                                         (768, 512, 1024, 1), (256, 256, 5632, 3),
-                                        (4096, 2304, 128, 4),   # 144 tiles: split over the CUs
+                                        (4096, 2304, 128, 4),   # two steps in many blocks
+                                        (256, 1280, 11008, 4),  # five tiles split over the CUs
                                         (640, 1664, 384, 4), (192, 320, 448, 2)])   # outputs ending inside a tile
 def test_weight_only_gemm_matches_oracle(M, N, K, bits):
     """Sec. 4.4: bf16 activations in the Hadamard domain (the transform alone is the trust
@@ -893,10 +902,15 @@ def test_weight_only_gemm_matches_oracle(M, N, K, bits):
     print(f"b={bits}: relative error against x w^T {np.linalg.norm(got - exact) / np.linalg.norm(exact):.3f}")
 
 
+# a weight gradient whose tiles are split over the CUs (four tiles with a contraction of 384 steps)
+SPLIT = (12288, 512, 512)
+
+
 def test_split_tiles_are_summed_in_a_fixed_order():
-    """The weight gradient at the headline shape has its tiles split over the CUs; the partial tiles
-    are added in workgroup order, so two runs (with other work in between) agree bit for bit."""
-    M, N, K, bits = 8192, 768, 512, 4
+    """A weight gradient with its tiles split over the CUs; the partial tiles are added in workgroup
+    order, so two runs (with other work in between) agree bit for bit."""
+    (M, N, K), bits = SPLIT, 4
+    assert plan.grad_gemm(1, M, N, K).kernel == plan.SPLIT
     x = synth.gaussian(M, K, 1.0, 1, "bf16")
     dy = to_device(synth.upstream_gradient(M, N, 2, "bf16"))
     gx = gpu_quantize(x, 512, bits, want_xh=False, want_mask=False)
@@ -914,14 +928,14 @@ def test_split_tiles_are_summed_in_a_fixed_order():
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[1], outs[2])
 
 
-@pytest.mark.parametrize("which,M,N,K", [(1, 8192, 2560, 2304), (0, 2560, 8192, 2304), (1, 4096, 2368, 2560)])
+@pytest.mark.parametrize("which,M,N,K", [(1, 16384, 2112, 1088), (0, 448, 12288, 832), (1, 12288, 448, 832)])
 def test_split_tiles_mid_size_alternating_inputs(which, M, N, K):
-    """Ninety-odd tiles with a long contraction over 256 CUs: every tile is shared by three or four
-    workgroups (the benchmark's weight-gradient situation at a size whose whole output can be
-    checked).  The whole output against the fp64 product of the same 16-bit operands, sampled rows
-    against the oracle, and runs on alternating inputs over one workspace bit-identical (a stale
-    partial tile from the call before would show)."""
-    bits, n = 4, 256
+    """A few tiles (45 and 8) with a long contraction over 256 CUs: every tile is shared by several
+    workgroups, at sizes whose whole output can be checked.  The whole output against the fp64 product
+    of the same 16-bit operands, sampled rows against the oracle, and runs on alternating inputs over one
+    workspace bit-identical (a stale partial tile from the call before would show)."""
+    assert plan.grad_gemm(which, M, N, K).kernel == plan.SPLIT
+    bits, n = 4, 64
     src_rows, out_rows = (N, M) if which == 0 else (M, N)
     ws = grad_ws(which, M, N, K)
     results = {}
@@ -953,7 +967,7 @@ def test_split_tiles_mid_size_alternating_inputs(which, M, N, K):
 
 
 @pytest.mark.parametrize("which,M,N,K", [(0, 512, 256, 512), (1, 512, 256, 512), (0, 768, 8192, 512),
-                                          (1, 8192, 768, 512),
+                                          (1, 8192, 768, 512), (0, 576, 12288, 128), (1, 16384, 576, 320),   # split: the last two
                                           (0, 640, 1664, 384), (1, 1664, 640, 896)])   # outputs ending inside a tile
 def test_fp4_grad_gemm_matches_oracle(which, M, N, K):
     """Backward matmuls of the FP4 variant (Algorithm 2 on E2M1-coded operands), whole and split tiles."""
@@ -1014,9 +1028,10 @@ def test_whole_step_replayed_from_a_graph_matches_eager_launches():
     call) captured into one HIP graph with no eager call before the capture (only quest_init), then
     a larger gradient matmul run eagerly with scratch of its own, then replays on new input contents
     with eager work and synchronisations between them: every replay must reproduce, bit for bit,
-    what the step gives when launched eagerly as seven single-operand calls.  Shapes that split tiles
-    (second launch, partial tiles in the caller's workspace)."""
-    M, N, K, bits, n = 768, 8192, 512, 4, 512
+    what the step gives when launched eagerly as seven single-operand calls.  The input gradient splits
+    its tiles (second launch, partial tiles in the caller's workspace)."""
+    M, N, K, bits, n = 512, 12288, 512, 4, 512
+    assert plan.grad_gemm(0, M, N, K).kernel == plan.SPLIT
     dev = torch.device(DEV)
     q.quest_init()
 
@@ -1086,7 +1101,7 @@ def test_whole_step_replayed_from_a_graph_matches_eager_launches():
 def test_two_streams_with_two_workspaces_run_concurrently():
     """Two weight-gradient matmuls (split tiles: expanded operand and partial tiles in scratch) issued to
     two streams with a workspace each must give what each gives alone."""
-    M, N, K, bits = 8192, 768, 512, 4
+    (M, N, K), bits = SPLIT, 4
     dev = torch.device(DEV)
     jobs = []
     for seed in (1, 2):

@@ -1,0 +1,63 @@
+"""The GPU tests' cases against the dispatch rules, on the CPU: each kernel and block shape of the products that a
+rule can choose is run by a case that is listed for it.  A change of a rule that takes a case elsewhere fails here."""
+import pytest
+
+import plan
+import test_gpu_forward_edges as edges
+import test_gpu_mid_products as mid
+import test_gpu_parity as parity
+import test_gpu_tile_heights as tiles
+
+from paper_2502_05003_amd import binding as q
+
+
+@pytest.mark.parametrize("kernel,rows,several,form,C,R,cols,grid", tiles.RUNS)
+def test_tile_cases_are_where_they_are_listed(kernel, rows, several, form, C, R, cols, grid):
+    p = plan.grad_gemm(form, *tiles.layer(form, C, R, cols), fp4=grid == "fp4")
+    assert (p.kernel, p.rows, p.count > 1) == (kernel, rows, several)
+
+
+def test_tile_cases_have_every_height_in_every_form():
+    heights = {(case[3], case[0], case[1]) for case in tiles.CASES}
+    assert heights == {(form, plan.TILES, rows) for form in (0, 1, 2) for rows in (64, 128, 192, 256)} | \
+        {(form, plan.SPLIT, 256) for form in (0, 1, 2)}
+    assert {(case[0], case[1]) for case in tiles.RUNS if case[-1] == "fp4"} == {k[1:] for k in heights}
+
+
+def test_mid_cases_have_every_block_in_every_form_and_grid():
+    found = {}
+    for C, R, cols, form, grid in mid.CASES:
+        p = plan.grad_gemm(form, *tiles.layer(form, C, R, cols), fp4=grid == "fp4")
+        assert p.kernel == plan.MID
+        found.setdefault((form, grid), set()).add(p[1:])
+    blocks = {(64, 64, 2), (64, 64, 4), (64, 128, 1), (64, 128, 2), (128, 128, 1), (128, 128, 2)}
+    assert len(found) == 14 and all(b == blocks for b in found.values()), found
+
+
+def test_forward_cases_reach_the_tile_kernels():
+    for M, N, K, _ in edges.SHAPES:
+        assert plan.forward(M, N, K, 0).kernel == plan.TILES
+    assert {plan.forward(M, N, K, 0).rows for M, N, K, _ in edges.SHAPES} == {128, 256}
+    for M, N, K, _, bits in edges.INTEGER_CASES:
+        assert plan.forward(M, N, K, bits)[::3] == (plan.TILES, 2 if bits == 2 else 0)
+
+
+def test_forward_cases_reach_every_kernel():
+    found = {}
+    for M, N, K, bits, scratch in parity.GEMM_RUNS:
+        p = plan.forward(M, N, K, bits, scratch and q.quest_lowbit_gemm_workspace_bytes(M, N, K, bits) > 0)
+        found.setdefault(bits, set()).add((p.kernel, p.rows, p.cols))
+    general, few = (plan.GENERAL, 128, 128), (plan.FEW, 0, 0)
+    assert found[1] >= {few, general} and found[2] >= {few, general}
+    assert {k[0] for k in found[1]} >= {plan.TILES} and {k[0] for k in found[2]} >= {plan.TILES}
+    assert found[3] >= {few, general, (plan.TILES, 256, 128)} and found[4] >= {few, general, (plan.TILES, 256, 128)}
+
+
+def test_quantizer_kernels():
+    assert plan.quantize(24, 2560, 512, 4, "bf16") == plan.quantize(8192, 2560, 512, 4, "bf16") == plan.ROWS
+    assert plan.quantize(24, 2048, 2048, 4, "bf16") == plan.quantize(8192, 2048, 2048, 4, "bf16") == plan.INSTANCE
+    assert plan.quantize(24, 2048, 2048, 4, "f32") == plan.INSTANCE
+    assert plan.quantize(8192, 2048, 2048, 4, "f32") == plan.ROWS
+    import test_gpu_stage_isolated as stages
+    assert all(plan.quantize(rows, cols, n, bits, dtype) == plan.GENERAL for rows, cols, n, bits, dtype in stages.CASES)
+    assert all(plan.quantize(rows, cols, n, bits, dtype) == plan.ROWS for rows, cols, n, bits, dtype in stages.TILE_CASES)

@@ -8,6 +8,7 @@ import torch
 
 from paper_2502_05003_amd import binding as q
 
+import plan
 from gpu_util import DEV, lowbit_ws
 
 pytestmark = pytest.mark.gpu
@@ -26,10 +27,11 @@ def _operands(M, N, K, bits, seed):
 
 @pytest.mark.parametrize("bits", [2, 1])
 def test_static_scratch_entry_point_matches_the_workspace_one(bits):
-    # first call: 14 MiB of scratch, ragged tiles; second call: a smaller shape over the same buffer
-    for seed, (M, N, K) in enumerate([(9000, 5000, 2048), (700, 600, 512)]):
+    # first call: 14 MiB of scratch, ragged tiles; second call: a smaller shape over the same buffer, re-coded too
+    for seed, (M, N, K) in enumerate([(9000, 5000, 2048), (2000, 2100, 512)]):
         a, sa, b, sb = _operands(M, N, K, bits, seed)
         assert 0 < q.quest_lowbit_gemm_workspace_bytes(M, N, K, bits) <= 32 << 20
+        assert plan.forward(M, N, K, bits).count == 2
         y_ref = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
         acc_ref = torch.empty(M, N, dtype=torch.int32, device=DEV)
         q.quest_lowbit_gemm(a, sa, b, sb, K, bits, y=y_ref, acc_out=acc_ref, workspace=lowbit_ws(M, N, K, bits))
