@@ -336,13 +336,12 @@ hipError_t launch(const QuantizeArgs &a, hipStream_t stream)
     const int buffer = RowStaging<(int)sizeof(In)>::buffer_bytes((int)a.cols), groups = (int)((a.cols + 1024 * G - 1) / (1024 * G));
     const int64_t rows = a.rows + a.rows2;
     // A workgroup shares a row when there are few rows, and when sixteen waves' rows would not fit a compute
-    // unit's LDS (us, a row per wave / shared: 333 x 5120 8.8 / 5.8, 1400 x 2560 7.3 / 7.7,
-    // 8192 x 2560 16.1 / 20.5, 8192 x 11008 87 / 59; fp32 8192 x 5120 67 / 47).
+    // unit's LDS (us, a row per wave / shared, both 3 to 6 % more since codes are the floor of the product:
+    // 333 x 5120 8.8 / 5.8, 1400 x 2560 7.3 / 7.7, 8192 x 2560 16.1 / 20.5, 8192 x 11008 87 / 59; fp32 8192 x 5120 67 / 47).
     const bool shared_row = groups > 1 && (rows <= 1024 || buffer > 10 * 1024);
-    // waves per workgroup: four; fewer when a shared row has fewer groups of tiles, or when four rows would
-    // not fit a workgroup's LDS; sixteen waves per compute unit at most
-    const int waves = shared_row ? (groups < 4 ? groups : 4)   // one partial sum each
-                      : buffer <= 16 * 1024 ? 4 : buffer <= 32 * 1024 ? 2 : 1;
+    // waves per workgroup: four, fewer when a shared row has fewer groups of tiles (one partial sum each); sixteen
+    // per compute unit at most.  LDS: a shared row's buffer or, of rows of one group or of 10 KiB, four: 64 KiB at most.
+    const int waves = shared_row ? partial_sums_of_row((int)((a.cols + 1023) / 1024), G) : 4;
     const int lds = shared_row ? buffer : waves * buffer;
     if (lds > 48 * 1024) {
         const hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), 64 * 1024);
