@@ -448,7 +448,8 @@ hipError_t launch(const GradMidArgs &a, hipStream_t stream)
     const int tiles_r = (int)((a.R + 64 * WI - 1) / (64 * WI)), tiles_k = (int)((a.K + 64 * WJ - 1) / (64 * WJ));
     constexpr int kLds = GROUPS * 2 * (64 * WI + 64 * WJ) * GC * 2;
     if (kLds > 64 * 1024) {
-        const hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLds);
+        static OncePerDevice once;
+        const hipError_t err = once([&] { return allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLds); });
         if (err != hipSuccess)
             return err;
     }

@@ -344,7 +344,8 @@ hipError_t launch(const QuantizeArgs &a, hipStream_t stream)
     const int waves = shared_row ? partial_sums_of_row((int)((a.cols + 1023) / 1024), G) : 4;
     const int lds = shared_row ? buffer : waves * buffer;
     if (lds > 48 * 1024) {
-        const hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), 64 * 1024);
+        static OncePerDevice once;
+        const hipError_t err = once([&] { return allow_dynamic_lds(reinterpret_cast<const void *>(kernel), 64 * 1024); });
         if (err != hipSuccess)
             return err;
     }
