@@ -100,10 +100,17 @@ def _ptr(t: torch.Tensor | None):
     return None if t is None else t.data_ptr()      # the argtypes make it a pointer
 
 
+# Two functions of torch that are not part of its documented interface; without them _stream takes the documented way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
     """Handle of torch's current stream on the current device.  Asked for as a number: building the
     Stream object that holds it took 2.7 us, a third of a call (7.7 us, now 4.6)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _check(status: int, where: str):

@@ -90,3 +90,12 @@ def test_a_captured_decode_step_replays_on_new_inputs():
         torch.cuda.synchronize()
         for a, b in zip(captured, eager):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), seed
+
+
+def test_calls_go_to_the_current_stream():
+    """The stream handle the binding passes on is that of torch's current stream, default and others."""
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+    for stream in streams:
+        with torch.cuda.stream(stream):
+            assert q._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
+    assert len({stream.cuda_stream for stream in streams}) == 3

@@ -207,3 +207,18 @@ def test_status_strings(lib):
     assert q.status_string(0) == "ok"
     assert len({q.status_string(s) for s in range(10)}) == 10
     assert "unknown" in q.status_string(99)
+
+
+def test_the_current_stream_without_the_undocumented_functions(monkeypatch):
+    """This torch has both; a torch without one of them is asked for its current stream in the documented way."""
+    import torch
+    assert q._raw_stream is not None and q._device is not None
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 77})())
+    for name in ("_raw_stream", "_device"):
+        with monkeypatch.context() as patch:
+            patch.setattr(q, name, None)
+            assert q._stream() == 77
+    with monkeypatch.context() as patch:
+        patch.setattr(q, "_device", lambda: 3)
+        patch.setattr(q, "_raw_stream", lambda device: 100 + device)
+        assert q._stream() == 103
