@@ -173,11 +173,12 @@ float quest_alpha_star_fp4(void);
  *            M, N <= 2^22 and max(M, N) * K / 2 < 2^32 (QUEST_ERR_SHAPE otherwise)
  *   y        out bf16 [M, ld_y], ld_y >= N (row stride in elements);  may be NULL if acc_out is given
  *   acc_out  out int32 [M, N] raw accumulators, or NULL (NULL in production)
- *   workspace, workspace_bytes   scratch for bits = 1 or 2 with M, N >= 128 and K a multiple of 128:
- *            both operands are first re-coded as 4-bit codes of the same odd integers
- *            ((M + N) * K / 2 bytes, see quest_lowbit_gemm_workspace_bytes) and multiplied by the
- *            4-bit kernels.  NULL is allowed: the narrow containers are then multiplied directly by
- *            a slower kernel, with the same result.  Given but too small: QUEST_ERR_ARG.  Unused
+ *   workspace, workspace_bytes   scratch for bits = 1 or 2 with M, N >= 128 and K a multiple of 128
+ *            ((M + N) * K / 2 bytes, see quest_lowbit_gemm_workspace_bytes): larger products re-code both
+ *            operands there as 4-bit codes of the same odd integers and multiply by the 4-bit kernels;
+ *            smaller ones read the narrow containers as they are and leave it alone.  NULL is allowed:
+ *            larger products then multiply the narrow containers by a slower kernel, with the same
+ *            result.  Given but too small: QUEST_ERR_ARG, whether the product would use it or not.  Unused
  *            (may be NULL, 0) for bits = 3 or 4.
  * M = 0 or N = 0 is a no-op.  Code pointers must be 16-byte aligned.
  */
@@ -260,11 +261,11 @@ quest_status quest_trust_backward_pair(const void *g_x, const uint8_t *mask_x, i
  *   which = 1:  out[N, K] = dy[M, N]^T * xhat_h[M, K]    (q = activation codes [M, K*cb/8], scales [M])
  *   dy bf16 [M, N] row-major, out bf16, fp32 accumulation.  bits in {1,2,3,4}.
  *   M, N, K multiples of 64, each at most 2^22.
- *   workspace, workspace_bytes   scratch of quest_grad_gemm_workspace_bytes(which, M, N, K) bytes:
- *            when the output is at least 128 x 128 the call first expands the packed operand to bf16
- *            and, if the tiles do not fill the GPU's compute units evenly, leaves partial tiles there
- *            that a second pass sums in a fixed order.  Missing or too small: QUEST_ERR_ARG.  Smaller
- *            outputs need none (the query returns 0).
+ *   workspace, workspace_bytes   scratch of quest_grad_gemm_workspace_bytes(which, M, N, K) bytes for
+ *            outputs of at least 128 x 128: outputs of many tiles first expand the packed operand to bf16
+ *            there and, if the tiles do not fill the GPU's compute units evenly, leave partial tiles
+ *            that a second pass sums in a fixed order; outputs of few tiles leave it alone.  Missing or
+ *            too small: QUEST_ERR_ARG, in either case.  Smaller outputs need none (the query returns 0).
  */
 quest_status quest_grad_gemm(int32_t which, const void *dy, const uint8_t *q_codes,
                              const float *q_scales, int32_t bits, int64_t M, int64_t N, int64_t K,

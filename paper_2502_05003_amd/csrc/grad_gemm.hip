@@ -28,17 +28,18 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 //
 // 256 x 256 outputs per workgroup, four waves of 128 x 128 (sixteen 32 x 32 fp32 accumulator
 // tiles, one wave per SIMD), 32 contraction elements per step, a ring of LDS stages of 32 KiB that
-// the transfers fill several steps ahead of the step being multiplied.  The same with tiles of 192, 128 and 64
-// rows (TI = 3, 2, 1) for outputs whose tiles of 256 would leave compute units idle or need splitting: one
-// and the same loop, fewer accumulators.  A step costs 0.78, 0.59, 0.41, 0.28 us with the chip full, so
-// the smaller tiles give away 1, 5 and 40 % per operation.  Before, whole or split tiles of 256 only, and now
-// (us per call, the expansion included; tokens x N x K):
-//   G_w 16384 x 5632 x 2048: 342 (split) -> 318 (30 x 8 tiles of 192)    G_x 4096 x 6912 x 2560: 167 (split) -> 136
-//   G_x 4096 x 5632 x 2048: 111 (split) -> 90 (tiles of 128)             weight-only 4096 x 5632 x 2048: 133 -> 107
-//   G_w 4096 x 6912 x 2560: 184 (split) -> 147                           G_w 16384 x 1664 x 1664: 169 -> 146 (64)  An operand whose rows are
+// the transfers fill several steps ahead of the step being multiplied.  An operand whose rows are
 // contraction rows in memory ([c][k]: the expanded operand, and dy for which = 1) is staged as it
 // is and read with the transposing LDS load, which hands each lane four contraction elements of
 // one column; an operand whose rows are output rows (dy for which = 0) is read with 128-bit loads.
+//
+// The same with tiles of 192, 128 and 64 rows (TI = 3, 2, 1) for outputs whose tiles of 256 would leave compute
+// units idle or need splitting: one and the same loop, fewer accumulators.  A step costs 0.78, 0.59, 0.41,
+// 0.28 us with the chip full, so the smaller tiles give away 1, 5 and 40 % per operation.  Whole or split tiles of
+// 256 only, and with the smaller ones (us per call, the expansion included; tokens x N x K):
+//   G_w 16384 x 5632 x 2048: 341 (split) -> 318 (30 x 8 tiles of 192)    G_x 4096 x 6912 x 2560: 168 (split) -> 138 (192)
+//   G_x 4096 x 5632 x 2048: 110 (split) -> 91 (128)                      weight-only 4096 x 5632 x 2048: 135 -> 107 (192)
+//   G_w 4096 x 6912 x 2560: 181 (split) -> 153 (192)                     G_w 4096 x 2816 x 768: 64 -> 44 (64)
 // ------------------------------------------------------------------------------------------
 
 constexpr int GT = 256;                        // tile columns, and rows of the largest tile
@@ -622,7 +623,10 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
     const int64_t units = (int64_t)tiles * p.steps;
     // What a step of 32 contraction elements takes, us, with a share `busy` of the CUs at work (the chip is
     // power-limited: the more of them, the slower each), and what a tile's two ends take.  Fitted to
-    // 30 products with 49 .. 2816 tiles and 64 .. 512 steps, most of which are met within 5 %.  The weight-only
+    // 30 products with 49 .. 2816 tiles and 64 .. 512 steps, each alone: most are met within 5 %.  Inside a training
+    // step (estimate / mean, us): G_x 16384 x 2048 x 5632 356 / 356, 16384 x 5632 x 2048 302 / 316; the form with
+    // both operands in columns, which has no term of its own, is further off: G_w 16384 x 5632 x 2048 294 / 332,
+    // 4096 x 5632 x 2048 81 / 94, 4096 x 6912 x 2560 (360 tiles in two rounds) 133 / 179.  The weight-only
     // form reads half lines of both operands, which the smaller tiles feel.
     constexpr double kStepUs[5] = {0.0, 0.20, 0.25, 0.30, 0.46}, kBusyUs[5] = {0.0, 0.08, 0.16, 0.29, 0.32};
     constexpr double kEndsUs[5] = {0.0, 5.0, 7.0, 9.5, 13.5};

@@ -76,7 +76,8 @@ struct PackedCodes {
     static constexpr int kPerByte = 8 / kContainer;
     // The eight codes of group g as signed bytes: bytes[d] holds, in byte i, element kPerByte i + d of the group as
     // 2^(7 - b) u: the code at the top of its byte, top bit inverted, the bit below the code set.  (The power of
-    // two goes into the scale; a product by it is exact.)
+    // two goes into the scale: s u exactly as by fp32(s u), for scales of 2^-120 or more.  Below, the scale is
+    // subnormal and rounded by at most 2^-150, the product by 127 times that, 2^-10 of the spacing of bf16 there.)
     template <int g, bool WHOLE>
     __device__ __forceinline__ void to_bytes(uint32_t (&bytes)[8]) const
     {
