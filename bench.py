@@ -56,9 +56,9 @@ FP4_KERNELS = ("quantize_x_fp4", "lowbit_gemm_fp4")   # the FP4 variant of the f
 MIB = 1 << 20
 MEASURED_TRAFFIC_MIB = {
     "quantize_xw": (86.1, 27.2),
-    "lowbit_gemm": (126.5, 176.0),
-    "grad_gemm_x": (555.7, 102.8),
-    "grad_gemm_w": (1005.5, 205.7),
+    "lowbit_gemm": (125.9, 176.0),
+    "grad_gemm_x": (555.5, 102.8),
+    "grad_gemm_w": (862.4, 86.0),
     "trust_backward_xw": (91.5, 86.0),
 }
 
