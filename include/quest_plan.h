@@ -30,8 +30,9 @@ typedef struct {
     int32_t count;             /* TILES (16-bit products): tiles per workgroup; MID: groups of waves; forward: re-coding launches */
 } quest_plan;
 
-/* form 0, 1: quest_grad_gemm (fp4: quest_grad_gemm_fp4), 2: quest_weight_only_gemm; on a device of `cus` compute units */
-quest_plan quest_plan_grad_gemm(int32_t form, int32_t fp4, int64_t M, int64_t N, int64_t K, int32_t cus);
+/* form 0, 1: quest_grad_gemm (bits 1 .. 4) or quest_grad_gemm_fp4 (bits = 0), 2: quest_weight_only_gemm; on a device of `cus`
+ * compute units */
+quest_plan quest_plan_grad_gemm(int32_t form, int32_t bits, int64_t M, int64_t N, int64_t K, int32_t cus);
 
 /* quest_lowbit_gemm (bits 1 .. 4; with_workspace: scratch given) and quest_lowbit_gemm_fp4 (bits = 0) */
 quest_plan quest_plan_forward(int32_t bits, int64_t M, int64_t N, int64_t K, int32_t with_workspace);

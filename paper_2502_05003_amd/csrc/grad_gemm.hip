@@ -595,7 +595,8 @@ struct GradGemmPlan {
     size_t expanded_bytes, partial_bytes;
 };
 
-GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K, int cus)
+// grid: 1 .. 4 bits of the Eq. 1 grid, 0 E2M1; what scratch the plan needs does not depend on it
+GradGemmPlan plan_grad_gemm(int which, int grid, int64_t M, int64_t N, int64_t K, int cus)
 {
     GradGemmPlan p = {};
     // which = 0: out[M, K] = dy what;  1: out[N, K] = dy^T xhat;  2: out[M, N] = x what^T (weight-only)
@@ -608,7 +609,7 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
     p.tile_path = p.out_rows >= GT / 2 && p.out_cols >= GT / 2 && (p.contraction % GC) == 0 &&
                   p.out_rows * p.out_cols < ((int64_t)1 << 31) &&
                   std::max(M, N) * std::max(K, N) < ((int64_t)1 << 30);
-    p.covered = p.tile_path || !(which == 2 || fp4);   // these two forms: outputs of 128 x 128 or more only
+    p.covered = p.tile_path || !(which == 2 || grid == 0);   // these two forms: outputs of 128 x 128 or more only
     p.mid = true;
     if (!p.tile_path)
         return p;
@@ -622,26 +623,28 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
     const int tiles = tiles_of(4);
     const int64_t units = (int64_t)tiles * p.steps;
     // What a step of 32 contraction elements takes, us, with a share `busy` of the CUs at work (the chip is
-    // power-limited: the more of them, the slower each), and what a tile's two ends take.  Fitted to
-    // 30 products with 49 .. 2816 tiles and 64 .. 512 steps, each alone: most are met within 5 %.  Inside a training
-    // step (estimate / mean, us): G_x 16384 x 2048 x 5632 356 / 356, 16384 x 5632 x 2048 302 / 316; the form with
-    // both operands in columns, which has no term of its own, is further off: G_w 16384 x 5632 x 2048 294 / 332,
-    // 4096 x 5632 x 2048 81 / 94, 4096 x 6912 x 2560 (360 tiles in two rounds) 133 / 179.  The weight-only
-    // form reads half lines of both operands, which the smaller tiles feel.
-    constexpr double kStepUs[5] = {0.0, 0.20, 0.25, 0.30, 0.46}, kBusyUs[5] = {0.0, 0.08, 0.16, 0.29, 0.32};
+    // power-limited: the more of them, the slower each), and what a tile's two ends take.  The weight-only
+    // form reads half lines of both operands, which the smaller tiles feel, and tiles of 64 and 128 rows in many
+    // rounds share fewer fetches of the right operand.  Fitted to 260 products of 128 .. 16384 tokens, each
+    // timed alone in every way there is, and checked on 260 others: the way chosen takes 1.4 % more than the best in
+    // the mean, 18 % at most.  Inside a training step a product takes up to 15 % more than alone, 360 tiles of
+    // 192 rows in two rounds (G_w 4096 x 6912 x 2560) 25 %.
+    constexpr double kStepUs[5] = {0.0, 0.212, 0.265, 0.318, 0.488}, kBusyUs[5] = {0.0, 0.085, 0.17, 0.307, 0.339};
     constexpr double kEndsUs[5] = {0.0, 5.0, 7.0, 9.5, 13.5};
     auto whole_cost = [&](int ti) {
         const int n = tiles_of(ti), rounds = (n + cus - 1) / cus;
         const double busy = (double)n / ((double)rounds * cus);
-        const double step = (kStepUs[ti] + kBusyUs[ti] * busy * busy) * (which == 2 && ti < 4 ? 1.15 : 1.0);
-        return rounds * (step * p.steps + kEndsUs[ti]);
+        const double step = (kStepUs[ti] + kBusyUs[ti] * busy * busy) * (which == 2 && ti < 4 ? 1.18 : 1.0);
+        return rounds * (step * p.steps + kEndsUs[ti]) * (ti <= 2 && rounds >= 3 ? 1.15 : 1.0);
     };
     // split: a share of the units, partial tiles written and read back (0.08 us each), the second launch;
-    // a step costs more when no other workgroup is at the same contraction position (see phase_period)
+    // a step costs more when no other workgroup of the XCD is at the same contraction position, which those are
+    // whose period divides the number of workgroups (see phase_period)
     const int share = cus >= 8 ? (int)((units + cus - 1) / cus) : 0;
     const int period = cus >= 8 ? p.steps / std::gcd(share, p.steps) : 0;
+    const bool in_phase = period != 0 && cus % period == 0 && period <= 32;
     const double split_cost = cus >= 8 && units >= 4 * (int64_t)cus
-                                  ? (period <= 32 ? 0.78 : 1.0) * share + 0.08 * (cus + tiles) + 8.0
+                                  ? (!in_phase ? 1.12 : which == 2 ? 0.78 : 0.80) * share + 0.08 * (cus + tiles) + 8.0
                                   : 1e30;
     p.ti = 4;
     double cost = cus > 0 ? whole_cost(4) : 0.0;
@@ -678,7 +681,7 @@ GradGemmPlan plan_grad_gemm(int which, bool fp4, int64_t M, int64_t N, int64_t K
     // Whether the kernels that expand on the way into LDS are cheaper: theirs is their own estimate; here
     // the expansion (read 0.5, written 2 bytes per code at 4.5 TB/s) and two or three launches come on top.
     const double expand_cost = 3.0 + (double)p.q_rows * (double)K * 2.5 / 4.5e6;
-    p.mid = grad_gemm_mid_cost(p.contraction, p.out_rows, p.out_cols, cus >= 8 ? cus : 256) < expand_cost + cost;
+    p.mid = grad_gemm_mid_cost(grid, p.contraction, p.out_rows, p.out_cols, cus >= 8 ? cus : 256) < expand_cost + cost;
     p.expanded_bytes = ((size_t)p.q_rows * K * 2 + 255) / 256 * 256;
     p.partial_bytes = p.split ? (size_t)2 * p.blocks * kSlotQuads * sizeof(float4) : 0;
     return p;
@@ -690,7 +693,7 @@ int64_t grad_gemm_workspace_bytes(int which, bool fp4, int64_t M, int64_t N, int
 {
     if (M == 0 || N == 0 || K == 0)
         return 0;
-    const GradGemmPlan p = plan_grad_gemm(which, fp4, M, N, K, cus);
+    const GradGemmPlan p = plan_grad_gemm(which, fp4 ? 0 : 4, M, N, K, cus);
     if (!p.covered)
         return -1;
     return p.tile_path ? (int64_t)(p.expanded_bytes + p.partial_bytes) : 0;
@@ -752,7 +755,7 @@ hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)
         return hipSuccess;
     const auto *dy = static_cast<const uint16_t *>(a.dy);
     auto *out = static_cast<uint16_t *>(a.out);
-    const GradGemmPlan p = plan_grad_gemm(a.which, a.fp4, a.M, a.N, a.K, device_compute_units());
+    const GradGemmPlan p = plan_grad_gemm(a.which, a.fp4 ? 0 : a.bits, a.M, a.N, a.K, device_compute_units());
     if (!p.covered)
         return hipErrorInvalidValue;
     if (p.mid) {
@@ -794,12 +797,12 @@ hipError_t launch_grad_gemm(const GradGemmArgs &a, hipStream_t stream)
 
 }  // namespace quest
 
-quest_plan quest_plan_grad_gemm(int32_t form, int32_t fp4, int64_t M, int64_t N, int64_t K, int32_t cus)
+quest_plan quest_plan_grad_gemm(int32_t form, int32_t bits, int64_t M, int64_t N, int64_t K, int32_t cus)
 {
-    const quest::GradGemmPlan p = quest::plan_grad_gemm(form, fp4 != 0, M, N, K, cus);
+    const quest::GradGemmPlan p = quest::plan_grad_gemm(form, bits, M, N, K, cus);
     if (!p.covered)
         return {QUEST_PLAN_NONE, 0, 0, 0};
     if (p.mid)
-        return quest::grad_gemm_mid_plan(p.contraction, p.out_rows, p.out_cols, cus);
+        return quest::grad_gemm_mid_plan(bits, p.contraction, p.out_rows, p.out_cols, cus);
     return {p.split ? QUEST_PLAN_SPLIT : QUEST_PLAN_TILES, 64 * p.ti, quest::GT, p.split ? 1 : p.per_block / p.steps};
 }

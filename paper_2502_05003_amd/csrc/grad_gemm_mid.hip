@@ -465,25 +465,32 @@ hipError_t launch(const GradMidArgs &a, hipStream_t stream)
 // workgroup and round when several take turns.  What bounds a round is a wave's issue rate (expansion:
 // three vector instructions per code) and the LDS traffic, so small blocks are cheap per round and dear
 // per operation; several groups halve or quarter the number of rounds where a unit has one workgroup.
+// One-bit codes (eight to a byte, each expanded by itself in blocks whose order is the compiler's) make a round of
+// the smaller blocks dearer, by `one_bit`: measured / estimated without it 1.2 to 1.45 (G_x 384 x 9792 x 3136 with
+// 64 x 128 blocks of two groups: 63.8 us at 4 bits, 92.5 at one).  Those, at 1.45, would never be the
+// cheapest and are not built for one bit (0).
 struct Shape {
     int wi, wj, groups;
-    double alone, shared;
+    double alone, shared, one_bit;
 };
-constexpr Shape kShapes[] = {{1, 1, 2, 0.56, 0.44}, {1, 1, 4, 1.00, 1.00}, {1, 2, 1, 0.53, 0.39},
-                             {1, 2, 2, 0.79, 0.79}, {2, 2, 1, 0.74, 0.64}, {2, 2, 2, 1.08, 1.30}};
+constexpr Shape kShapes[] = {{1, 1, 2, 0.56, 0.44, 1.20}, {1, 1, 4, 1.00, 1.00, 1.25}, {1, 2, 1, 0.53, 0.39, 1.30},
+                             {1, 2, 2, 0.79, 0.79, 0.00}, {2, 2, 1, 0.70, 0.61, 1.00}, {2, 2, 2, 1.08, 1.30, 1.05}};
 
-double shape_cost(const Shape &s, int64_t C, int64_t R, int64_t K, int cus)
+double shape_cost(const Shape &s, int grid, int64_t C, int64_t R, int64_t K, int cus)
 {
+    if (grid == 1 && s.one_bit == 0.0)
+        return 1e30;
     const int64_t blocks = ((R + 64 * s.wi - 1) / (64 * s.wi)) * ((K + 64 * s.wj - 1) / (64 * s.wj));
     const int64_t per_cu = (blocks + cus - 1) / cus, rounds = (C / GC + s.groups - 1) / s.groups;
-    return 3.0 + (double)per_cu * 1.0 + (double)rounds * (per_cu == 1 ? s.alone : (double)per_cu * s.shared);
+    const double round = (per_cu == 1 ? s.alone : (double)per_cu * s.shared) * (grid == 1 ? s.one_bit : 1.0);
+    return 3.0 + (double)per_cu * 1.0 + (double)rounds * round;
 }
 
-int cheapest_shape(int64_t C, int64_t R, int64_t K, int cus)
+int cheapest_shape(int grid, int64_t C, int64_t R, int64_t K, int cus)
 {
     int best = 0;
     for (int i = 1; i < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++i)
-        if (shape_cost(kShapes[i], C, R, K, cus) < shape_cost(kShapes[best], C, R, K, cus))
+        if (shape_cost(kShapes[i], grid, C, R, K, cus) < shape_cost(kShapes[best], grid, C, R, K, cus))
             best = i;
     return best;
 }
@@ -495,7 +502,10 @@ hipError_t launch_shape(const GradMidArgs &a, int shape, hipStream_t stream)
     case 0: return launch<MODE, GRID, 1, 1, 2>(a, stream);
     case 1: return launch<MODE, GRID, 1, 1, 4>(a, stream);
     case 2: return launch<MODE, GRID, 1, 2, 1>(a, stream);
-    case 3: return launch<MODE, GRID, 1, 2, 2>(a, stream);
+    case 3:
+        if constexpr (GRID != 1)
+            return launch<MODE, GRID, 1, 2, 2>(a, stream);
+        return hipErrorInvalidValue;
     case 4: return launch<MODE, GRID, 2, 2, 1>(a, stream);
     default: return launch<MODE, GRID, 2, 2, 2>(a, stream);
     }
@@ -524,8 +534,10 @@ hipError_t prepare_grid()
         return allow_dynamic_lds(reinterpret_cast<const void *>(kernel), groups * 2 * (64 * wi + 64 * wj) * GC * 2);
     };
     hipError_t err = limit(grad_gemm_mid_kernel<MODE, GRID, 1, 1, 4>, 1, 1, 4);
-    if (err == hipSuccess)
-        err = limit(grad_gemm_mid_kernel<MODE, GRID, 1, 2, 2>, 1, 2, 2);
+    if constexpr (GRID != 1) {
+        if (err == hipSuccess)
+            err = limit(grad_gemm_mid_kernel<MODE, GRID, 1, 2, 2>, 1, 2, 2);
+    }
     if (err == hipSuccess)
         err = limit(grad_gemm_mid_kernel<MODE, GRID, 2, 2, 2>, 2, 2, 2);
     return err;
@@ -550,15 +562,15 @@ hipError_t prepare_mode()
 
 }  // namespace
 
-quest_plan grad_gemm_mid_plan(int64_t C, int64_t R, int64_t K, int cus)
+quest_plan grad_gemm_mid_plan(int grid, int64_t C, int64_t R, int64_t K, int cus)
 {
-    const Shape &s = kShapes[cheapest_shape(C, R, K, cus)];
+    const Shape &s = kShapes[cheapest_shape(grid, C, R, K, cus)];
     return {QUEST_PLAN_MID, 64 * s.wi, 64 * s.wj, s.groups};
 }
 
-double grad_gemm_mid_cost(int64_t C, int64_t R, int64_t K, int cus)
+double grad_gemm_mid_cost(int grid, int64_t C, int64_t R, int64_t K, int cus)
 {
-    return shape_cost(kShapes[cheapest_shape(C, R, K, cus)], C, R, K, cus);
+    return shape_cost(kShapes[cheapest_shape(grid, C, R, K, cus)], grid, C, R, K, cus);
 }
 
 hipError_t prepare_grad_gemm_mid_kernels()
@@ -573,7 +585,7 @@ hipError_t prepare_grad_gemm_mid_kernels()
 
 hipError_t launch_grad_gemm_mid(const GradMidArgs &a, hipStream_t stream)
 {
-    const int shape = cheapest_shape(a.C, a.R, a.K, device_compute_units());
+    const int shape = cheapest_shape(a.grid, a.C, a.R, a.K, device_compute_units());
     return a.mode == 0   ? launch_mode<0>(a, shape, stream)
            : a.mode == 1 ? launch_mode<1>(a, shape, stream)
                          : launch_mode<2>(a, shape, stream);

@@ -150,9 +150,9 @@ struct GradMidArgs {
 // every shape of multiples of 64; E2M1 codes for modes 0 and 1 only
 hipError_t launch_grad_gemm_mid(const GradMidArgs &a, hipStream_t stream);
 // the block of the kernel the call gets (kernel, block_rows, block_cols, count)
-quest_plan grad_gemm_mid_plan(int64_t C, int64_t R, int64_t K, int cus);
+quest_plan grad_gemm_mid_plan(int grid, int64_t C, int64_t R, int64_t K, int cus);
 // what the call is expected to take, us
-double grad_gemm_mid_cost(int64_t C, int64_t R, int64_t K, int cus);
+double grad_gemm_mid_cost(int grid, int64_t C, int64_t R, int64_t K, int cus);
 
 // hipErrorInvalidValue: the shape is not one the kernels cover, or the workspace is too small
 // (the entry points check both beforehand with grad_gemm_workspace_bytes).

@@ -25,8 +25,9 @@ def _i64(*values):
     return [ctypes.c_int64(v) for v in values]
 
 
-def grad_gemm(form, M, N, K, fp4=False):
-    return _ask("quest_plan_grad_gemm", form, int(fp4), *_i64(M, N, K), CUS)
+def grad_gemm(form, M, N, K, bits=4):
+    """bits = 0: E2M1 codes"""
+    return _ask("quest_plan_grad_gemm", form, bits, *_i64(M, N, K), CUS)
 
 
 def forward(M, N, K, bits, workspace=True):

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 # blocks for two groups, rows ending inside one; 3 of 128 x 128 blocks, both edges inside one
 SHAPES = [(64, 64, 64), (192, 64, 64), (576, 64, 128), (1792, 2048, 640), (704, 576, 5632), (192, 4160, 2112),
           # the smaller blocks at outputs that every form and grid takes
-          (128, 128, 128), (192, 192, 192), (128, 320, 11008)]
+          (128, 128, 128), (192, 192, 192), (128, 320, 11008), (192, 640, 1664)]
 
 
 # (E2M1 codes and the weight-only product: outputs of at least 128 x 128; no weight-only product on E2M1)
