@@ -397,8 +397,11 @@ hipError_t prepare_quantize_rows_kernels()
 }
 
 // Which calls come here (`rows`: of both operands).  Everything that hadamard_quantize_mfma.hip has no instantiation
-// for, up to blocks of 4096: faster than the general kernel at every number of rows (us, here / there, 24 rows:
-// 2560 elements 4.7 / 6.6, 5120 4.9 / 11.0, 64 3.4 / 4.3).  Of the fp32 shapes that it has, which it holds in registers as
+// for, up to blocks of 4096: faster than the general kernel, in most shapes at every number of rows (us, here / there, 24
+// rows: 2560 elements 4.7 / 6.6, 5120 4.9 / 11.0, 64 3.4 / 4.3).  The exceptions are blocks of 8 or less, which the
+// general kernel has in registers straight from its loads: bf16 rows still come here (50 x 1280 4.6 / 4.0, 750 x 1280
+// 4.8 / 4.9, 8192 x 1280 10.8 / 21.8), fp32 rows, which gain little, do not (50 x 1344 5.7 / 4.0, 8192 x 3584 30 / 35).
+// Of the fp32 shapes that it has, which it holds in registers as
 // a whole: long rows, and many rows (here / there: 24 rows of 2816 5.8 / 5.1, 3584 5.9 / 6.9, 5632 6.1 / 9.1;
 // 1024 x 2048 6.9 / 6.7, 2048 x 2048 8.5 / 8.9, 8192 x 2048 19.2 / 24.6; blocks of 4096, 24 rows 9.2 / 6.1,
 // 2048 rows 15.4 / 15.0, 8192 rows 43.9 / 51.7).  Both kernels make the same bits of these rows, so the number
@@ -408,7 +411,7 @@ bool quantize_rows_preferred(const QuantizeArgs &a, int64_t rows)
     if (a.cols % 64 != 0 || a.log2n > 12 || a.mode == kQuantAbsMax)
         return false;
     if (!launch_hadamard_quantize_mfma(a, nullptr, true))
-        return true;
+        return a.dtype == QUEST_BF16 || a.log2n > 3;
     return a.dtype == QUEST_F32 && a.cols >= 1024 && (rows >= 2048 || (a.cols > 2816 && a.log2n < 12));
 }
 

@@ -49,28 +49,27 @@ __device__ __forceinline__ void hadamard_operand(int log2n, int m, int h, v8bf (
         }
         return;
     }
+    // column m has entries in the 2^nb rows of its block only: of the eight rows base .. base + 7 those whose bit is set in
+    // `there` (all or none for blocks of eight or more), with the signs of the block's own pattern
     const int nb = log2n < 5 ? log2n : 5;
-    const int low = (1 << nb) - 1;
+    const int low = (1 << nb) - 1, own = m & low, first = m & ~low;
+    const uint32_t pattern = ((own & 1) ? 0xAAu : 0u) ^ ((own & 2) ? 0xCCu : 0u) ^ ((own & 4) ? 0xF0u : 0u);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
+        const int base = 16 * h + 8 * s;
+        const uint32_t there = nb >= 3 ? ((base & ~low) == first ? 0xFFu : 0u)
+                                       : (first >> 3 == base >> 3 ? ((1u << (1 << nb)) - 1u) << (first & 7) : 0u);
+        const uint32_t minus = (__builtin_popcount(base & own) & 1) ? pattern ^ 0xFFu : pattern;   // bit e: entry is -1
         uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int q = 16 * h + 8 * s + e;
-            uint32_t v = 0;
-            if ((q >> nb) == (m >> nb))
-                v = (__builtin_popcount(q & m & low) & 1) ? 0xBF80u : 0x3F80u;
-            if (e & 1)
-                w[e >> 1] |= v << 16;
-            else
-                w[e >> 1] = v;
-        }
+        for (int k = 0; k < 4; ++k)
+            w[k] = ((there >> (2 * k)) & 1u) * (0x3F80u | ((minus << (15 - 2 * k)) & 0x8000u)) |
+                   ((there >> (2 * k + 1)) & 1u) * (0x3F800000u | ((minus << (30 - 2 * k)) & 0x80000000u));
         __builtin_memcpy(&bmat[s], w, 16);
     }
 }
 
-// The same for a block size known only at run time (wave-uniform): the general form costs about 200
-// instructions, 1 us of a short launch, and is needed for blocks below 32 only.
+// The same for a block size known only at run time (wave-uniform); the general form is needed for blocks below 32 only.
 __device__ __forceinline__ void hadamard_operand_any(int log2n, int m, int h, v8bf (&bmat)[2])
 {
     if (log2n >= 5)

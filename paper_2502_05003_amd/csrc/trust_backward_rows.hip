@@ -158,9 +158,12 @@ hipError_t prepare_trust_backward_rows_kernels()
     return hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(tb_rows_kernel<uint16_t, 1>));
 }
 
+// Not blocks of 8 or less, which the general kernel has in registers straight from its loads and never exchanges (us, here /
+// there: block 8, 8192 x 3392 23.3 / 20.1, 8192 x 1280 to fp32 14.0 / 11.9, 300 x 448 3.2 / 2.6; 8192 x 448 6.4 / 7.3; block 16,
+// 8192 x 3392 23.3 / 33.6, 300 x 448 3.2 / 3.0).
 bool trust_backward_rows_covers(const BackwardArgs &a)
 {
-    return a.g_dtype == QUEST_BF16 && a.cols % 64 == 0 && a.log2n <= 12;
+    return a.g_dtype == QUEST_BF16 && a.cols % 64 == 0 && a.log2n >= 4 && a.log2n <= 12;
 }
 
 hipError_t launch_trust_backward_rows(const BackwardArgs &a, hipStream_t stream)

@@ -99,10 +99,10 @@ def mirror_projection(xh, bits, alpha, outer_trust=1.0):
     return scale, codes, mask
 
 
-# shapes the general kernel serves: rows that are no multiple of 64, blocks above 4096
+# shapes the general kernel serves: rows that are no multiple of 64, blocks above 4096, fp32 rows with blocks of 8 or less
 CASES = [(96, 1544, 8, 4, "f32"), (64, 1560, 8, 3, "bf16"), (33, 776, 8, 2, "bf16"),
          (40, 8192, 8192, 8, "f32"), (57, 3080, 8, 1, "bf16"), (19, 24, 8, 4, "f32"),
-         (200, 72, 8, 8, "f32"), (31, 16384, 8192, 4, "bf16")]
+         (200, 72, 8, 8, "f32"), (31, 16384, 8192, 4, "bf16"), (40, 1344, 4, 4, "f32")]
 
 
 @pytest.mark.parametrize("rows,cols,block,bits,dtype", CASES)

@@ -60,6 +60,8 @@ def test_quantizer_kernels():
     assert plan.quantize(24, 2048, 2048, 4, "bf16") == plan.quantize(8192, 2048, 2048, 4, "bf16") == plan.INSTANCE
     assert plan.quantize(24, 2048, 2048, 4, "f32") == plan.INSTANCE
     assert plan.quantize(8192, 2048, 2048, 4, "f32") == plan.ROWS
+    # blocks of 8 or less: bf16 rows only
+    assert plan.quantize(24, 1344, 8, 4, "bf16") == plan.ROWS and plan.quantize(8192, 1344, 8, 4, "f32") == plan.GENERAL
     import test_gpu_stage_isolated as stages
     assert all(plan.quantize(rows, cols, n, bits, dtype) == plan.GENERAL for rows, cols, n, bits, dtype in stages.CASES)
     assert all(plan.quantize(rows, cols, n, bits, dtype) == plan.ROWS for rows, cols, n, bits, dtype in stages.TILE_CASES)
