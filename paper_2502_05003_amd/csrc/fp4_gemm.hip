@@ -210,8 +210,13 @@ __global__ __launch_bounds__(kTileThreads, AF == 4 ? 2 : 3) void fp4_gemm_tile_k
 
 // Fewer tiles of 256 x 128 than three quarters of the chip's slots (two per CU), as for the integer kernels:
 // tiles of 128 x 128 (us, 256 / 128 rows: 323 x 2992 x 4608, 24 tiles, 16.5 / 10.4; 768 x 2816 x 4096, 66 tiles,
-// 14.5 / 10.5; 1728 x 1920 x 5760, 105 tiles, 26.3 / 19.3; 4096 x 2816 x 1024, 352 tiles, 14.7 / 14.4).
-constexpr int64_t kFewTiles = 384;
+// 14.5 / 10.5; 1728 x 1920 x 5760, 105 tiles, 26.3 / 19.3; 4096 x 2816 x 1024, 352 tiles, 14.7 / 14.4).  But not
+// where each CU gets at most one large tile and some get two small ones: those CUs have the same products to do
+// and read a third more for them, which a long contraction does not win back by its shorter prologue and
+// epilogue (3072 x 1536, 144 tiles: K = 2048 11.4 / 11.1, K = 3072 15.4 / 15.5, K = 7296 31.6 / 36.7;
+// 1815 x 4096, 256 tiles: K = 2048 14.8 / 14.5, K = 3072 18.8 / 19.7, K = 7296 36.9 / 39.7; beside it 121 tiles,
+// all small ones in one round, K = 7296 31.1 / 23.2, and 288 tiles, two rounds either way, 60.2 / 55.9).
+constexpr int64_t kFewTiles = 384, kUnits = 256, kLongContraction = 2560;
 
 template <int AF>
 hipError_t launch(const Fp4GemmArgs &a, hipStream_t stream)
@@ -241,8 +246,10 @@ quest_plan plan_fp4_gemm(int64_t M, int64_t N, int64_t K)
 {
     if (skinny_gemm_preferred(M, N, K, 0))
         return {QUEST_PLAN_FEW, 0, 0, 0};
-    const int64_t big_tiles = ((M + Tile<4>::kRows - 1) / Tile<4>::kRows) * ((N + TN - 1) / TN);
-    return {QUEST_PLAN_TILES, big_tiles < kFewTiles ? Tile<2>::kRows : Tile<4>::kRows, TN, 0};
+    const auto tiles = [&](int rows) { return ((M + rows - 1) / rows) * ((N + TN - 1) / TN); };
+    const int64_t large = tiles(Tile<4>::kRows);
+    const bool one_large_each = large <= kUnits && tiles(Tile<2>::kRows) > kUnits && K >= kLongContraction;
+    return {QUEST_PLAN_TILES, large < kFewTiles && !one_large_each ? Tile<2>::kRows : Tile<4>::kRows, TN, 0};
 }
 
 hipError_t launch_fp4_gemm(const Fp4GemmArgs &a, hipStream_t stream)

@@ -65,3 +65,10 @@ def test_quantizer_kernels():
     import test_gpu_stage_isolated as stages
     assert all(plan.quantize(rows, cols, n, bits, dtype) == plan.GENERAL for rows, cols, n, bits, dtype in stages.CASES)
     assert all(plan.quantize(rows, cols, n, bits, dtype) == plan.ROWS for rows, cols, n, bits, dtype in stages.TILE_CASES)
+
+
+def test_fp4_one_large_tile_per_unit():
+    """Long contractions: tiles of 128 rows only where they come out in no more rounds than those of 256."""
+    rows = {(tiles, K): plan.forward(256 * tiles // 8, 1024, K, 0).rows
+            for tiles in (128, 136, 256, 264, 376, 384) for K in (2048, 2560, 11008)}
+    assert all((h == 256) == (tiles == 384 or (tiles in (136, 256) and K > 2048)) for (tiles, K), h in rows.items()), rows
