@@ -39,7 +39,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // 256 only, and with the smaller ones (us per call, the expansion included; tokens x N x K):
 //   G_w 16384 x 5632 x 2048: 341 (split) -> 318 (30 x 8 tiles of 192)    G_x 4096 x 6912 x 2560: 168 (split) -> 138 (192)
 //   G_x 4096 x 5632 x 2048: 110 (split) -> 91 (128)                      weight-only 4096 x 5632 x 2048: 135 -> 107 (192)
-//   G_w 4096 x 6912 x 2560: 181 (split) -> 153 (192)                     G_w 4096 x 2816 x 768: 64 -> 44 (64)
+//   G_w 4096 x 6912 x 2560: 181 (split) -> 153 (192)                     G_x 1088 x 4096 x 3648: 91 -> 55 (64)
 // ------------------------------------------------------------------------------------------
 
 constexpr int GT = 256;                        // tile columns, and rows of the largest tile

@@ -1,6 +1,6 @@
 // The fused quantizer on the matrix cores for row lengths and block sizes that hadamard_quantize_mfma.hip
 // has no instantiation for: any row of a multiple of 64 elements, any block up to 4096, every grid,
-// bf16 and fp32 rows (Algorithm 1, one operand or both; Sec. 3.1, 3.2 and 4.4 of arXiv 2502.05003).
+// bf16 rows, and fp32 rows in blocks of 16 or more (Algorithm 1, one operand or both; Sec. 3.1, 3.2 and 4.4 of arXiv 2502.05003).
 //
 // Data flow per row as in that file (which see for the index bookkeeping), with the row length and the
 // block size as run-time values: a wave brings a row into its own LDS buffer by global -> LDS transfers,

@@ -1,6 +1,6 @@
 // The trust-masked inverse transform on the matrix cores for row lengths and block sizes that
-// trust_backward_mfma.hip has no instantiation for: bf16 rows of any multiple of 64 elements, any block
-// up to 4096, bf16 or fp32 out (Algorithm 2, out = IHT(M (.) g); Sec. 3.2 of arXiv 2502.05003).
+// trust_backward_mfma.hip has no instantiation for: bf16 rows of any multiple of 64 elements, blocks
+// of 16 to 4096, bf16 or fp32 out (Algorithm 2, out = IHT(M (.) g); Sec. 3.2 of arXiv 2502.05003).
 //
 // Data flow as in that file, with the row length and the block size as run-time values: the unit of work is
 // a group of G tiles of 1024 elements (G: the tiles one block spans), so that few long rows fill the chip

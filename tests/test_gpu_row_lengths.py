@@ -1,6 +1,7 @@
 """The quantizer and the masked inverse transform at row lengths and blocks without an instantiation of
 their own (csrc/hadamard_quantize_rows.hip, csrc/trust_backward_rows.hip) against the CPU oracle: rows that
-end anywhere in a tile, every kind of block, one and several rows per wave, rows shared by a workgroup."""
+end anywhere in a tile, every kind of block, one and several rows per wave, rows shared by a workgroup.  (The
+blocks of 8 or less among them run the general kernels for fp32 rows and for the inverse transform.)"""
 import numpy as np
 import pytest
 import torch
