@@ -221,6 +221,14 @@ __device__ __forceinline__ void store_word_counted(uint32_t *p, uint32_t v)
     asm volatile("global_store_dword %0, %1, off nt" : : "v"(p), "v"(v) : "memory");
 }
 
+// The same with the address as a wave-uniform base, a per-lane byte offset and a constant: a 64-bit addition per store less.
+template <int IMM>
+__device__ __forceinline__ void store_word_counted(void *uniform_base, uint32_t lane_offset, uint32_t v)
+{
+    static_assert(IMM >= 0 && IMM < 4096, "the instruction's offset field");
+    asm volatile("global_store_dword %0, %1, %2 offset:%3 nt" : : "v"(lane_offset), "v"(v), "s"(uniform_base), "n"(IMM) : "memory");
+}
+
 // 16 bytes per lane from global memory straight into LDS (lane l lands at lds_base + 16 l), streaming
 // (the input is read once).  Source = wave-uniform base + per-lane byte offset.
 __device__ __forceinline__ void lds_dma16_stream(const void *uniform_base, uint32_t lane_offset, uint32_t lds_base)

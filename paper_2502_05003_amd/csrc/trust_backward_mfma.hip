@@ -270,18 +270,24 @@ hipError_t prepare_trust_backward_mfma_kernels()
 
 // Launches the matrix-core kernel if it covers the call; returns false (nothing launched) otherwise.
 // Covered (U = row length / 128): bf16 in; bf16 out for rows of 512, 1024, 2048 or 4096 elements with a
-// Hadamard block of at most 32, or 128, 512, 1024, 2048, 4096 where it divides the row, and for the
-// shorter of the other widths of the paper's model family (640, 768, 1280, 1664, 1792, 2816) with a block
-// of at most 32 or their widest one; fp32 out (a weight gradient for an fp32 optimizer) for all of these
-// row lengths with their widest block.  Longer rows are better off in the kernel that deals out
-// groups of tiles (trust_backward_rows.hip), measured against instantiations here: 8192 x 5632 37 us against 39,
-// 8192 x 11008 71 against 77, 333 x 5632 4.4 against 6.2; 8192 x 1792 14.3 against 13.2.
+// Hadamard block of at most 32, or 128, 512, 1024, 2048, 4096 where it divides the row, and for rows of 640, 768
+// and 1280 with a block of at most 32 or their widest one; fp32 out (a weight gradient for an fp32
+// optimizer) for all of these row lengths with their widest block.  Everything else is better off in the kernel that
+// cuts the gradient without regard to its rows (trust_backward_rows.hip), and so are the rows that are not whole pieces
+// of 2048 elements once there are enough of them (us, here / there: 4882 x 512 3.9 / 4.5, 6835 x 512
+// 5.0 / 4.9, 15625 x 512 8.5 / 6.8; 3906 x 640 4.1 / 4.5, 7812 x 640 6.0 / 5.3; 1953 x 1280 4.4 / 4.5, 3906 x 1280
+// 6.2 / 5.4; of rows with an instantiation before: 2048 x 1792 5.3 / 4.9, 16384 x 2816 35.9 / 33.3; whole
+// pieces with the block size known to the compiler, 22016 x 2048 32.3 / 33.9, 2048 x 4096 7.1 / 8.1).  Both make the
+// same bits: the same sums in the same order.
 bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
 {
     if (a.g_dtype != QUEST_BF16 || (a.cols % 128) != 0)
         return false;
     const int u = (int)(a.cols / 128);
     const int l = a.log2n <= 5 ? 5 : a.log2n;
+    constexpr int64_t kFewElements = 3 << 20;
+    if ((u % 8 != 0) && (a.rows + a.rows2) * a.cols > kFewElements && trust_backward_rows_covers(a))
+        return false;
     if (a.out_dtype != QUEST_BF16) {
 #define QUEST_F32_OUT_CASE(U_, L_)                 \
     if (u == U_ && l == L_) {                      \
@@ -289,8 +295,7 @@ bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
         return true;                               \
     }
         QUEST_F32_OUT_CASE(4, 9) QUEST_F32_OUT_CASE(8, 10) QUEST_F32_OUT_CASE(16, 11) QUEST_F32_OUT_CASE(32, 12)
-        QUEST_F32_OUT_CASE(5, 7) QUEST_F32_OUT_CASE(6, 8) QUEST_F32_OUT_CASE(10, 8) QUEST_F32_OUT_CASE(13, 7)
-        QUEST_F32_OUT_CASE(14, 8) QUEST_F32_OUT_CASE(22, 8)
+        QUEST_F32_OUT_CASE(5, 7) QUEST_F32_OUT_CASE(6, 8) QUEST_F32_OUT_CASE(10, 8)
 #undef QUEST_F32_OUT_CASE
         return false;
     }
@@ -303,9 +308,7 @@ bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
     QUEST_CASE(8, 5) QUEST_CASE(8, 7) QUEST_CASE(8, 9) QUEST_CASE(8, 10)
     QUEST_CASE(16, 5) QUEST_CASE(16, 7) QUEST_CASE(16, 9) QUEST_CASE(16, 10) QUEST_CASE(16, 11)
     QUEST_CASE(32, 5) QUEST_CASE(32, 7) QUEST_CASE(32, 9) QUEST_CASE(32, 10) QUEST_CASE(32, 11) QUEST_CASE(32, 12)
-    // the other widths of the paper's models (hidden 640 .. 1664, MLP 1792, 2816): no transform / widest block
     QUEST_CASE(5, 5) QUEST_CASE(5, 7) QUEST_CASE(6, 5) QUEST_CASE(6, 8) QUEST_CASE(10, 5) QUEST_CASE(10, 8)
-    QUEST_CASE(13, 5) QUEST_CASE(13, 7) QUEST_CASE(14, 5) QUEST_CASE(14, 8) QUEST_CASE(22, 5) QUEST_CASE(22, 8)
 #undef QUEST_CASE
     return false;
 }

@@ -129,3 +129,34 @@ def test_inverse_transform(rows, cols, n, masked, od):
     scale = np.sqrt(np.mean(ref * ref, axis=1, keepdims=True))
     rounding = BF16_HALF_ULP if od == "bf16" else 0.0
     assert np.all(np.abs(to_host_f64(out) - ref) <= rounding * np.abs(ref) + 1e-5 * scale + 1e-30)
+
+
+# row lengths that have an instantiation for few elements (512, 640, 1280), none (2560: units end inside a row; 64), blocks of
+# 2048 and 4096; the second gradient starts a unit of its own
+@pytest.mark.parametrize("od", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,cols,n", [(7001, 512, 512), (5503, 640, 128), (2611, 1280, 256), (1601, 2560, 512),
+                                         (4097, 64, 64), (701, 6144, 2048), (401, 12288, 4096)])
+def test_inverse_transform_of_a_row_does_not_depend_on_the_others(rows, cols, n, od):
+    """A row alone, in a short call, in a long one and as the second gradient gets the same bits; an infinity and a
+    NaN stay in their rows."""
+    g = torch.randn(rows, cols, device=DEV).bfloat16()
+    mask = torch.randint(0, 256, (rows, cols // 8), dtype=torch.uint8, device=DEV)
+    g[rows // 2, 3], g[rows - 2, cols - 1] = float("inf"), float("nan")
+    clean = torch.ones(rows, dtype=torch.bool, device=DEV)
+    clean[rows // 2] = clean[rows - 2] = False
+
+    def transform(*parts):
+        out = [torch.full((p.stop - p.start, cols), 7.0, dtype=od, device=DEV) for p in parts]
+        if len(parts) == 1:
+            q.quest_trust_backward(*(t[parts[0]].clone() for t in (g, mask)), n, out=out[0])
+        else:
+            q.quest_trust_backward_pair(*(t[p].clone() for p in parts for t in (g, mask)), n, out_x=out[0], out_w=out[1])
+        return out
+
+    whole, = transform(slice(0, rows))
+    for parts in ([slice(0, 2)], [slice(rows - 16, rows)], [slice(0, 304)], [slice(0, 32), slice(rows - 2, rows)],
+                  [slice(0, rows - 1), slice(16, 32)]):
+        for part, out in zip(parts, transform(*parts)):
+            keep = clean[part]
+            assert torch.equal(out[keep], whole[part][keep])
+    assert torch.isfinite(whole[clean].float()).all()
