@@ -4,6 +4,10 @@ Every function has the name and the argument order of the C entry point it wraps
 (include/quest.h).  Tensors are torch device tensors used purely as device memory; every step of
 the path runs in the HIP kernels behind the C ABI, on torch's current stream.  There is no CPU or
 eager fallback: a missing library raises.
+
+The calls of the path are marshalled in native code (csrc/python_calls.cpp); a method of `load().calls` returns
+the call's status, or None for arguments that are not plain tensors and numbers, with nothing called: those take the ctypes
+way, which converts what can be converted and raises for the rest.
 """
 from __future__ import annotations
 
@@ -24,6 +28,10 @@ EXPORTS = ("quest_hadamard_quantize", "quest_hadamard_quantize_pair", "quest_had
 
 _i64, _i32, _f32, _p = ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p
 _lib = None
+# entry points of quest_python.Calls, in its order
+_NATIVE = ("quest_hadamard_quantize", "quest_hadamard_quantize_pair", "quest_hadamard_quantize_fp4",
+           "quest_hadamard_quantize_fp4_pair", "quest_lowbit_gemm", "quest_lowbit_gemm_fp4", "quest_trust_backward",
+           "quest_trust_backward_pair", "quest_grad_gemm", "quest_grad_gemm_fp4", "quest_weight_only_gemm")
 
 
 class QuestError(RuntimeError):
@@ -84,6 +92,8 @@ def load():
         lib.quest_container_bits.restype = _i32
         lib.quest_status_string.argtypes = [ctypes.c_int]
         lib.quest_status_string.restype = ctypes.c_char_p
+        from . import quest_python
+        lib.calls = quest_python.Calls(*(ctypes.cast(getattr(lib, name), _p).value for name in _NATIVE))
         _lib = lib
     return _lib
 
@@ -135,11 +145,15 @@ def quest_hadamard_quantize(x: torch.Tensor, had_block: int, bits: int, alpha: f
                             scales: torch.Tensor, mask: torch.Tensor | None = None,
                             xh_out: torch.Tensor | None = None) -> None:
     """x [rows, cols] (row stride x.stride(0)) -> codes, scales, mask, xh_out (caller-allocated)."""
-    rows, cols = x.shape
-    _check(load().quest_hadamard_quantize(_ptr(x), _dtype_code(x), rows, cols, x.stride(0),
-                                          had_block, bits, alpha, outer_trust, _ptr(codes),
-                                          _ptr(scales), _ptr(mask), _ptr(xh_out), _stream()),
-           "quest_hadamard_quantize")
+    status = (_lib or load()).calls.hadamard_quantize(x, had_block, bits, alpha, outer_trust, codes, scales, mask, xh_out,
+                                                      _stream)
+    if status is None:
+        rows, cols = x.shape
+        status = load().quest_hadamard_quantize(_ptr(x), _dtype_code(x), rows, cols, x.stride(0),
+                                                had_block, bits, alpha, outer_trust, _ptr(codes),
+                                                _ptr(scales), _ptr(mask), _ptr(xh_out), _stream())
+    if status:
+        raise QuestError(status, "quest_hadamard_quantize")
 
 
 def quest_hadamard_quantize_pair(x: torch.Tensor, w: torch.Tensor, had_block: int, bits: int, alpha: float = 0.0,
@@ -147,13 +161,17 @@ def quest_hadamard_quantize_pair(x: torch.Tensor, w: torch.Tensor, had_block: in
                                  w_codes: torch.Tensor, w_scales: torch.Tensor,
                                  x_mask: torch.Tensor | None = None, w_mask: torch.Tensor | None = None) -> None:
     """Activations x [rows_x, cols] and weights w [rows_w, cols] of one layer quantized by one call."""
-    if x.shape[1] != w.shape[1] or x.dtype != w.dtype:
-        raise ValueError("the two operands of a pair call share the row length and the dtype")
-    _check(load().quest_hadamard_quantize_pair(_ptr(x), x.shape[0], x.stride(0), _ptr(x_codes), _ptr(x_scales),
-                                               _ptr(x_mask), _ptr(w), w.shape[0], w.stride(0), _ptr(w_codes),
-                                               _ptr(w_scales), _ptr(w_mask), _dtype_code(x), x.shape[1], had_block,
-                                               bits, alpha, outer_trust, _stream()),
-           "quest_hadamard_quantize_pair")
+    status = (_lib or load()).calls.hadamard_quantize_pair(x, w, had_block, bits, alpha, outer_trust, x_codes, x_scales,
+                                                           x_mask, w_codes, w_scales, w_mask, _stream)
+    if status is None:
+        if x.shape[1] != w.shape[1] or x.dtype != w.dtype:
+            raise ValueError("the two operands of a pair call share the row length and the dtype")
+        status = load().quest_hadamard_quantize_pair(_ptr(x), x.shape[0], x.stride(0), _ptr(x_codes), _ptr(x_scales),
+                                                     _ptr(x_mask), _ptr(w), w.shape[0], w.stride(0), _ptr(w_codes),
+                                                     _ptr(w_scales), _ptr(w_mask), _dtype_code(x), x.shape[1], had_block,
+                                                     bits, alpha, outer_trust, _stream())
+    if status:
+        raise QuestError(status, "quest_hadamard_quantize_pair")
 
 
 def quest_hadamard_quantize_absmax(x: torch.Tensor, had_block: int, bits: int, *, codes: torch.Tensor,
@@ -171,11 +189,14 @@ def quest_hadamard_quantize_fp4(x: torch.Tensor, had_block: int, alpha: float = 
                                 scales: torch.Tensor, mask: torch.Tensor | None = None,
                                 xh_out: torch.Tensor | None = None) -> None:
     """As quest_hadamard_quantize, rounding to the scaled E2M1 grid; codes are E2M1 nibbles."""
-    rows, cols = x.shape
-    _check(load().quest_hadamard_quantize_fp4(_ptr(x), _dtype_code(x), rows, cols, x.stride(0), had_block,
-                                              alpha, _ptr(codes), _ptr(scales), _ptr(mask), _ptr(xh_out),
-                                              _stream()),
-           "quest_hadamard_quantize_fp4")
+    status = (_lib or load()).calls.hadamard_quantize_fp4(x, had_block, alpha, codes, scales, mask, xh_out, _stream)
+    if status is None:
+        rows, cols = x.shape
+        status = load().quest_hadamard_quantize_fp4(_ptr(x), _dtype_code(x), rows, cols, x.stride(0), had_block,
+                                                    alpha, _ptr(codes), _ptr(scales), _ptr(mask), _ptr(xh_out),
+                                                    _stream())
+    if status:
+        raise QuestError(status, "quest_hadamard_quantize_fp4")
 
 
 def quest_hadamard_quantize_fp4_pair(x: torch.Tensor, w: torch.Tensor, had_block: int, alpha: float = 0.0, *,
@@ -183,13 +204,17 @@ def quest_hadamard_quantize_fp4_pair(x: torch.Tensor, w: torch.Tensor, had_block
                                      w_scales: torch.Tensor, x_mask: torch.Tensor | None = None,
                                      w_mask: torch.Tensor | None = None) -> None:
     """As quest_hadamard_quantize_pair, rounding to the scaled E2M1 grid."""
-    if x.shape[1] != w.shape[1] or x.dtype != w.dtype:
-        raise ValueError("the two operands of a pair call share the row length and the dtype")
-    _check(load().quest_hadamard_quantize_fp4_pair(_ptr(x), x.shape[0], x.stride(0), _ptr(x_codes),
-                                                   _ptr(x_scales), _ptr(x_mask), _ptr(w), w.shape[0],
-                                                   w.stride(0), _ptr(w_codes), _ptr(w_scales), _ptr(w_mask),
-                                                   _dtype_code(x), x.shape[1], had_block, alpha, _stream()),
-           "quest_hadamard_quantize_fp4_pair")
+    status = (_lib or load()).calls.hadamard_quantize_fp4_pair(x, w, had_block, alpha, x_codes, x_scales, x_mask, w_codes,
+                                                               w_scales, w_mask, _stream)
+    if status is None:
+        if x.shape[1] != w.shape[1] or x.dtype != w.dtype:
+            raise ValueError("the two operands of a pair call share the row length and the dtype")
+        status = load().quest_hadamard_quantize_fp4_pair(_ptr(x), x.shape[0], x.stride(0), _ptr(x_codes),
+                                                         _ptr(x_scales), _ptr(x_mask), _ptr(w), w.shape[0],
+                                                         w.stride(0), _ptr(w_codes), _ptr(w_scales), _ptr(w_mask),
+                                                         _dtype_code(x), x.shape[1], had_block, alpha, _stream())
+    if status:
+        raise QuestError(status, "quest_hadamard_quantize_fp4_pair")
 
 
 def quest_alpha_star_fp4() -> float:
@@ -213,12 +238,16 @@ def quest_lowbit_gemm(a_codes: torch.Tensor, a_scales: torch.Tensor, b_codes: to
                       b_scales: torch.Tensor, K: int, bits: int, *, y: torch.Tensor | None,
                       acc_out: torch.Tensor | None = None, workspace: torch.Tensor | None = None) -> None:
     """y[M, N] (bf16) and/or acc_out[M, N] (int32) from packed codes [M, K*cb/8] and [N, K*cb/8]."""
-    M, N = a_codes.shape[0], b_codes.shape[0]
-    ld_y = y.stride(0) if y is not None else N
-    _check(load().quest_lowbit_gemm(_ptr(a_codes), _ptr(a_scales), M, _ptr(b_codes), _ptr(b_scales),
-                                    N, K, bits, _ptr(y), ld_y, _ptr(acc_out), _ptr(workspace),
-                                    _bytes(workspace), _stream()),
-           "quest_lowbit_gemm")
+    status = (_lib or load()).calls.lowbit_gemm(a_codes, a_scales, b_codes, b_scales, K, bits, y, acc_out, workspace,
+                                                _stream)
+    if status is None:
+        M, N = a_codes.shape[0], b_codes.shape[0]
+        ld_y = y.stride(0) if y is not None else N
+        status = load().quest_lowbit_gemm(_ptr(a_codes), _ptr(a_scales), M, _ptr(b_codes), _ptr(b_scales),
+                                          N, K, bits, _ptr(y), ld_y, _ptr(acc_out), _ptr(workspace),
+                                          _bytes(workspace), _stream())
+    if status:
+        raise QuestError(status, "quest_lowbit_gemm")
 
 
 def quest_lowbit_gemm_static(a_codes: torch.Tensor, a_scales: torch.Tensor, b_codes: torch.Tensor,
@@ -236,32 +265,41 @@ def quest_lowbit_gemm_fp4(a_codes: torch.Tensor, a_scales: torch.Tensor, b_codes
                           b_scales: torch.Tensor, K: int, *, y: torch.Tensor | None,
                           acc_out: torch.Tensor | None = None) -> None:
     """y[M, N] (bf16) and/or acc_out[M, N] (fp32) from packed E2M1 codes [M, K/2] and [N, K/2]."""
-    M, N = a_codes.shape[0], b_codes.shape[0]
-    ld_y = y.stride(0) if y is not None else N
-    _check(load().quest_lowbit_gemm_fp4(_ptr(a_codes), _ptr(a_scales), M, _ptr(b_codes), _ptr(b_scales),
-                                        N, K, _ptr(y), ld_y, _ptr(acc_out), _stream()),
-           "quest_lowbit_gemm_fp4")
+    status = (_lib or load()).calls.lowbit_gemm_fp4(a_codes, a_scales, b_codes, b_scales, K, y, acc_out, _stream)
+    if status is None:
+        M, N = a_codes.shape[0], b_codes.shape[0]
+        ld_y = y.stride(0) if y is not None else N
+        status = load().quest_lowbit_gemm_fp4(_ptr(a_codes), _ptr(a_scales), M, _ptr(b_codes), _ptr(b_scales),
+                                              N, K, _ptr(y), ld_y, _ptr(acc_out), _stream())
+    if status:
+        raise QuestError(status, "quest_lowbit_gemm_fp4")
 
 
 def quest_trust_backward(g: torch.Tensor, mask: torch.Tensor | None, had_block: int, *,
                          out: torch.Tensor) -> None:
     """out = IHT(mask (.) g) for contiguous g, out of shape [rows, cols]."""
-    rows, cols = g.shape
-    _check(load().quest_trust_backward(_ptr(g), _dtype_code(g), _ptr(mask), rows, cols, had_block,
-                                       _ptr(out), _dtype_code(out), _stream()),
-           "quest_trust_backward")
+    status = (_lib or load()).calls.trust_backward(g, mask, had_block, out, _stream)
+    if status is None:
+        rows, cols = g.shape
+        status = load().quest_trust_backward(_ptr(g), _dtype_code(g), _ptr(mask), rows, cols, had_block,
+                                             _ptr(out), _dtype_code(out), _stream())
+    if status:
+        raise QuestError(status, "quest_trust_backward")
 
 
 def quest_trust_backward_pair(g_x: torch.Tensor, mask_x: torch.Tensor | None, g_w: torch.Tensor,
                               mask_w: torch.Tensor | None, had_block: int, *, out_x: torch.Tensor,
                               out_w: torch.Tensor) -> None:
     """out_x = IHT(mask_x (.) g_x) and out_w = IHT(mask_w (.) g_w) by one call (contiguous, same row length)."""
-    if g_x.shape[1] != g_w.shape[1] or g_x.dtype != g_w.dtype or out_x.dtype != out_w.dtype:
-        raise ValueError("the two gradients of a pair call share the row length and the dtypes")
-    _check(load().quest_trust_backward_pair(_ptr(g_x), _ptr(mask_x), g_x.shape[0], _ptr(out_x), _ptr(g_w),
-                                            _ptr(mask_w), g_w.shape[0], _ptr(out_w), _dtype_code(g_x),
-                                            g_x.shape[1], had_block, _dtype_code(out_x), _stream()),
-           "quest_trust_backward_pair")
+    status = (_lib or load()).calls.trust_backward_pair(g_x, mask_x, g_w, mask_w, had_block, out_x, out_w, _stream)
+    if status is None:
+        if g_x.shape[1] != g_w.shape[1] or g_x.dtype != g_w.dtype or out_x.dtype != out_w.dtype:
+            raise ValueError("the two gradients of a pair call share the row length and the dtypes")
+        status = load().quest_trust_backward_pair(_ptr(g_x), _ptr(mask_x), g_x.shape[0], _ptr(out_x), _ptr(g_w),
+                                                  _ptr(mask_w), g_w.shape[0], _ptr(out_w), _dtype_code(g_x),
+                                                  g_x.shape[1], had_block, _dtype_code(out_x), _stream())
+    if status:
+        raise QuestError(status, "quest_trust_backward_pair")
 
 
 def quest_grad_gemm_workspace_bytes(which: int, M: int, N: int, K: int) -> int:
@@ -272,9 +310,12 @@ def quest_grad_gemm(which: int, dy: torch.Tensor, q_codes: torch.Tensor, q_scale
                     bits: int, M: int, N: int, K: int, *, out: torch.Tensor,
                     workspace: torch.Tensor | None = None) -> None:
     """which = 0: out[M, K] = dy what_h;  which = 1: out[N, K] = dy^T xhat_h (bf16)."""
-    _check(load().quest_grad_gemm(which, _ptr(dy), _ptr(q_codes), _ptr(q_scales), bits, M, N, K,
-                                  _ptr(out), _ptr(workspace), _bytes(workspace), _stream()),
-           "quest_grad_gemm")
+    status = (_lib or load()).calls.grad_gemm(which, dy, q_codes, q_scales, bits, M, N, K, out, workspace, _stream)
+    if status is None:
+        status = load().quest_grad_gemm(which, _ptr(dy), _ptr(q_codes), _ptr(q_scales), bits, M, N, K,
+                                        _ptr(out), _ptr(workspace), _bytes(workspace), _stream())
+    if status:
+        raise QuestError(status, "quest_grad_gemm")
 
 
 def quest_grad_gemm_fp4_workspace_bytes(which: int, M: int, N: int, K: int) -> int:
@@ -285,9 +326,12 @@ def quest_grad_gemm_fp4(which: int, dy: torch.Tensor, q_codes: torch.Tensor, q_s
                         M: int, N: int, K: int, *, out: torch.Tensor,
                         workspace: torch.Tensor | None = None) -> None:
     """quest_grad_gemm for E2M1 codes (operands from quest_hadamard_quantize_fp4)."""
-    _check(load().quest_grad_gemm_fp4(which, _ptr(dy), _ptr(q_codes), _ptr(q_scales), M, N, K, _ptr(out),
-                                      _ptr(workspace), _bytes(workspace), _stream()),
-           "quest_grad_gemm_fp4")
+    status = (_lib or load()).calls.grad_gemm_fp4(which, dy, q_codes, q_scales, M, N, K, out, workspace, _stream)
+    if status is None:
+        status = load().quest_grad_gemm_fp4(which, _ptr(dy), _ptr(q_codes), _ptr(q_scales), M, N, K, _ptr(out),
+                                            _ptr(workspace), _bytes(workspace), _stream())
+    if status:
+        raise QuestError(status, "quest_grad_gemm_fp4")
 
 
 def quest_weight_only_gemm_workspace_bytes(M: int, N: int, K: int) -> int:
@@ -297,8 +341,11 @@ def quest_weight_only_gemm_workspace_bytes(M: int, N: int, K: int) -> int:
 def quest_weight_only_gemm(x: torch.Tensor, w_codes: torch.Tensor, w_scales: torch.Tensor, bits: int,
                            *, y: torch.Tensor, workspace: torch.Tensor | None = None) -> None:
     """y[M, N] (bf16) = x[M, K] (bf16) times the transposed weights given as packed codes [N, K*cb/8]."""
-    M, K = x.shape
-    N = w_codes.shape[0]
-    _check(load().quest_weight_only_gemm(_ptr(x), _ptr(w_codes), _ptr(w_scales), bits, M, N, K, _ptr(y),
-                                         _ptr(workspace), _bytes(workspace), _stream()),
-           "quest_weight_only_gemm")
+    status = (_lib or load()).calls.weight_only_gemm(x, w_codes, w_scales, bits, y, workspace, _stream)
+    if status is None:
+        M, K = x.shape
+        N = w_codes.shape[0]
+        status = load().quest_weight_only_gemm(_ptr(x), _ptr(w_codes), _ptr(w_scales), bits, M, N, K, _ptr(y),
+                                               _ptr(workspace), _bytes(workspace), _stream())
+    if status:
+        raise QuestError(status, "quest_weight_only_gemm")

@@ -1,4 +1,4 @@
-"""Builds libquest.so (the C-ABI HIP library) in-tree with hipcc for gfx950."""
+"""Builds libquest.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and the binding's native part."""
 from __future__ import annotations
 
 import os
@@ -7,6 +7,7 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libquest.so")
+PYTHON_LIB = os.path.join(_HERE, "quest_python.so")    # binding.py's calls in native code (csrc/python_calls.cpp)
 PROBE_LIB = os.path.join(_HERE, "libquest_probe.so")   # measurement aid of bench.py (include/quest_probe.h)
 SOURCES = ["quest_api.hip", "hadamard_quantize.hip", "hadamard_quantize_mfma.hip", "hadamard_quantize_rows.hip",
            "lowbit_gemm.hip", "skinny_gemm.hip", "fp4_gemm.hip", "trust_backward.hip", "trust_backward_mfma.hip",
@@ -25,6 +26,19 @@ HIPCC_FLAGS = [
 ]
 
 
+def python_calls_command(out: str) -> list[str]:
+    """The CPython module: host code against the headers and libraries of the installed torch."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"],
+            "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            os.path.join(CSRC, "python_calls.cpp"), "-o", out, "-L" + os.path.join(root, "lib"), "-ltorch_python",
+            "-ltorch_cpu", "-lc10", "-Wl,-rpath," + os.path.join(root, "lib")]
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile every source and link libquest.so; always recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -32,6 +46,9 @@ def build_library(verbose: bool = False) -> str:
     os.makedirs(objdir, exist_ok=True)
     procs = []
     objects = []
+    python_tmp = PYTHON_LIB + f".tmp{os.getpid()}"
+    cmd = python_calls_command(python_tmp)
+    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
         objects.append(obj)
@@ -41,12 +58,13 @@ def build_library(verbose: bool = False) -> str:
         out = proc.communicate()[0].decode()
         lines = [l for l in out.splitlines() if "not a recognized feature" not in l]
         if proc.returncode != 0:
-            raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + "\n".join(lines))
+            raise RuntimeError("compilation failed: " + " ".join(cmd) + "\n" + "\n".join(lines))
         if verbose and lines:
             print("\n".join(lines))
     tmp = LIB + f".tmp{os.getpid()}"
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objects])
     os.replace(tmp, LIB)
+    os.replace(python_tmp, PYTHON_LIB)
     tmp = PROBE_LIB + f".tmp{os.getpid()}"
     out = subprocess.run([hipcc, *HIPCC_FLAGS, "-shared", os.path.join(CSRC, "peak_probe.hip"), "-o", tmp],
                          stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
