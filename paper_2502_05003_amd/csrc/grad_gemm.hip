@@ -19,6 +19,7 @@ namespace {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------------
 // Main path.  The code-packed operand is first expanded once to bf16(s u), [C, K] row-major, in
@@ -55,8 +56,8 @@ struct TileSizes {
     static constexpr int kStage = kLeftBytes + kRightBytes;   // left operand, then right operand
     static constexpr int kStages = 160 * 1024 / kStage;       // ring of stages: 5 (TI = 4, 3), 6, 8
     static constexpr int kLds = kStages * kStage;
-    static constexpr int kParkBytes = 4 * (32 * TI) * 256;    // epilogue: 32 TI rows of 256 bytes per wave
-    static_assert(kParkBytes <= kLds && kLds <= 160 * 1024, "the epilogue reuses the stages");
+    static constexpr int kParkBytes = 32 * 128;               // epilogue: a wave's 32 rows by 64 columns
+    static_assert(4 * kParkBytes <= kStage && kLds <= 160 * 1024, "the epilogue parks in the stage that was read last");
 };
 
 typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
@@ -222,9 +223,18 @@ __device__ __forceinline__ int column_swz(int crow)
     return EDGE % 128 != 0 ? ((crow >> 1) & 1) << 2 : (crow & 3) << 2;
 }
 
+/*
+ * RING: for workgroups that work through several whole tiles.  A tile's two ends, a prologue that waits for its first
+ * transfers and an epilogue whose stores all workgroups issue at once, took 10 to 13 us with nothing to multiply meanwhile; with
+ * RING the next tile's first steps are requested during the last ones of a tile, and its stores are waited for only when
+ * the counter of vector-memory operations cannot tell them from transfers any more, three or four steps into the next
+ * tile (us per call, alone, before / now: G_x 16384 x 5632 x 2048, 2 tiles of 256 rows each, 310 / 296, 16384 x 2048 x 5632, 8 of 192
+ * rows, 354 / 337, 16384 x 1024 x 4096 162 / 136; weight-only 16384 x 4096 x 1024 161 / 132).  Workgroups with a single tile run the
+ * loop without the two instructions per step that this costs.
+ */
 constexpr int kSpreadModes = 5;   // bit m: MODE m spreads its transfers over the whole step (measured, see below)
 
-template <int MODE, int TI>
+template <int MODE, int TI, bool RING>
 __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     const uint16_t *__restrict__ dy, int64_t ld_dy, const uint16_t *__restrict__ qhat, int64_t ld_right,
     int C, int R, int K, int tiles_r, int tiles_k, int per_block, int phase_period, uint16_t *__restrict__ out,
@@ -249,7 +259,12 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
         block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);   // one contiguous run per XCD
     }
     const int64_t unit_begin = (int64_t)block * per_block;
-    const int64_t unit_end = min(unit_begin + per_block, total_units);
+    if (unit_begin >= total_units)
+        return;
+    // wave-uniform, and 32-bit from here on: this workgroup's units, and where the first one is
+    int units_left = __builtin_amdgcn_readfirstlane((int)min((int64_t)per_block, total_units - unit_begin));
+    const int first_tile = __builtin_amdgcn_readfirstlane((int)(unit_begin / steps));
+    const int first_step = __builtin_amdgcn_readfirstlane((int)(unit_begin - (int64_t)first_tile * steps));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -291,13 +306,22 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     else
         row_offsets(wr * 32 * TI, left_off);
 
-    for (int64_t unit = unit_begin; unit < unit_end;) {
-    const int tile = (int)(unit / steps);
-    const int s_begin = (int)(unit - (int64_t)tile * steps);
-    const int s_end = (int)min((int64_t)steps, unit_end - (int64_t)tile * steps);
-    unit += s_end - s_begin;
+    // where a tile begins (wave-uniform)
+    auto origin = [&](int tile, int &r0, int &k0) __attribute__((always_inline)) {
+        int r, k;
+        tile_origin(tile, Sizes::kRows, tiles_r, tiles_k, phase_period, r, k);
+        r0 = __builtin_amdgcn_readfirstlane(r);
+        k0 = __builtin_amdgcn_readfirstlane(k);
+    };
+    constexpr int kStores = 8 * TI;   // of a wave and a whole tile
+    bool carried = false;             // the first steps of this tile were requested during the last ones of the tile before
+    int storing = 0;                  // steps to come whose wait has a whole tile's stores behind it
+    int cur_off = 0;                  // byte offset of the current stage
     int r0, k0;
-    tile_origin(tile, Sizes::kRows, tiles_r, tiles_k, phase_period, r0, k0);
+    origin(first_tile, r0, k0);
+    for (int tile = first_tile, s_begin = first_step; units_left > 0; ++tile, s_begin = 0) {
+    const int s_end = min(steps, s_begin + units_left);
+    units_left -= s_end - s_begin;
     // Transfers: piece q of an operand is the 1 KiB at offset (4 q + wave) KiB; lane l of it lands at 16 l.
     // Per-lane byte offsets from the operand's position of the step:
     //   row form:    row 16 (4 q + wave) + l / 4, chunk (l % 4) ^ ((l / 16) & 3)
@@ -335,9 +359,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = 0.0f;
-
     // TI + 4 transfers per wave fill the stage at LDS byte address `stage` with contraction step `step`
-    auto transfer = [&](auto pc, uint32_t stage, int step) {
+    auto transfer = [&](auto pc, uint32_t stage, int step) __attribute__((always_inline)) {
         constexpr int p = decltype(pc)::value;
         const int at = min(step, s_end - 1);   // past the end: a valid step again, never used
         if constexpr (p < TI)
@@ -406,25 +429,49 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
     constexpr int kIssuedAtWait = kSpread ? (kTransfers + 1) / 2 : 0;   // transfers of this step before its wait
     static_assert(transfer_slot(kIssuedAtWait) >= kHalf && (kIssuedAtWait == 0 || transfer_slot(kIssuedAtWait - 1) < kHalf),
                   "the wait counts the transfers issued before it");
-    static_for<kAhead>([&](auto sc) {
-        static_for<kTransfers>([&](auto pc) {
-            transfer(pc, smem_addr + decltype(sc)::value * kGStage, s_begin + decltype(sc)::value);
+    if (!carried) {
+        static_for<kAhead>([&](auto sc) {
+            static_for<kTransfers>([&](auto pc) {
+                transfer(pc, smem_addr + decltype(sc)::value * kGStage, s_begin + decltype(sc)::value);
+            });
         });
-    });
-    wait_vmcnt<kTransfers * (kAhead - 1)>();
-    __builtin_amdgcn_s_barrier();
-    static_for<kReads>([&](auto nc) { load_frag(nc, smem, std::integral_constant<int, 0>{}); });
+        wait_vmcnt<kTransfers * (kAhead - 1)>();
+        __builtin_amdgcn_s_barrier();
+        cur_off = 0;
+        static_for<kReads>([&](auto nc) { load_frag(nc, smem, std::integral_constant<int, 0>{}); });
+    }
+    // The ring runs on from tile to tile where the next one's transfers differ in their base addresses alone (neither or
+    // both end at the same edge of the output).  Else, and after the last tile, the look-ahead fetches the last step again.
+    int next_r0 = 0, next_k0 = 0;
+    bool carry = false;
+    if (units_left > 0) {
+        origin(tile + 1, next_r0, next_k0);
+        carry = RING && s_end - s_begin >= 2 * kAhead && min(R - next_r0, Sizes::kRows) == min(R - r0, Sizes::kRows) &&
+                min(K - next_k0, GT) == min(K - k0, GT);
+    }
 
     // Scalar bookkeeping of a step is kept to additions and selects (one wave per SIMD: a chain of
     // dependent scalar instructions between two matrix instructions is time the matrix pipe idles):
     // byte offsets of the current stage and of the stage being refilled, and the operands' positions
     // at the step being fetched, min(step + kAhead, s_end - 1).
     constexpr int kRing = STAGES * kGStage;
-    int cur_off = 0;
-    int refill_off = (kSpread ? kAhead : STAGES - 1) * kGStage;
+    static_assert(kTransfers * (kAhead - 2) + kIssuedAtWait + kStores <= 63, "the six-bit counter tells them apart");
+    int refill_off = cur_off + (kSpread ? kAhead : STAGES - 1) * kGStage;
+    refill_off = refill_off >= kRing ? refill_off - kRing : refill_off;
     const char *left_fetch = left_base + (int64_t)min(s_begin + kAhead, s_end - 1) * left_step;
     const char *right_fetch = right_base + (int64_t)min(s_begin + kAhead, s_end - 1) * right_step;
-    for (int step = s_begin; step < s_end; ++step) {
+    // RING: the steps in three runs, which differ in the wait and in what is fetched: the ones whose wait has stores behind it,
+    // the ones up to the last that fetches from this tile, the ones that fetch the next tile's first.
+    const int tail = carry ? kAhead : 0, head = min(storing, s_end - s_begin - tail);
+    for (int run = RING ? 0 : 1, step = s_begin; run < (RING ? 3 : 2); ++run) {
+    const int run_end = !RING ? s_end : run == 0 ? s_begin + head : run == 1 ? s_end - tail : s_end;
+    if (RING && run == 2 && tail > 0) {
+        left_fetch = reinterpret_cast<const char *>(TRANSPOSED ? dy + next_r0 : dy + (int64_t)next_r0 * ld_dy);
+        right_fetch = reinterpret_cast<const char *>(RIGHT_ROWS ? qhat + (int64_t)next_k0 * ld_right : qhat + next_k0);
+    }
+    // (steps to go that advance the operands' positions)
+    const int last_advance = RING && run == 2 ? s_end : s_end - 1 - kAhead;
+    for (; step < run_end; ++step) {
         const uint8_t *cur_stage = smem + cur_off;
         const int nxt_off = cur_off + kGStage == kRing ? 0 : cur_off + kGStage;
         const uint8_t *nxt_stage = smem + nxt_off;
@@ -455,7 +502,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
             if constexpr (k == kHalf - 1) {
                 // all transfers of step + 1 have landed: what may still be in flight are the groups of
                 // the steps after it and, when spread, the transfers this step has issued so far
-                wait_vmcnt<kTransfers * (kAhead - 2) + kIssuedAtWait>();
+                constexpr int kNewer = kTransfers * (kAhead - 2) + kIssuedAtWait;
+                if constexpr (RING)
+                    wait_vmcnt_either<kNewer + kStores, kNewer>(run);
+                else
+                    wait_vmcnt<kNewer>();
                 __builtin_amdgcn_s_barrier();
             }
             static_for<kTransfers>([&](auto pc) {
@@ -466,59 +517,80 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
         });
         cur_off = nxt_off;
         refill_off = refill_off + kGStage == kRing ? 0 : refill_off + kGStage;
-        if (step + 1 + kAhead < s_end) {
+        if (step < last_advance) {
             left_fetch += left_step;
             right_fetch += right_step;
         }
     }
-    wait_vmcnt<0>();   // the look-ahead transfers still write into the stages
+    }
+    if (!carry)
+        wait_vmcnt<0>();   // the look-ahead transfers still write into the stages
 
     // Epilogue.  A segment that is not a whole tile leaves its accumulators as they are, in fp32.
+    const int block_row = r0 + (wave_u >> 1) * 32 * TI, block_col = k0 + (wave_u & 1) * 128;
+    storing = 0;
+    carried = carry;
+    r0 = next_r0;
+    k0 = next_k0;
     __syncthreads();
-    if (TI == 4 && (s_begin != 0 || s_end != steps)) {   // (only tiles of 256 rows are ever split)
+    if (TI == 4 && !RING && s_end - s_begin != steps) {   // (only tiles of 256 rows are ever split, and not with RING)
         float4 *slot = partial + ((int64_t)(2 * block + (s_begin == 0 ? 1 : 0)) * 4 + wave) * (64 * 64) + lane;
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 4; ++j) {
+                asm volatile("" : "+a"(acc[i][j]));   // as below
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     __builtin_nontemporal_store(
                         v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]},
                         reinterpret_cast<v4f *>(slot + ((i * 4 + j) * 4 + q) * 64));
+            }
         continue;   // LDS untouched since the barrier
     }
     // Each accumulator tile is a transposed output tile: lane l holds output row l % 32
-    // and, in register r, output column 8 (r / 4) + 4 (l / 32) + r % 4.  Each wave parks its
-    // 32 TI x 128 block as bf16 in LDS of its own (chunks swizzled by row) and writes it out as
-    // 256-byte row segments.
-    uint8_t *park = smem + wave * (Sizes::kParkBytes / 4);
+    // and, in register r, output column 8 (r / 4) + 4 (l / 32) + r % 4.  A wave parks its block as bf16 in
+    // pieces of 32 rows by 64 columns (chunks swizzled by row) and writes them out as 128-byte row segments.  It parks
+    // in the stage that was read last, which every wave has left and which the next step does not refill (spread) or
+    // only behind its barrier (late).
+    uint8_t *const park = smem + (cur_off == 0 ? kRing : cur_off) - kGStage + wave * Sizes::kParkBytes;
+    const uint32_t lane_offset = (uint32_t)(lane >> 3) * (uint32_t)K * 2u + 16u * (lane & 7);
+    v4u out_reg[2][4];
+    auto store_piece = [&](auto pc) __attribute__((always_inline)) {   // (rows and columns come in multiples of 64)
+        constexpr int piece = decltype(pc)::value, i = piece / 2, half = piece % 2;
+        if (block_row + 32 * i < R && block_col + 64 * half < K) {
+            uint16_t *at = out + (int64_t)(block_row + 32 * i) * K + block_col + 64 * half;
 #pragma unroll
-    for (int i = 0; i < TI; ++i) {
-        const int row = i * 32 + lm;
+            for (int pass = 0; pass < 4; ++pass)
+                store_16_counted(at + (int64_t)(8 * pass) * K, lane_offset, out_reg[piece & 1][pass]);
+        }
+    };
+    static_for<2 * TI>([&](auto pc) {
+        constexpr int piece = decltype(pc)::value, i = piece / 2, half = piece % 2;
+        // (in accumulation registers until then: brought over all at once they would need as many others)
+        asm volatile("" : "+a"(acc[i][2 * half]), "+a"(acc[i][2 * half + 1]));
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int col = j * 32 + 8 * q + 4 * lh;
-                const int chunk = (col >> 3) ^ (row & 15);
-                *reinterpret_cast<uint2 *>(park + row * 256 + chunk * 16 + (col & 4) * 2) =
-                    make_uint2(pack_bf16(acc[i][j][4 * q + 0], acc[i][j][4 * q + 1]),
-                               pack_bf16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
+                const v16f &a = acc[i][2 * half + j];
+                *reinterpret_cast<uint2 *>(park + lm * 128 + (((4 * j + q) ^ (lm & 7)) << 4) + 8 * lh) =
+                    make_uint2(pack_bf16(a[4 * q + 0], a[4 * q + 1]), pack_bf16(a[4 * q + 2], a[4 * q + 3]));
             }
+#pragma unroll
+        for (int pass = 0; pass < 4; ++pass) {
+            const int row = 8 * pass + (lane >> 3), c = lane & 7;
+            out_reg[piece & 1][pass] = *reinterpret_cast<const v4u *>(park + row * 128 + ((c ^ (row & 7)) << 4));
         }
-    }
-    const int block_row = r0 + wr * 32 * TI;
-    uint16_t *out_base = out + (int64_t)block_row * K + k0 + wc * 128;
-#pragma unroll 4
-    for (int pass = 0; pass < 8 * TI; ++pass) {
-        const int row = pass * 4 + (lane >> 4);
-        const int c = lane & 15;
-        const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 256 + ((c ^ (row & 15)) << 4));
-        if (block_row + row < R && k0 + wc * 128 + c * 8 < K)
-            *reinterpret_cast<uint4 *>(out_base + (int64_t)row * K + c * 8) = v;
-    }
-    __syncthreads();   // the next segment's first stage overwrites the parked block
+        if constexpr (piece > 0)
+            store_piece(std::integral_constant<int, piece - 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    store_piece(std::integral_constant<int, 2 * TI - 1>{});
+    if (!carry)
+        __syncthreads();   // the next tile's first stages may be where a block is parked
+    else if (block_row + 32 * TI <= R && block_col + 128 <= K)   // (fewer stores at the output's edge: waited for)
+        storing = kAhead - 1;
     }
 }
 
@@ -705,7 +777,9 @@ template <int MODE, int TI>
 hipError_t launch_tiles(const GradGemmPlan &p, const uint16_t *left, const uint16_t *qhat, int64_t ld_right, uint16_t *out,
                         float4 *partial, hipStream_t stream)
 {
-    hipLaunchKernelGGL((grad_gemm_tile_kernel<MODE, TI>), dim3((unsigned)p.blocks), dim3(kGemmThreads), TileSizes<TI>::kLds,
+    const bool ring = !p.split && p.per_block > p.steps;
+    auto kernel = ring ? grad_gemm_tile_kernel<MODE, TI, true> : grad_gemm_tile_kernel<MODE, TI, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)p.blocks), dim3(kGemmThreads), TileSizes<TI>::kLds,
                        stream, left, p.ld_left, qhat, ld_right, (int)p.contraction, (int)p.out_rows, (int)p.out_cols,
                        p.tiles_r, p.tiles_k, p.per_block, p.phase_period, out, partial);
     return hipGetLastError();
@@ -721,16 +795,26 @@ hipError_t launch_mode(const GradGemmPlan &p, const uint16_t *left, const uint16
                        : launch_tiles<MODE, 1>(p, left, qhat, ld_right, out, partial, stream);
 }
 
+template <int MODE, int TI>
+hipError_t prepare_tiles()
+{
+    const hipError_t err =
+        allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, TI, false>), TileSizes<TI>::kLds);
+    return err != hipSuccess ? err
+                             : allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, TI, true>),
+                                                 TileSizes<TI>::kLds);
+}
+
 template <int MODE>
 hipError_t prepare_mode()
 {
-    hipError_t err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 4>), TileSizes<4>::kLds);
+    hipError_t err = prepare_tiles<MODE, 4>();
     if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 3>), TileSizes<3>::kLds);
+        err = prepare_tiles<MODE, 3>();
     if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 2>), TileSizes<2>::kLds);
+        err = prepare_tiles<MODE, 2>();
     if (err == hipSuccess)
-        err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, 1>), TileSizes<1>::kLds);
+        err = prepare_tiles<MODE, 1>();
     return err;
 }
 

@@ -208,6 +208,18 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// wait until at most A (choice = 0) or B < A operations are outstanding; one block, so that the code around stays one, without
+// a jump for B
+template <int A, int B>
+__device__ __forceinline__ void wait_vmcnt_either(int choice)
+{
+    static_assert(B >= 0 && B < A && A <= 63, "vmcnt is a six-bit counter");
+    asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 0f\n\ts_waitcnt vmcnt(%2)\n0:\ts_waitcnt vmcnt(%1)"
+                 :
+                 : "s"(choice), "n"(A), "n"(B)
+                 : "memory", "scc");
+}
+
 // ---- rows staged through LDS by the memory system (fused quantizer, trust backward) ----
 // A wave requests its next row with global -> LDS transfers, which hold no registers while in flight,
 // and goes on with the current row; when it comes back for the row, the vector-memory operations it
@@ -227,6 +239,14 @@ __device__ __forceinline__ void store_word_counted(void *uniform_base, uint32_t 
 {
     static_assert(IMM >= 0 && IMM < 4096, "the instruction's offset field");
     asm volatile("global_store_dword %0, %1, %2 offset:%3 nt" : : "v"(lane_offset), "v"(v), "s"(uniform_base), "n"(IMM) : "memory");
+}
+
+// 16 bytes per lane, as an instruction whose place among the vector-memory operations is the program's (what else is in
+// memory does not matter to it: no clobber, LDS accesses may move across)
+typedef uint32_t quest_v4u __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_16_counted(void *uniform_base, uint32_t lane_offset, quest_v4u v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, %2" : : "v"(lane_offset), "v"(v), "s"(uniform_base));
 }
 
 // 16 bytes per lane from global memory straight into LDS (lane l lands at lds_base + 16 l), streaming
