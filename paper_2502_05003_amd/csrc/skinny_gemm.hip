@@ -92,11 +92,11 @@ struct Sum<true> {
 
 /*
  * blockIdx.x: weight rows 16 NT blockIdx.x .., blockIdx.y: activation rows 16 MT blockIdx.y ..
- * blockDim.x / 64 waves.  Dynamic LDS: waves * MT * NT * 1 KiB.
+ * Dynamic LDS: WAVES * MT * NT * 1 KiB.
  * The weights are the row operand, so a lane's four sums are four consecutive outputs of one row.
  */
-template <int GRID, int MT, int NT, int BATCH>
-__global__ __launch_bounds__(512) void skinny_gemm_kernel(
+template <int GRID, int MT, int NT, int BATCH, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void skinny_gemm_kernel(
     const uint8_t *__restrict__ a_codes, const float *__restrict__ a_scales, const uint8_t *__restrict__ b_codes,
     const float *__restrict__ b_scales, int M, int N, int K, uint16_t *__restrict__ y, int64_t ld_y,
     void *__restrict__ acc_out)
@@ -107,7 +107,8 @@ __global__ __launch_bounds__(512) void skinny_gemm_kernel(
     constexpr int kContainer = C::kContainer;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, waves = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr int waves = WAVES;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row16 = lane & 15, quarter = lane >> 4;
     const int n0 = blockIdx.x * 16 * NT, m0 = blockIdx.y * 16 * MT;
@@ -206,9 +207,8 @@ __global__ __launch_bounds__(512) void skinny_gemm_kernel(
         }
     }
 
-    // The waves' sums: [wave][i][j][lane].  (The block of 64 x 64 always has four waves; their number as a constant makes
-    // the summation 0.2 to 0.4 us shorter.)
-    const int parked = MT * NT > 8 ? 4 : waves;
+    // The waves' sums: [wave][i][j][lane].  (Their number is a constant: the reads of a sum are then in flight together, which
+    // makes a call 0.1 to 0.4 us shorter.)
     Acc *park = reinterpret_cast<Acc *>(smem);
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -217,9 +217,10 @@ __global__ __launch_bounds__(512) void skinny_gemm_kernel(
             park[((wave * MT + i) * NT + j) * 64 + lane] = acc[i][j];
     __syncthreads();
     const bool quad_ok = y && (ld_y & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 7) == 0;
-    for (int t = tid; t < MT * NT * 64; t += blockDim.x) {
+    for (int t = tid; t < MT * NT * 64; t += 64 * WAVES) {
         Acc sum = park[t];
-        for (int v = 1; v < parked; ++v)
+#pragma unroll
+        for (int v = 1; v < waves; ++v)
             sum += park[v * (MT * NT * 64) + t];
         const int tile = t >> 6, l = t & 63;
         const int m = m0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
@@ -255,11 +256,11 @@ __global__ __launch_bounds__(512) void skinny_gemm_kernel(
     }
 }
 
-template <int GRID, int MT, int NT, int BATCH>
-hipError_t launch(const SkinnyGemmArgs &a, int waves, hipStream_t stream)
+template <int GRID, int MT, int NT, int BATCH, int WAVES>
+hipError_t launch(const SkinnyGemmArgs &a, hipStream_t stream)
 {
     const dim3 grid((unsigned)((a.N + 16 * NT - 1) / (16 * NT)), (unsigned)((a.M + 16 * MT - 1) / (16 * MT)));
-    hipLaunchKernelGGL((skinny_gemm_kernel<GRID, MT, NT, BATCH>), grid, dim3(64 * waves), waves * MT * NT * 1024, stream,
+    hipLaunchKernelGGL((skinny_gemm_kernel<GRID, MT, NT, BATCH, WAVES>), grid, dim3(64 * WAVES), WAVES * MT * NT * 1024, stream,
                        a.a_codes, a.a_scales, a.b_codes, a.b_scales, (int)a.M, (int)a.N, (int)a.K,
                        static_cast<uint16_t *>(a.y), a.ld_y, a.acc_out);
     return hipGetLastError();
@@ -273,27 +274,34 @@ int64_t block_count(int64_t M, int64_t N, int mt, int nt)
 // The block: the smallest one that leaves no more than a workgroup per compute unit.  Small blocks
 // spread the loads over the chip, large ones read each operand less often; a workgroup more than the
 // chip holds costs a second round of latency.  Measured (us, block / waves; 4 bits):
-//   2048 x 5632, 24 rows: 1x1 5.4, 2x1 6.2, 2x2 7+     5632 x 2048, 24 rows: 2x2 4.7, 2x1 5.2, 1x1 5.2
-//   4096 x 1024, 64 rows: 2x2 3.4, 4x1 3.7, 1x1 4.2    5632 x 2048, 128 rows: 4x4 8.1, 4x2 8.8, 4x1 10+
+//   2048 x 5632, 24 rows: 1x1/8 4.9, 1x1/4 6.2, 1x2/8 6.3   4096 x 1024, 64 rows: 2x2/4 3.3, 1x2/4 3.6, 1x1/4 4.0
+//   4096 x 1024, 128 rows: 4x2/8 4.0, 2x2/4 4.2, 4x4/4 4.4  5632 x 2048, 128 rows: 4x4/4 7.8, 2x2/4 8.2, 4x2/8 8.4
 // With 16 rows or fewer the activations are next to nothing, and 1x1 is within 3 % of the best
-// everywhere (11008 x 4096, 1 row: 1x1 6.4, 1x2 7.0).
+// everywhere (11008 x 4096, 8 rows: 1x1 6.9, 1x2 7.4).  Where blocks are many the largest one pays when the
+// contraction is long enough for what it saves in reads (5632 x 5632, 128 rows: 4x4/4 14.1, 4x2/8 17.6), else 4x2 with its
+// shorter summation, by eight waves as long as a unit has two of its blocks at most (2048 x 1664, 512 rows: 4x2/8
+// 5.6, 4x2/4 6.2, 4x4/4 6.3; 2 bits: 4096 x 1024, 333 rows: 4x2/4 7.1, 4x4/4 7.6, 4x2/8 7.7).
 template <int GRID>
 hipError_t launch_grid(const SkinnyGemmArgs &a, hipStream_t stream)
 {
     constexpr int64_t kUnitsOfChip = 256;
     auto fits = [&](int mt, int nt) { return block_count(a.M, a.N, mt, nt) <= kUnitsOfChip; };
     if (a.M <= 16 || fits(1, 1)) {
-        // eight waves when workgroups are few and the contraction is long (2048 x 5632, 1 row: 4.4 against 5.1)
-        const bool more_waves = a.K >= 32 * kUnit && 2 * block_count(a.M, a.N, 1, 1) <= kUnitsOfChip;
-        return launch<GRID, 1, 1, 2>(a, more_waves ? 8 : 4, stream);
+        // two units of a wave in flight when workgroups are few and the contraction is long (2048 x 5632, 1 row: 4.2
+        // against 4.3; 24 rows, a workgroup for each compute unit, 5.1 against 4.9)
+        if (a.K >= 32 * kUnit && 2 * block_count(a.M, a.N, 1, 1) <= kUnitsOfChip)
+            return launch<GRID, 1, 1, 2, 8>(a, stream);
+        return launch<GRID, 1, 1, 1, 8>(a, stream);
     }
     if (fits(1, 2))
-        return launch<GRID, 1, 2, 2>(a, 4, stream);
+        return launch<GRID, 1, 2, 2, 4>(a, stream);
     if (a.M <= 32 || fits(2, 2))
-        return launch<GRID, 2, 2, 2>(a, 4, stream);
-    if (fits(4, 2))
-        return launch<GRID, 4, 2, 1>(a, 8, stream);
-    return launch<GRID, 4, 4, 1>(a, 4, stream);
+        return launch<GRID, 2, 2, 2, 4>(a, stream);
+    if (!fits(4, 2) && a.K >= 16 * kUnit)
+        return launch<GRID, 4, 4, 1, 4>(a, stream);
+    if (block_count(a.M, a.N, 4, 2) <= 2 * kUnitsOfChip)
+        return launch<GRID, 4, 2, 1, 8>(a, stream);
+    return a.K >= 8 * kUnit ? launch<GRID, 4, 2, 2, 4>(a, stream) : launch<GRID, 4, 2, 1, 4>(a, stream);
 }
 
 }  // namespace
@@ -319,7 +327,7 @@ bool skinny_gemm_preferred(int64_t M, int64_t N, int64_t K, int grid)
 hipError_t prepare_skinny_gemm_kernels()
 {
     hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(skinny_gemm_kernel<4, 1, 1, 2>));
+    return hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(skinny_gemm_kernel<4, 1, 1, 1, 8>));
 }
 
 hipError_t launch_skinny_gemm(const SkinnyGemmArgs &a, hipStream_t stream)

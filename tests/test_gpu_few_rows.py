@@ -99,3 +99,10 @@ def test_calls_go_to_the_current_stream():
         with torch.cuda.stream(stream):
             assert q._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
     assert len({stream.cuda_stream for stream in streams}) == 3
+
+
+# many blocks: 4x2 sixteens by four waves, one and two units of a wave in flight; 4x4
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("M,N,K", [(65, 8200, 192), (70, 8200, 1088), (66, 8200, 2112)])
+def test_integer_grids_many_blocks(M, N, K, bits):
+    test_integer_grids(M, N, K, bits)
