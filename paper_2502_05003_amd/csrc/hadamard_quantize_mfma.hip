@@ -47,6 +47,7 @@ constexpr int kWavesPerEu = 4;
 
 constexpr int kThreads = 256;
 constexpr int kRowsPerBlock = kThreads / 64;
+constexpr int64_t kSharedRows = 128;   // up to here a row may be a workgroup's (see launch)
 
 // Streaming stores: the outputs are not read again by this kernel.  The inline-assembly form is for
 // the code path that counts its own outstanding memory operations (see the row loop).
@@ -77,8 +78,21 @@ constexpr int hq_waves_per_eu()
     return (HOLD_ALL && (U > 32 || (F32 && U >= 24))) ? 2 : U > 40 ? 3 : kWavesPerEu;
 }
 
+// Groups of tiles that a row is worked off in (one group: nothing to share)
+template <int U, int LOG2N, bool HOLD_ALL>
+constexpr int hq_groups()
+{
+    constexpr int tiles = (U + 7) / 8, span = LOG2N > 10 ? 1 << (LOG2N - 10) : 2;
+    return HOLD_ALL || span >= tiles ? 1 : (tiles + span - 1) / span;
+}
+
+/*
+ * SHARED: a workgroup's four waves share its one row, for launches of few rows.  They bring it in together, each takes the
+ * whole row's sum of squares (in the order of a wave that has the row to itself, so that the scale does not depend on
+ * who computes it), then transforms, rounds and stores every fourth group of tiles.
+ */
 template <int U, int LOG2N, bool WITH_MASK, bool FP4 = false, int BITS = 4, typename In = uint16_t,
-          bool ABSMAX = false>
+          bool ABSMAX = false, bool SHARED = false>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(hq_waves_per_eu<U, (sizeof(In) == 4 || ABSMAX), sizeof(In) == 4>())))
 void hq_mfma_kernel(
@@ -127,8 +141,9 @@ void hq_mfma_kernel(
     constexpr int kPieces = U / 4;
     extern __shared__ __attribute__((aligned(16))) uint8_t row_buffers[];
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const uint8_t *my_buffer = row_buffers + wave_u * (256 * U);
-    const uint32_t my_buffer_addr = lds_address(row_buffers) + (uint32_t)wave_u * (256u * U);
+    const int buffer_wave = SHARED ? 0 : wave_u;
+    const uint8_t *my_buffer = row_buffers + buffer_wave * (256 * U);
+    const uint32_t my_buffer_addr = lds_address(row_buffers) + (uint32_t)buffer_wave * (256u * U);
     const uint32_t piece_offset = (uint32_t)(64 * (lane >> 2) + 16 * ((lane & 3) ^ ((lane >> 4) & 3)));
     auto request_row = [&](int64_t row_of_launch) {
         const bool from_b = row_of_launch >= rows_a;
@@ -137,11 +152,12 @@ void hq_mfma_kernel(
                    : reinterpret_cast<const uint16_t *>(x_a) + row_of_launch * ld_a);
 #pragma unroll
         for (int i = 0; i < kPieces; ++i)
-            lds_dma16_stream(base + 1024 * i, piece_offset, my_buffer_addr + 1024 * i);
+            if (!SHARED || (i & 3) == wave_u)
+                lds_dma16_stream(base + 1024 * i, piece_offset, my_buffer_addr + 1024 * i);
     };
     // the first row is requested before anything else is set up
-    const int64_t row_stride = (int64_t)gridDim.x * kRowsPerBlock;
-    int64_t row_of_launch = (int64_t)blockIdx.x * kRowsPerBlock + wave_u;
+    const int64_t row_stride = (int64_t)gridDim.x * (SHARED ? 1 : kRowsPerBlock);
+    int64_t row_of_launch = SHARED ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kRowsPerBlock + wave_u;
     if constexpr (kLdsRow) {
         if (row_of_launch < rows)
             request_row(row_of_launch);
@@ -196,8 +212,9 @@ void hq_mfma_kernel(
                 raw.a[t][0] = make_uint4(0, 0, 0, 0);
                 raw.a[t][1] = make_uint4(0, 0, 0, 0);
                 if (t < T - 1 || m < kTailRows) {
-                    const v4u n0 = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(src + 1024 * t));
-                    const v4u n1 = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(src + 1024 * t + 8));
+                    const v4u *at = reinterpret_cast<const v4u *>(src + 1024 * t);
+                    const v4u n0 = SHARED ? at[0] : __builtin_nontemporal_load(at);       // (shared: read by four waves)
+                    const v4u n1 = SHARED ? at[1] : __builtin_nontemporal_load(at + 1);
                     raw.a[t][0] = make_uint4(n0.x, n0.y, n0.z, n0.w);
                     raw.a[t][1] = make_uint4(n1.x, n1.y, n1.z, n1.w);
                 }
@@ -248,10 +265,12 @@ void hq_mfma_kernel(
         uint8_t *mask = from_b ? mask_b : mask_a;
         RawRow raw;
         if constexpr (kLdsRow) {
-            wait_vmcnt_upto(stores_after_request);   // this row has landed
+            wait_vmcnt_upto(SHARED ? 0 : stores_after_request);   // this row has landed
+            if constexpr (SHARED)
+                __syncthreads();
             read_row(raw);
             __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): the buffer has been read, it may be refilled
-            if (row_of_launch + row_stride < rows)
+            if (!SHARED && row_of_launch + row_stride < rows)
                 request_row(row_of_launch + row_stride);
             stores_issued = 0;
         } else {
@@ -288,7 +307,7 @@ void hq_mfma_kernel(
             // raw -> 2^(8-b) * (position in grid cells): the code ends up in the top b bits of a byte
             cell16 = inv_step * inv_sqrt_n * (float)(256 >> BITS);
             to_e2m1 = zero_row ? 0.0f : 6.0f * __builtin_amdgcn_rcpf(clip) * inv_sqrt_n;   // raw -> E2M1 units
-            emit_if(lane == 0, reinterpret_cast<uint32_t *>(scales + row),
+            emit_if(lane == 0 && (!SHARED || wave_u == 0), reinterpret_cast<uint32_t *>(scales + row),
                     __float_as_uint(clip * (FP4 ? 1.0f / 6.0f : 1.0f / (float)(kLevels - 1))));
         };
         float sumsq[kSums];
@@ -319,6 +338,8 @@ void hq_mfma_kernel(
         // that a long row holds its packed inputs and 32 transformed values, not all of them.
 #pragma unroll
         for (int g0 = 0; g0 < T; g0 += G) {
+            if (SHARED && ((g0 / G) & 3) != wave_u)
+                continue;
             float acc[G][16];
 #pragma unroll
             for (int u = 0; u < G; ++u) {
@@ -542,7 +563,13 @@ void hq_mfma_kernel(
 template <int U, int LOG2N, bool FP4 = false, int BITS = 4, typename In = uint16_t, bool ABSMAX = false>
 void launch(const QuantizeArgs &a, hipStream_t stream)
 {
-    const int64_t blocks_needed = (a.rows + a.rows2 + kRowsPerBlock - 1) / kRowsPerBlock;
+    // Few rows of three groups of tiles or more: a workgroup for each (us, a wave / a workgroup for a row: 5632 elements, with mask,
+    // 1 row 4.5 / 3.2, 24 rows 5.4 / 4.6, 128 rows 5.6 / 4.7, 512 rows 6.1 / 7.3; without mask 24 rows 4.7 / 4.45, 256
+    // rows 5.0 / 5.2; 11008, 128 rows 8.0 / 6.3.  Two groups, 2816: 1 row 2.9 / 2.9, 24 rows 3.7 / 4.3).
+    constexpr bool kMayShare = hq_groups<U, LOG2N, (sizeof(In) == 4 || ABSMAX)>() > 2;
+    const int64_t rows = a.rows + a.rows2;
+    const bool shared = kMayShare && rows <= kSharedRows;
+    const int64_t blocks_needed = shared ? rows : (rows + kRowsPerBlock - 1) / kRowsPerBlock;
     const int64_t max_blocks = 256 * kBlocksPerCu;
     const dim3 grid((unsigned)(blocks_needed < max_blocks ? blocks_needed : max_blocks));
     const auto *x = static_cast<const In *>(a.x);
@@ -550,14 +577,16 @@ void launch(const QuantizeArgs &a, hipStream_t stream)
     // one row buffer per wave for the rows that are staged through LDS (see the kernel), 45 KiB at most
     constexpr bool kLdsRow = sizeof(In) == 2 && (U % 4) == 0 && U <= 44;
     constexpr unsigned lds_bytes = kLdsRow ? kRowsPerBlock * 256 * U : 0;
-    if (a.mask)
-        hipLaunchKernelGGL((hq_mfma_kernel<U, LOG2N, true, FP4, BITS, In, ABSMAX>), grid, dim3(kThreads),
-                           lds_bytes, stream, x, a.rows, a.ld, a.log2n, a.alpha, a.trust_edge, a.codes, a.scales,
-                           a.mask, a.xh_out, x2, a.rows2, a.ld2, a.codes2, a.scales2, a.mask2);
-    else
-        hipLaunchKernelGGL((hq_mfma_kernel<U, LOG2N, false, FP4, BITS, In, ABSMAX>), grid, dim3(kThreads),
-                           lds_bytes, stream, x, a.rows, a.ld, a.log2n, a.alpha, a.trust_edge, a.codes, a.scales,
-                           a.mask, a.xh_out, x2, a.rows2, a.ld2, a.codes2, a.scales2, a.mask2);
+    static_assert(kSharedRows <= 256 * kBlocksPerCu, "a workgroup for each shared row");
+    auto kernel = a.mask ? hq_mfma_kernel<U, LOG2N, true, FP4, BITS, In, ABSMAX, false>
+                         : hq_mfma_kernel<U, LOG2N, false, FP4, BITS, In, ABSMAX, false>;
+    if constexpr (kMayShare) {
+        if (shared)
+            kernel = a.mask ? hq_mfma_kernel<U, LOG2N, true, FP4, BITS, In, ABSMAX, true>
+                            : hq_mfma_kernel<U, LOG2N, false, FP4, BITS, In, ABSMAX, true>;
+    }
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds_bytes, stream, x, a.rows, a.ld, a.log2n, a.alpha, a.trust_edge,
+                       a.codes, a.scales, a.mask, a.xh_out, x2, a.rows2, a.ld2, a.codes2, a.scales2, a.mask2);
 }
 
 }  // namespace

@@ -160,3 +160,21 @@ def test_inverse_transform_of_a_row_does_not_depend_on_the_others(rows, cols, n,
             keep = clean[part]
             assert torch.equal(out[keep], whole[part][keep])
     assert torch.isfinite(whole[clean].float()).all()
+
+
+# rows of three groups of tiles and more, which a workgroup shares up to 128 rows: 5632 and 4608 through LDS, 11008 not
+@pytest.mark.parametrize("cols,n,grid", [(5632, 512, 4), (5632, 32, 4), (5632, 512, 1), (5632, 512, 2), (5632, 512, 3), (5632, 512, 8),
+                                         (5632, 512, "fp4"), (4608, 512, 4), (11008, 256, 4), (11008, 1, 4)])
+def test_a_row_that_a_workgroup_shares_has_the_same_bytes(cols, n, grid):
+    """One row, the most that are shared, and more; with and without mask; with an infinity and a zero row among them."""
+    x = synth.outlier_activations(130, cols, 0.01, 20.0, seed=cols, dtype="bf16")
+    x[5], x[9] = 0, 0
+    x[9, 17] = 0x7F80   # infinity: this row's codes are unspecified
+    args = dict(bits=4, fp4=True) if grid == "fp4" else dict(bits=grid)
+    whole = gpu_quantize(x, n, want_xh=False, **args)
+    for rows in (1, 9, 128):
+        for want_mask in (True, False):
+            part = gpu_quantize(x[:rows], n, want_xh=False, want_mask=want_mask, **args)
+            keep = np.arange(rows) != 9
+            for name in ("codes", "scales") + (("mask",) if want_mask else ()):
+                assert np.array_equal(part[name][keep].view(np.uint8), whole[name][:rows][keep].view(np.uint8)), (name, rows)
