@@ -10,13 +10,16 @@
 // fewer rows than waves to fill the chip, a workgroup shares a row instead.  A tile that the row
 // does not reach is skipped; one that it ends in is transformed whole, with zeros.
 //
-// Measured against the general kernel (b = 4, us): bf16 8192 x 2560 48.7 -> 18.2, 8192 x 5120 94 -> 33.7,
-// 333 x 2560 7.2 -> 5.6; fp32 8192 x 2560 48.9 -> 30.1.  What bounds it is the vector unit (the row is touched
-// twice, the sum of squares being half an instruction per element), so the run-time branches, a handful per
-// 2048 elements, do not show.
+// Measured against the general kernel (b = 4, us): bf16 8192 x 2560 48.7 -> 15.6, 8192 x 5120 94 -> 29.7,
+// 333 x 2560 7.2 -> 5.1; fp32 8192 x 2560 48.9 -> 26.7.  What bounds it is the vector unit: of 11008 x 2560, b = 4 with its
+// mask, 24.6 us for 1045 vector instructions per row.  Hence straight code where the row fills a group of tiles (no test
+// for its end, no zeroing of what is not there) and for each block size (see one_tile_stages): 20.8 us, and 8192 elements
+// in blocks of 4096, 4096 rows, 32.1 -> 23.1.
 #include "hadamard_tile.h"
 #include "quest_internal.h"
 #include "row_staging.h"
+
+#include <type_traits>
 
 namespace quest {
 namespace {
@@ -26,7 +29,7 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // GRID: bits of the Eq. 1 grid (1, 2, 3, 4, 8), or 0 for E2M1.
 template <int GRID, typename In, int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 2 ? 4 : 3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 2 || sizeof(In) == 2 ? 4 : 3)))
 void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, int cols, int log2n, float alpha,
                     float trust_edge, uint8_t *__restrict__ codes_a, float *__restrict__ scales_a,
                     uint8_t *__restrict__ mask_a, float *__restrict__ xh_out, const In *__restrict__ x_b,
@@ -35,6 +38,10 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
 {
     constexpr bool kF32 = sizeof(In) == 4, kFp4 = GRID == 0;
     constexpr int BITS = kFp4 ? 4 : GRID, CB = BITS == 3 ? 4 : BITS, kLevels = 1 << BITS;
+    // Whether a row can end within a group of tiles: not where a block is as long as a group
+    constexpr bool kCanEnd = G == 2;
+    typedef std::true_type Whole;
+    typedef std::false_type Ending;
     extern __shared__ __attribute__((aligned(16))) uint8_t row_buffers[];
     __shared__ float wave_sums[4];
 
@@ -88,19 +95,21 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
     const float inv_sqrt_n = inv_sqrt_pow2(log2n), sqrt_n = sqrt_pow2(log2n);
     const int code_word = ((lane >> 3) & 3) + 4 * h + 8 * (lane & 7);
 
-    // This lane's share of a tile: 16 consecutive elements of tile row m (zeros beyond the row's end)
-    auto read_bf16 = [&](int t, uint32_t (&w)[8]) {
+    // This lane's share of a tile: 16 consecutive elements of tile row m (zeros beyond the row's end, which
+    // only the tile past the last whole one can reach)
+    const int whole_tiles = cols >> 10;
+    auto read_bf16 = [&](auto whole, int t, uint32_t (&w)[8]) __attribute__((always_inline)) {
         const v4u a = *reinterpret_cast<const v4u *>(buffer + Staging::read(t, m, h, 0, row_buffer));
         const v4u b = *reinterpret_cast<const v4u *>(buffer + Staging::read(t, m, h, 1, row_buffer));
-        const bool there = 1024 * t + 32 * m < cols;
+        const bool there = whole() || 1024 * t + 32 * m < cols;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             w[i] = there ? a[i] : 0u;
             w[4 + i] = there ? b[i] : 0u;
         }
     };
-    auto read_f32 = [&](int t, float (&f)[16]) {
-        const bool there = 1024 * t + 32 * m < cols;
+    auto read_f32 = [&](auto whole, int t, float (&f)[16]) __attribute__((always_inline)) {
+        const bool there = whole() || 1024 * t + 32 * m < cols;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const v4u v = *reinterpret_cast<const v4u *>(buffer + Staging::read(t, m, h, i, row_buffer));
@@ -123,16 +132,16 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
         // row has waves (see partial_sums_of_row)
         auto partial_sum = [&](int c) {
             float sumsq = 0.0f;
-            for (int t = c; t < tiles; t += sums) {
+            auto add_tile = [&](auto whole, int t) __attribute__((always_inline)) {
                 if constexpr (kF32) {
                     float f[16];
-                    read_f32(t, f);
+                    read_f32(whole, t, f);
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         sumsq = __fmaf_rn(f[i], f[i], sumsq);
                 } else {
                     uint32_t w[8];
-                    read_bf16(t, w);
+                    read_bf16(whole, t, w);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         v2bf pair;
@@ -140,7 +149,12 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                         sumsq = __builtin_amdgcn_fdot2_f32_bf16(pair, pair, sumsq, false);
                     }
                 }
-            }
+            };
+            int t = c;
+            for (; t < whole_tiles; t += sums)
+                add_tile(Whole(), t);
+            if (kCanEnd && t < tiles)
+                add_tile(Ending(), t);
             return wave_sum_dpp(sumsq);
         };
         float total = partial_sum(part);   // shared_row: parts = sums
@@ -163,12 +177,13 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
         uint32_t *code_row = reinterpret_cast<uint32_t *>((from_b ? codes_b : codes_a) + row * (cols * CB / 8));
         uint32_t *mask_row = reinterpret_cast<uint32_t *>(mask + row * (cols / 8));
 
-        for (int g0 = G * part; g0 < tiles; g0 += G * parts) {
+        // A group of tiles that the row fills has no test in it; the one that it ends in skips what is not there
+        auto group = [&](auto whole, int g0) __attribute__((always_inline)) {
             float acc[G][16];
 #pragma unroll
             for (int u = 0; u < G; ++u) {
                 const int t = g0 + u;
-                if (t < tiles) {   // wave-uniform
+                if (whole() || t < tiles) {   // wave-uniform
                     v16f z;
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
@@ -176,7 +191,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                     v8bf p0, p1;
                     if constexpr (kF32) {
                         float f[16];
-                        read_f32(t, f);
+                        read_f32(whole, t, f);
                         uint32_t hi[8], mid[8], lo[8];
                         split_bf16(f, hi, mid, lo);
                         __builtin_memcpy(&p0, &lo[0], 16);      // smallest piece first
@@ -191,7 +206,7 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                         __builtin_memcpy(&p1, &hi[4], 16);
                     } else {
                         uint32_t w[8];
-                        read_bf16(t, w);
+                        read_bf16(whole, t, w);
                         __builtin_memcpy(&p0, &w[0], 16);
                         __builtin_memcpy(&p1, &w[4], 16);
                     }
@@ -200,11 +215,8 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         acc[u][r] = z[r];
-                    one_tile_stages(log2n, acc[u]);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        acc[u][r] = 0.0f;
+                    if (G == 2)
+                        one_tile_stages(log2n, acc[u]);
                 }
             }
             if (!shared_row && g0 + G >= tiles) {   // the last tiles of the row have been read: the buffer may be refilled
@@ -213,11 +225,14 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                 if (row_of_launch + row_stride < rows)
                     request_row(row_of_launch + row_stride);
             }
-            tile_pair_stages<G>(log2n, acc);
+            if constexpr (G == 4)   // blocks of 4096
+                tile_stages<12, G>(acc);
+            else if (whole())   // (blocks of several tiles are in whole groups only)
+                tile_pair_stages<G>(log2n, acc);
 
             // in-lane elements of this group: 16 g0 .. , as far as the row goes
             constexpr int kGroupI = 16 * G;
-            const int first = 16 * g0, count_i = min(per_lane - first, kGroupI);
+            const int first = 16 * g0, count_i = whole() ? kGroupI : per_lane - first;
             auto elem = [&](int i) { return acc[i >> 4][reg_of_iota(i & 15)]; };
             if (xh_out && !from_b) {   // debug output of the first operand only: element = lane + 64 iota
                 float *dst = xh_out + row * cols + lane + 64 * first;
@@ -302,8 +317,13 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                     if constexpr (CB == 1) {
                         uint32_t negative = 0;
 #pragma unroll
-                        for (int i = 31; i >= 0; --i)
-                            negative = __builtin_amdgcn_alignbit(negative, __float_as_uint(elem(32 * cc + i)), 31);
+                        for (int half = 1; half >= 0; --half)
+                            if (32 * cc + 16 * half < count_i) {
+#pragma unroll
+                                for (int i = 15; i >= 0; --i)
+                                    negative = __builtin_amdgcn_alignbit(
+                                        negative, __float_as_uint(elem(32 * cc + 16 * half + i)), 31);
+                            }
                         const uint32_t code = bit_plan.apply(zero_row ? ~0u : ~negative);
                         if (mine)
                             store(code_row + at, code);
@@ -311,17 +331,26 @@ void hq_rows_kernel(const In *__restrict__ x_a, int64_t rows_a, int64_t ld_a, in
                     if (mask) {
                         uint32_t untrusted = 0;
 #pragma unroll
-                        for (int i = 31; i >= 0; --i) {
-                            const float slack = trust_raw - fabsf(elem(32 * cc + i));   // negative <=> untrusted
-                            untrusted = __builtin_amdgcn_alignbit(untrusted, __float_as_uint(slack), 31);
-                        }
+                        for (int half = 1; half >= 0; --half)
+                            if (32 * cc + 16 * half < count_i) {
+#pragma unroll
+                                for (int i = 15; i >= 0; --i) {   // slack negative <=> untrusted
+                                    const float slack = trust_raw - fabsf(elem(32 * cc + 16 * half + i));
+                                    untrusted = __builtin_amdgcn_alignbit(untrusted, __float_as_uint(slack), 31);
+                                }
+                            }
                         const uint32_t trusted = bit_plan.apply(~untrusted);
                         if (mine)
                             store(mask_row + at, trusted);
                     }
                 }
             }
-        }
+        };
+        int g0 = G * part;
+        for (; g0 + G <= whole_tiles; g0 += G * parts)
+            group(Whole(), g0);
+        if (kCanEnd && g0 < tiles)
+            group(Ending(), g0);
         if (shared_row && row_of_launch + row_stride < rows) {
             __syncthreads();   // every wave has read its tiles and the sums
             request_row(row_of_launch + row_stride);
@@ -336,8 +365,9 @@ hipError_t launch(const QuantizeArgs &a, hipStream_t stream)
     const int buffer = RowStaging<(int)sizeof(In)>::buffer_bytes((int)a.cols), groups = (int)((a.cols + 1024 * G - 1) / (1024 * G));
     const int64_t rows = a.rows + a.rows2;
     // A workgroup shares a row when there are few rows, and when sixteen waves' rows would not fit a compute
-    // unit's LDS (us, a row per wave / shared, both 3 to 6 % more since codes are the floor of the product:
-    // 333 x 5120 8.8 / 5.8, 1400 x 2560 7.3 / 7.7, 8192 x 2560 16.1 / 20.5, 8192 x 11008 87 / 59; fp32 8192 x 5120 67 / 47).
+    // unit's LDS (us, a row per wave / shared: 333 x 5120 7.7 / 5.5, 1000 x 2560 6.1 / 5.3, 1400 x 2560 6.8 / 6.8,
+    // 8192 x 2560 15.7 / 19.2, 8192 x 5120 29.1 / 29.7, 8192 x 6144 33.2 / 32.0, 4096 x 8192 in blocks of 4096 26.4 / 21.8;
+    // fp32 8192 x 5120 79 / 44).
     const bool shared_row = groups > 1 && (rows <= 1024 || buffer > 10 * 1024);
     // waves per workgroup: four, fewer when a shared row has fewer groups of tiles (one partial sum each); sixteen
     // per compute unit at most.  LDS: a shared row's buffer or, of rows of one group or of 10 KiB, four: 64 KiB at most.
@@ -398,21 +428,22 @@ hipError_t prepare_quantize_rows_kernels()
 
 // Which calls come here (`rows`: of both operands).  Everything that hadamard_quantize_mfma.hip has no instantiation
 // for, up to blocks of 4096: faster than the general kernel, in most shapes at every number of rows (us, here / there, 24
-// rows: 2560 elements 4.7 / 6.6, 5120 4.9 / 11.0, 64 3.4 / 4.3).  The exceptions are blocks of 8 or less, which the
+// rows: 2560 elements 4.6 / 6.6, 5120 4.6 / 11.0, 64 3.6 / 4.3).  The exceptions are blocks of 8 or less, which the
 // general kernel has in registers straight from its loads: bf16 rows still come here (50 x 1280 4.6 / 4.0, 750 x 1280
 // 4.8 / 4.9, 8192 x 1280 10.8 / 21.8), fp32 rows, which gain little, do not (50 x 1344 5.7 / 4.0, 8192 x 3584 30 / 35).
 // Of the fp32 shapes that it has, which it holds in registers as
-// a whole: long rows, and many rows (here / there: 24 rows of 2816 5.8 / 5.1, 3584 5.9 / 6.9, 5632 6.1 / 9.1;
-// 1024 x 2048 6.9 / 6.7, 2048 x 2048 8.5 / 8.9, 8192 x 2048 19.2 / 24.6; blocks of 4096, 24 rows 9.2 / 6.1,
-// 2048 rows 15.4 / 15.0, 8192 rows 43.9 / 51.7).  Both kernels make the same bits of these rows, so the number
-// of rows may decide; for bf16 rows they do not, and the shape alone does.
+// a whole: long rows, and many rows (here / there: 24 rows of 2816 5.4 / 5.5, 3584 5.4 / 6.3, 5632 5.5 / 7.9;
+// 768 x 2048 5.6 / 5.3, 1024 x 2048 5.8 / 6.6, 8192 x 2048 18.6 / 25.2; 1024 x 1024 4.6 / 4.3, 2048 x 1024 5.2 / 6.4;
+// blocks of 4096, 24 rows 6.9 / 6.3, 1024 rows 8.7 / 9.2, 8192 rows 38.6 / 50.9).  Both kernels make the same bits of these
+// rows, so the number of rows may decide; for bf16 rows they do not, and the shape alone does.
 bool quantize_rows_preferred(const QuantizeArgs &a, int64_t rows)
 {
     if (a.cols % 64 != 0 || a.log2n > 12 || a.mode == kQuantAbsMax)
         return false;
     if (!launch_hadamard_quantize_mfma(a, nullptr, true))
         return a.dtype == QUEST_BF16 || a.log2n > 3;
-    return a.dtype == QUEST_F32 && a.cols >= 1024 && (rows >= 2048 || (a.cols > 2816 && a.log2n < 12));
+    return a.dtype == QUEST_F32 && a.cols >= 1024 &&
+           (rows >= 2048 || (rows >= 1024 && a.cols >= 2048) || (a.cols > 2816 && a.log2n < 12));
 }
 
 hipError_t launch_hadamard_quantize_rows(const QuantizeArgs &a, hipStream_t stream)

@@ -292,43 +292,25 @@ struct TransposePlan {
     }
 };
 
-// tile_stages for a block size known only at run time: the stages on index bits 5 .. 9 of one tile
-// (wave-uniform branches), and the stages that pair whole tiles, bits 10 and up, of G tiles.
-__device__ __forceinline__ void one_tile_stages(int log2n, float (&acc)[16])
+// tile_stages for a block size known only at run time: the stages on index bits 5 .. 9 of one tile, and the
+// stages that pair whole tiles, bits 10 and up, of G tiles (wave-uniform branches).  One tile's are straight code for
+// each size: with a branch for each stage the values come together behind every one of them, a move per
+// butterfly.  (Not more tiles than one: of 32 values from eight such pieces of code, nine to eighteen went to scratch.)
+__device__ __forceinline__ void one_tile_stages(int log2n, float (&tile)[16])
 {
-    if (log2n > 5) {
-#pragma unroll
-        for (int r = 0; r < 16; r += 2)
-            bfly(acc[r], acc[r + 1]);
-    }
-    if (log2n > 6) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (!(r & 2))
-                bfly(acc[r], acc[r + 2]);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[r]), __float_as_uint(acc[r + 1]), false, false);
-        acc[r] = __uint_as_float(sw[0]);
-        acc[r + 1] = __uint_as_float(sw[1]);
-    }
-    if (log2n > 7) {
-#pragma unroll
-        for (int r = 0; r < 16; r += 2)
-            bfly(acc[r], acc[r + 1]);
-    }
-    if (log2n > 8) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (!(r & 4))
-                bfly(acc[r], acc[r + 4]);
-    }
-    if (log2n > 9) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            bfly(acc[r], acc[r + 8]);
-    }
+    float (&acc)[1][16] = *reinterpret_cast<float (*)[1][16]>(&tile);
+    if (log2n >= 10)
+        tile_stages<10, 1>(acc);
+    else if (log2n == 9)
+        tile_stages<9, 1>(acc);
+    else if (log2n == 8)
+        tile_stages<8, 1>(acc);
+    else if (log2n == 7)
+        tile_stages<7, 1>(acc);
+    else if (log2n == 6)
+        tile_stages<6, 1>(acc);
+    else
+        tile_stages<5, 1>(acc);
 }
 
 template <int G>

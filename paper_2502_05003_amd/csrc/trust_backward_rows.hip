@@ -68,9 +68,13 @@ __device__ __forceinline__ void transform(int log2n, const v8bf (&frag)[T][2], c
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             acc[u][r] = z[r];
-        one_tile_stages(log2n, acc[u]);
+        if constexpr (T < 4)
+            one_tile_stages(log2n, acc[u]);
     }
-    tile_pair_stages<T>(log2n, acc);
+    if constexpr (T == 4)   // blocks of 4096
+        tile_stages<12, T>(acc);
+    else
+        tile_pair_stages<T>(log2n, acc);
 }
 
 // Scales, rounds and stores a unit (WHOLE) or the part of it that exists, in order and by instructions that the compiler
@@ -114,7 +118,7 @@ constexpr int buffer_bytes(int tiles)
 }
 
 template <typename Out, int T>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 : 3)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void tb_rows_kernel(const uint16_t *__restrict__ g_a, const uint8_t *__restrict__ mask_a, int64_t elements_a,
                     uint32_t units_a, uint32_t units, int log2n, Out *__restrict__ out_a, const uint16_t *__restrict__ g_b,
                     const uint8_t *__restrict__ mask_b, int64_t elements_b, Out *__restrict__ out_b)
@@ -220,7 +224,7 @@ hipError_t launch(const BackwardArgs &a, hipStream_t stream)
 {
     int64_t units_a;
     const int64_t units = unit_count(a, T, &units_a);
-    const int64_t needed = (units + kWaves - 1) / kWaves, resident = 256 * (T == 2 ? 4 : 3);
+    const int64_t needed = (units + kWaves - 1) / kWaves, resident = 256 * 4;
     auto kernel = T == 1 ? tb_few_kernel<Out> : tb_rows_kernel<Out, T == 1 ? 2 : T>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(T == 1 || needed < resident ? needed : resident)), dim3(kThreads),
                        T == 1 ? 0 : kWaves * buffer_bytes(T), stream, static_cast<const uint16_t *>(a.g), a.mask,

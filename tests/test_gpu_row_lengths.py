@@ -82,6 +82,19 @@ def test_a_row_does_not_depend_on_the_number_of_rows(rows, cols, n, dtype, grid)
             assert np.array_equal(part[name].view(np.uint8), whole[name][rows_of_call].view(np.uint8)), (name, rows_of_call)
 
 
+# every block size has stages of its own, in whole groups of tiles and in the one that the row ends in; rows of 2048 and
+# 2816 fp32 elements change kernels between 40 and 1100 of them
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("cols,n", [(2112, 1), (3136, 4), (2112, 32), (3136, 64), (2432, 128), (2304, 256), (2560, 512),
+                                    (5120, 1024), (6144, 2048), (12288, 4096), (2048, 2048), (2816, 256)])
+def test_quantizer_block_sizes(cols, n, dtype):
+    x = synth.outlier_activations(1100, cols, 0.01, 20.0, seed=n, dtype=dtype)
+    whole, few = (gpu_quantize(x[:rows], n, 4, want_xh=False) for rows in (1100, 40))
+    compare_quantizer(whole, qo.hadamard_quantize(x, n, 4), cols, 4)
+    for name in ("codes", "scales", "mask"):
+        assert np.array_equal(few[name].view(np.uint8), whole[name][:40].view(np.uint8)), name
+
+
 def test_quantizer_strided_rows_and_no_mask():
     """A row pitch above the row length; the codes do not depend on whether the mask is asked for."""
     x = synth.outlier_activations(270, 2560, 0.01, 20.0, seed=1, dtype="bf16")
