@@ -57,8 +57,8 @@ MIB = 1 << 20
 MEASURED_TRAFFIC_MIB = {
     "quantize_xw": (86.1, 27.2),
     "lowbit_gemm": (125.9, 176.0),
-    "grad_gemm_x": (555.5, 102.8),
-    "grad_gemm_w": (862.4, 86.0),
+    "grad_gemm_x": (534.6, 86.0),
+    "grad_gemm_w": (860.9, 86.0),
     "trust_backward_xw": (91.5, 86.0),
 }
 
