@@ -1,6 +1,7 @@
 """The binding's two ways to an entry point, native code and ctypes, pass it the same arguments; what is not a plain call
 takes the second.  (No GPU: the entry points are stand-ins that record what they are given.)"""
 import ctypes
+import gc
 import inspect
 import types
 
@@ -68,7 +69,8 @@ def record(monkeypatch):
     from paper_2502_05003_amd import quest_python
     native = quest_python.Calls(*(ctypes.cast(f, ctypes.c_void_p).value for f in keep.values()))
     refuses = types.SimpleNamespace(**{name: lambda *args: None for name in dir(native) if not name.startswith("_")})
-    record = types.SimpleNamespace(seen=seen, status=0, native=native, refuses=refuses)
+    # (keep: `native` holds addresses only, the stand-ins have to outlive what a test takes out of the library)
+    record = types.SimpleNamespace(seen=seen, status=0, native=native, refuses=refuses, keep=keep)
     library = types.SimpleNamespace(calls=native, quest_status_string=real.quest_status_string, **keep)
     record.library = library
     monkeypatch.setattr(q, "_lib", library)
@@ -95,6 +97,7 @@ def test_plain_calls_are_native_ones(record):
     """Nothing of the general way is reached."""
     for name in q._NATIVE:
         setattr(record.library, name, None)
+    gc.collect()
     for name, args, kwargs in calls(tensors()):
         getattr(q, name)(*args, **kwargs)
     assert record.seen
