@@ -242,11 +242,12 @@ __device__ __forceinline__ void store_word_counted(void *uniform_base, uint32_t 
 }
 
 // 16 bytes per lane, as an instruction whose place among the vector-memory operations is the program's (what else is in
-// memory does not matter to it: no clobber, LDS accesses may move across)
+// memory does not matter to it: no clobber, LDS accesses may move across).  Two wait states have to lie between a store of
+// more than 8 bytes and a vector instruction that overwrites its data; behind its own stores the compiler puts them.
 typedef uint32_t quest_v4u __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_16_counted(void *uniform_base, uint32_t lane_offset, quest_v4u v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, %2" : : "v"(lane_offset), "v"(v), "s"(uniform_base));
+    asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" : : "v"(lane_offset), "v"(v), "s"(uniform_base));
 }
 
 // 16 bytes per lane from global memory straight into LDS (lane l lands at lds_base + 16 l), streaming
