@@ -7,12 +7,14 @@ eager fallback: a missing library raises.
 
 The calls of the path are marshalled in native code (csrc/python_calls.cpp); a method of `load().calls` returns
 the call's status, or None for arguments that are not plain tensors and numbers, with nothing called: those take the ctypes
-way, which converts what can be converted and raises for the rest.
+way, which converts what can be converted and raises for the rest.  So does every call where the native module is missing
+or was built for another torch.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -92,10 +94,35 @@ def load():
         lib.quest_container_bits.restype = _i32
         lib.quest_status_string.argtypes = [ctypes.c_int]
         lib.quest_status_string.restype = ctypes.c_char_p
-        from . import quest_python
-        lib.calls = quest_python.Calls(*(ctypes.cast(getattr(lib, name), _p).value for name in _NATIVE))
+        lib.calls = _native_calls(lib)
         _lib = lib
     return _lib
+
+
+def torch_build() -> str:
+    """What quest_python is compiled against and has to be loaded with: it reads tensors through torch's C++ headers."""
+    return f"{torch.__version__} {torch.version.git_version}"
+
+
+class _NoCalls:
+    """In place of quest_python.Calls: every call takes the ctypes way."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_calls(lib):
+    try:
+        from . import quest_python
+        built_for = getattr(quest_python, "TORCH_BUILD", "an unknown torch")
+        if built_for == torch_build():
+            return quest_python.Calls(*(ctypes.cast(getattr(lib, name), _p).value for name in _NATIVE))
+        why = f"it was built for {built_for}, this is {torch_build()}"
+    except ImportError as error:
+        why = str(error)
+    warnings.warn(f"the native module quest_python is not used, calls take 3 us more ({why}); to build it: "
+                  "`python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=3)
+    return _NoCalls()
 
 
 def _dtype_code(t: torch.Tensor) -> int:

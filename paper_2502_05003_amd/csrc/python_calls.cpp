@@ -409,6 +409,10 @@ PyMODINIT_FUNC PyInit_quest_python(void)
     PyObject *m = PyModule_Create(&module);
     if (!m)
         return nullptr;
+    if (PyModule_AddStringConstant(m, "TORCH_BUILD", QUEST_TORCH_BUILD) < 0) {   // binding.py compares it
+        Py_DECREF(m);
+        return nullptr;
+    }
     Py_INCREF(&calls_type);
     if (PyModule_AddObject(m, "Calls", reinterpret_cast<PyObject *>(&calls_type)) < 0) {
         Py_DECREF(&calls_type);

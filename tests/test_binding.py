@@ -3,13 +3,17 @@ takes the second.  (No GPU: the entry points are stand-ins that record what they
 import ctypes
 import gc
 import inspect
+import sys
+import sysconfig
 import types
 
 import numpy as np
 import pytest
 import torch
 
+import paper_2502_05003_amd as package
 from paper_2502_05003_amd import binding as q
+from paper_2502_05003_amd import build
 
 
 class Subclass(torch.Tensor):
@@ -153,6 +157,41 @@ def test_a_stream_that_cannot_be_asked_for_raises(record, monkeypatch):
     with pytest.raises(RuntimeError, match="no device"):
         q.quest_hadamard_quantize(t.x, 64, 4, codes=t.codes, scales=t.scales)
     assert not record.seen
+
+
+@pytest.mark.parametrize("module", [None, types.SimpleNamespace(Calls=None),
+                                    types.SimpleNamespace(Calls=None, TORCH_BUILD="2.0.0 0123abc")])
+def test_without_a_native_module_that_fits_calls_take_the_general_way(module, record, monkeypatch):
+    """None at all, one that does not say what it was built for, and one for another torch."""
+    if module is None:
+        monkeypatch.delattr(package, "quest_python", raising=False)
+    else:
+        monkeypatch.setattr(package, "quest_python", module, raising=False)
+    monkeypatch.setitem(sys.modules, package.__name__ + ".quest_python", module)
+    monkeypatch.setattr(q, "_lib", None)
+    with pytest.warns(RuntimeWarning, match="g.build()"):
+        assert q.quest_alpha_star(4) > 2
+    record.library.calls = q.load().calls
+    monkeypatch.setattr(q, "_lib", record.library)
+    for name, args, kwargs in calls(tensors()):
+        getattr(q, name)(*args, **kwargs)
+        assert record.seen[-1][0] == name
+
+
+def test_the_native_module_says_what_it_was_built_for():
+    from paper_2502_05003_amd import quest_python
+    assert quest_python.__file__ == build.PYTHON_LIB and build.PYTHON_LIB.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert quest_python.TORCH_BUILD == q.torch_build() and torch.__version__ in q.torch_build()
+
+
+@pytest.mark.parametrize("compiler", ["false", "/nowhere/g++"])
+def test_a_build_without_a_host_compiler_goes_on_without_the_native_module(compiler, tmp_path, monkeypatch, capsys):
+    old = tmp_path / "quest_python.so"
+    old.write_bytes(b"of another build")
+    monkeypatch.setattr(build, "PYTHON_LIB", str(old))
+    monkeypatch.setenv("CXX", compiler)
+    assert not build.build_python_calls() and not old.exists()
+    assert "was not built" in capsys.readouterr().out
 
 
 def test_signatures():
