@@ -194,6 +194,47 @@ def test_a_build_without_a_host_compiler_goes_on_without_the_native_module(compi
     assert "was not built" in capsys.readouterr().out
 
 
+# positional parameters; keyword-only ones; "name=value": with a default
+SIGNATURES = {
+    "quest_hadamard_quantize": ("x had_block bits alpha=0.0 outer_trust=-1.0", "codes scales mask=None xh_out=None"),
+    "quest_hadamard_quantize_pair": ("x w had_block bits alpha=0.0 outer_trust=-1.0",
+                                     "x_codes x_scales w_codes w_scales x_mask=None w_mask=None"),
+    "quest_hadamard_quantize_absmax": ("x had_block bits", "codes scales mask=None xh_out=None"),
+    "quest_hadamard_quantize_fp4": ("x had_block alpha=0.0", "codes scales mask=None xh_out=None"),
+    "quest_hadamard_quantize_fp4_pair": ("x w had_block alpha=0.0",
+                                         "x_codes x_scales w_codes w_scales x_mask=None w_mask=None"),
+    "quest_lowbit_gemm": ("a_codes a_scales b_codes b_scales K bits", "y acc_out=None workspace=None"),
+    "quest_lowbit_gemm_static": ("a_codes a_scales b_codes b_scales K bits", "y acc_out=None"),
+    "quest_lowbit_gemm_fp4": ("a_codes a_scales b_codes b_scales K", "y acc_out=None"),
+    "quest_trust_backward": ("g mask had_block", "out"),
+    "quest_trust_backward_pair": ("g_x mask_x g_w mask_w had_block", "out_x out_w"),
+    "quest_grad_gemm": ("which dy q_codes q_scales bits M N K", "out workspace=None"),
+    "quest_grad_gemm_fp4": ("which dy q_codes q_scales M N K", "out workspace=None"),
+    "quest_weight_only_gemm": ("x w_codes w_scales bits", "y workspace=None"),
+}
+
+
 def test_signatures():
-    """Names and defaults that callers use."""
-    assert str(inspect.signature(q.quest_grad_gemm)).startswith("(which: 'int', dy: 'torch.Tensor', q_codes: 'torch.Tensor'")
+    """Names, kinds and defaults that callers use, of every call of the path."""
+    assert set(q._NATIVE) < set(SIGNATURES)
+    for name, expected in SIGNATURES.items():
+        kinds = {inspect.Parameter.POSITIONAL_OR_KEYWORD: [], inspect.Parameter.KEYWORD_ONLY: []}
+        for p in inspect.signature(getattr(q, name)).parameters.values():
+            kinds[p.kind].append(p.name if p.default is p.empty else f"{p.name}={p.default}")
+        assert tuple(" ".join(names) for names in kinds.values()) == expected, name
+
+
+def test_defaults_that_reach_the_library(record):
+    """alpha 0: the built-in clip; outer trust -1: the paper's mask."""
+    t = tensors()
+    pair = dict(x_codes=t.codes, x_scales=t.scales, w_codes=t.w_codes, w_scales=t.w_scales)
+    for library_calls in (record.native, record.refuses):
+        record.library.calls = library_calls
+        q.quest_hadamard_quantize(t.x, 64, 4, codes=t.codes, scales=t.scales)
+        assert record.seen[-1][1][7:9] == (0.0, -1.0)
+        q.quest_hadamard_quantize_pair(t.x, t.w, 64, 4, **pair)
+        assert record.seen[-1][1][16:18] == (0.0, -1.0)
+        q.quest_hadamard_quantize_fp4(t.x, 64, codes=t.codes, scales=t.scales)
+        assert record.seen[-1][1][6] == 0.0
+        q.quest_hadamard_quantize_fp4_pair(t.x, t.w, 64, **pair)
+        assert record.seen[-1][1][15] == 0.0
