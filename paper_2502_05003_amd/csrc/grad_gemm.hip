@@ -777,8 +777,11 @@ template <int MODE, int TI>
 hipError_t launch_tiles(const GradGemmPlan &p, const uint16_t *left, const uint16_t *qhat, int64_t ld_right, uint16_t *out,
                         float4 *partial, hipStream_t stream)
 {
-    const bool ring = !p.split && p.per_block > p.steps;
-    auto kernel = ring ? grad_gemm_tile_kernel<MODE, TI, true> : grad_gemm_tile_kernel<MODE, TI, false>;
+    auto kernel = grad_gemm_tile_kernel<MODE, TI, false>;
+    if constexpr (TI > 1) {   // (tiles of 64 rows are taken where one each is plenty)
+        if (!p.split && p.per_block > p.steps)
+            kernel = grad_gemm_tile_kernel<MODE, TI, true>;
+    }
     hipLaunchKernelGGL(kernel, dim3((unsigned)p.blocks), dim3(kGemmThreads), TileSizes<TI>::kLds,
                        stream, left, p.ld_left, qhat, ld_right, (int)p.contraction, (int)p.out_rows, (int)p.out_cols,
                        p.tiles_r, p.tiles_k, p.per_block, p.phase_period, out, partial);
@@ -798,11 +801,13 @@ hipError_t launch_mode(const GradGemmPlan &p, const uint16_t *left, const uint16
 template <int MODE, int TI>
 hipError_t prepare_tiles()
 {
-    const hipError_t err =
+    hipError_t err =
         allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, TI, false>), TileSizes<TI>::kLds);
-    return err != hipSuccess ? err
-                             : allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, TI, true>),
-                                                 TileSizes<TI>::kLds);
+    if constexpr (TI > 1) {
+        if (err == hipSuccess)
+            err = allow_dynamic_lds(reinterpret_cast<const void *>(grad_gemm_tile_kernel<MODE, TI, true>), TileSizes<TI>::kLds);
+    }
+    return err;
 }
 
 template <int MODE>

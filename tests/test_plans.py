@@ -1,5 +1,8 @@
 """The GPU tests' cases against the dispatch rules, on the CPU: each kernel and block shape of the products that a
 rule can choose is run by a case that is listed for it.  A change of a rule that takes a case elsewhere fails here."""
+import math
+import random
+
 import pytest
 
 import plan
@@ -22,6 +25,19 @@ def test_tile_cases_have_every_height_in_every_form():
     assert heights == {(form, plan.TILES, rows) for form in (0, 1, 2) for rows in (64, 128, 192, 256)} | \
         {(form, plan.SPLIT, 256) for form in (0, 1, 2)}
     assert {(case[0], case[1]) for case in tiles.RUNS if case[-1] == "fp4"} == {k[1:] for k in heights}
+
+
+def test_tiles_of_64_rows_are_one_to_a_workgroup():
+    """There is no form of theirs that runs on from tile to tile: sizes of every magnitude, every form and grid."""
+    rng = random.Random(1)
+    size = lambda: 64 * round(math.exp(rng.uniform(0, math.log(rng.choice((256, 1024, 65536))))))
+    found = set()
+    for _ in range(30000):
+        form = rng.choice((0, 1, 2))
+        p = plan.grad_gemm(form, size(), size(), size(), bits=rng.choice((1, 2, 3, 4) if form == 2 else (0, 1, 2, 3, 4)))
+        if p.kernel == plan.TILES:
+            found.add((p.rows, p.count > 1))
+    assert found == {(64, False)} | {(rows, several) for rows in (128, 192, 256) for several in (False, True)}
 
 
 def test_mid_cases_have_every_block_in_every_form_and_grid():
