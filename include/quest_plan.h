@@ -34,6 +34,13 @@ typedef struct {
  * compute units */
 quest_plan quest_plan_grad_gemm(int32_t form, int32_t bits, int64_t M, int64_t N, int64_t K, int32_t cus);
 
+/* Of a launch with several whole tiles per workgroup: from how many tiles its ring of stages runs on to the workgroup's next
+ * one, after how many it begins anew (the next one ends at another edge of the output), and workgroups that do both */
+typedef struct {
+    int32_t on, anew, mixed;
+} quest_plan_ring;
+quest_plan_ring quest_plan_grad_gemm_ring(int32_t form, int32_t bits, int64_t M, int64_t N, int64_t K, int32_t cus);
+
 /* quest_lowbit_gemm (bits 1 .. 4; with_workspace: scratch given) and quest_lowbit_gemm_fp4 (bits = 0) */
 quest_plan quest_plan_forward(int32_t bits, int64_t M, int64_t N, int64_t K, int32_t with_workspace);
 

@@ -171,8 +171,8 @@ __global__ __launch_bounds__(256) void expand_fp4_codes_kernel(const uint8_t *__
 // that they share the fetch through that XCD's L2.  phase_period = 0: whole tiles, all in phase.
 constexpr int kSlotQuads = 4 * 64 * 64;   // float4 per partial tile (256 KiB)
 
-__device__ __forceinline__ void tile_origin(int tile, int tile_rows, int tiles_r, int tiles_k, int phase_period, int &r0,
-                                            int &k0)
+__host__ __device__ __forceinline__ void tile_origin(int tile, int tile_rows, int tiles_r, int tiles_k, int phase_period,
+                                                     int &r0, int &k0)
 {
     if (phase_period != 0) {   // split tiles: plain order along the longer side of the tile grid
         if (tiles_k > tiles_r) {
@@ -186,10 +186,17 @@ __device__ __forceinline__ void tile_origin(int tile, int tile_rows, int tiles_r
     }
     // four tile-rows deep, column by column: neighbours in the order share operand rows in L2
     const int band = tile / (4 * tiles_k);
-    const int band_rows = min(4, tiles_r - band * 4);
+    const int band_rows = tiles_r - band * 4 < 4 ? tiles_r - band * 4 : 4;
     const int in_band = tile - band * 4 * tiles_k;
     r0 = (band * 4 + in_band % band_rows) * tile_rows;
     k0 = (in_band / band_rows) * GT;
+}
+
+// Whether two tiles of an R x K output are of one size: neither or both end at the same edge
+__host__ __device__ __forceinline__ bool same_tile_size(int r0, int k0, int next_r0, int next_k0, int R, int K, int tile_rows)
+{
+    auto rest = [](int left, int whole) { return left < whole ? left : whole; };
+    return rest(R - next_r0, tile_rows) == rest(R - r0, tile_rows) && rest(K - next_k0, GT) == rest(K - k0, GT);
 }
 
 /*
@@ -440,14 +447,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grad_gemm_tile_kernel(
         cur_off = 0;
         static_for<kReads>([&](auto nc) { load_frag(nc, smem, std::integral_constant<int, 0>{}); });
     }
-    // The ring runs on from tile to tile where the next one's transfers differ in their base addresses alone (neither or
-    // both end at the same edge of the output).  Else, and after the last tile, the look-ahead fetches the last step again.
+    // The ring runs on from tile to tile where the next one's transfers differ in their base addresses alone.
+    // Else, and after the last tile, the look-ahead fetches the last step again.  (With 256 compute units no plan comes near
+    // the fewest steps: such contractions go to the kernels of grad_gemm_mid.hip.)
     int next_r0 = 0, next_k0 = 0;
     bool carry = false;
     if (units_left > 0) {
         origin(tile + 1, next_r0, next_k0);
-        carry = RING && s_end - s_begin >= 2 * kAhead && min(R - next_r0, Sizes::kRows) == min(R - r0, Sizes::kRows) &&
-                min(K - next_k0, GT) == min(K - k0, GT);
+        carry = RING && s_end - s_begin >= 2 * kAhead && same_tile_size(r0, k0, next_r0, next_k0, R, K, Sizes::kRows);
     }
 
     // Scalar bookkeeping of a step is kept to additions and selects (one wave per SIMD: a chain of
@@ -894,4 +901,25 @@ quest_plan quest_plan_grad_gemm(int32_t form, int32_t bits, int64_t M, int64_t N
     if (p.mid)
         return quest::grad_gemm_mid_plan(bits, p.contraction, p.out_rows, p.out_cols, cus);
     return {p.split ? QUEST_PLAN_SPLIT : QUEST_PLAN_TILES, 64 * p.ti, quest::GT, p.split ? 1 : p.per_block / p.steps};
+}
+
+quest_plan_ring quest_plan_grad_gemm_ring(int32_t form, int32_t bits, int64_t M, int64_t N, int64_t K, int32_t cus)
+{
+    const quest::GradGemmPlan p = quest::plan_grad_gemm(form, bits, M, N, K, cus);
+    quest_plan_ring ring = {0, 0, 0};
+    if (!p.covered || p.mid || p.split || p.ti == 1)
+        return ring;
+    const int tile_rows = 64 * p.ti, tiles = p.tiles_r * p.tiles_k, each = p.per_block / p.steps;
+    for (int first = 0; first < tiles; first += each) {
+        int on = 0, anew = 0, r0, k0, next_r0, next_k0;
+        for (int tile = first; tile + 1 < std::min(first + each, tiles); ++tile) {
+            quest::tile_origin(tile, tile_rows, p.tiles_r, p.tiles_k, 0, r0, k0);
+            quest::tile_origin(tile + 1, tile_rows, p.tiles_r, p.tiles_k, 0, next_r0, next_k0);
+            ++(quest::same_tile_size(r0, k0, next_r0, next_k0, (int)p.out_rows, (int)p.out_cols, tile_rows) ? on : anew);
+        }
+        ring.on += on;
+        ring.anew += anew;
+        ring.mixed += on > 0 && anew > 0;
+    }
+    return ring;
 }

@@ -14,11 +14,18 @@ class _Plan(ctypes.Structure):
     _fields_ = [(name, ctypes.c_int32) for name in ("kernel", "block_rows", "block_cols", "count")]
 
 
-def _ask(name, *args):
+Ring = namedtuple("Ring", "on anew mixed")
+
+
+class _Ring(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int32) for name in Ring._fields]
+
+
+def _ask(name, *args, result=_Plan):
     function = getattr(q.load(), name)
-    function.restype = _Plan
+    function.restype = result
     p = function(*args)
-    return Plan(p.kernel, p.block_rows, p.block_cols, p.count)
+    return (Plan if result is _Plan else Ring)(*(getattr(p, field) for field, _ in result._fields_))
 
 
 def _i64(*values):
@@ -28,6 +35,10 @@ def _i64(*values):
 def grad_gemm(form, M, N, K, bits=4):
     """bits = 0: E2M1 codes"""
     return _ask("quest_plan_grad_gemm", form, bits, *_i64(M, N, K), CUS)
+
+
+def ring(form, M, N, K, bits=4):
+    return _ask("quest_plan_grad_gemm_ring", form, bits, *_i64(M, N, K), CUS, result=_Ring)
 
 
 def forward(M, N, K, bits, workspace=True):

@@ -20,6 +20,20 @@ def test_tile_cases_are_where_they_are_listed(kernel, rows, several, form, C, R,
     assert (p.kernel, p.rows, p.count > 1) == (kernel, rows, several)
 
 
+@pytest.mark.parametrize("rows,form,C,R,cols,ends", tiles.RINGS)
+def test_ring_cases_do_what_they_are_listed_for(rows, form, C, R, cols, ends):
+    p, ring = plan.grad_gemm(form, *tiles.layer(form, C, R, cols)), plan.ring(form, *tiles.layer(form, C, R, cols))
+    assert (p.kernel, p.rows) == (plan.TILES, rows) and p.count >= (2 if rows == 128 else 3)
+    assert ring.on > 0 and (ring.anew, ring.mixed) == (0, 0) if ends == "on" else ring.mixed > 0
+
+
+def test_tile_cases_with_several_have_workgroups_that_begin_anew():
+    """(two tiles each: in one workgroup the ring either runs on or begins anew)"""
+    for kernel, rows, several, form, C, R, cols, grid in tiles.RUNS:
+        ring = plan.ring(form, *tiles.layer(form, C, R, cols), bits=0 if grid == "fp4" else grid)
+        assert (ring.on > 0) == several and ring.mixed == 0
+
+
 def test_tile_cases_have_every_height_in_every_form():
     heights = {(case[3], case[0], case[1]) for case in tiles.RUNS if case[-1] != "fp4"}
     assert heights == {(form, plan.TILES, rows) for form in (0, 1, 2) for rows in (64, 128, 192, 256)} | \
