@@ -175,6 +175,24 @@ def test_inverse_transform_of_a_row_does_not_depend_on_the_others(rows, cols, n,
     assert torch.isfinite(whole[clean].float()).all()
 
 
+# more units than the 4096 resident waves: of the second on, the stores of the one before are on their way while it is awaited
+@pytest.mark.parametrize("od", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("masked", [True, False])
+@pytest.mark.parametrize("rows,cols,n", [(8201, 2560, 512), (140001, 64, 64), (4100, 6144, 2048), (4201, 12288, 4096)])
+def test_inverse_transform_where_waves_have_several_units(rows, cols, n, masked, od):
+    """The same bits as from calls in which no wave has more than one."""
+    g = torch.randn(rows, cols, device=DEV).bfloat16()
+    mask = torch.randint(0, 256, (rows, cols // 8), dtype=torch.uint8, device=DEV)
+    whole = torch.full((rows, cols), 7.0, dtype=od, device=DEV)
+    q.quest_trust_backward(g, mask if masked else None, n, out=whole)
+    part_rows = (2 << 20) // cols // 2 * 2   # (an even number: 16 bytes of mask bits)
+    for at in range(0, rows, part_rows):
+        part = slice(at, min(at + part_rows, rows))
+        out = torch.full((part.stop - at, cols), 7.0, dtype=od, device=DEV)
+        q.quest_trust_backward(g[part], mask[part] if masked else None, n, out=out)
+        assert torch.equal(out, whole[part]), at
+
+
 # rows of three groups of tiles and more, which a workgroup shares up to 128 rows: 5632 and 4608 through LDS, 11008 not
 @pytest.mark.parametrize("cols,n,grid", [(5632, 512, 4), (5632, 32, 4), (5632, 512, 1), (5632, 512, 2), (5632, 512, 3), (5632, 512, 8),
                                          (5632, 512, "fp4"), (4608, 512, 4), (11008, 256, 4), (11008, 1, 4)])
