@@ -234,10 +234,10 @@ __device__ __forceinline__ int column_swz(int crow)
  * RING: for workgroups that work through several whole tiles.  A tile's two ends, a prologue that waits for its first
  * transfers and an epilogue whose stores all workgroups issue at once, took 10 to 13 us with nothing to multiply meanwhile; with
  * RING the next tile's first steps are requested during the last ones of a tile, and its stores are waited for only when
- * the counter of vector-memory operations cannot tell them from transfers any more, three or four steps into the next
- * tile (us per call, alone, before / now: G_x 16384 x 5632 x 2048, 2 tiles of 256 rows each, 310 / 296, 16384 x 2048 x 5632, 8 of 192
- * rows, 354 / 337, 16384 x 1024 x 4096 162 / 136; weight-only 16384 x 4096 x 1024 161 / 132).  Workgroups with a single tile run the
- * loop without the two instructions per step that this costs.
+ * the counter of vector-memory operations cannot tell them from transfers any more, in the next tile's third to fifth step
+ * (kAhead of them are in flight) (us per call, alone, before / now: G_x 16384 x 5632 x 2048, 2 tiles of 256 rows each, 310 / 296,
+ * 16384 x 2048 x 5632, 8 of 192 rows, 354 / 337, 16384 x 1024 x 4096 162 / 136; weight-only 16384 x 4096 x 1024 161 / 132).
+ * Workgroups with a single tile run the loop without the two instructions per step that this costs.
  */
 constexpr int kSpreadModes = 5;   // bit m: MODE m spreads its transfers over the whole step (measured, see below)
 
@@ -705,8 +705,11 @@ GradGemmPlan plan_grad_gemm(int which, int grid, int64_t M, int64_t N, int64_t K
     // power-limited: the more of them, the slower each), and what a tile's two ends take.  The weight-only
     // form reads half lines of both operands, which the smaller tiles feel, and tiles of 64 and 128 rows in many
     // rounds share fewer fetches of the right operand.  Fitted to 260 products of 128 .. 16384 tokens, each
-    // timed alone in every way there is, and checked on 260 others: the way chosen takes 1.4 % more than the best in
-    // the mean, 18 % at most.  Inside a training step a product takes up to 15 % more than alone, 360 tiles of
+    // timed alone in every way there is, before workgroups' rings ran on from tile to tile, and checked since on 520
+    // others: the way chosen takes 1.5 % more than the best in the mean, 18 % at most but for five (21 to 35 %).  Every tile's two ends
+    // are priced in full, also where RING hides them, which makes several tiles of 256 rows look dearer than they are: G_x 16384 x
+    // 2048 x 5632 takes 350 us in the tiles of 192 rows that are chosen and 337 in tiles of 256, 8192 x 1280 x 11008 251 and 229.
+    // Inside a training step a product takes up to 15 % more than alone, 360 tiles of
     // 192 rows in two rounds (G_w 4096 x 6912 x 2560) 25 %.
     constexpr double kStepUs[5] = {0.0, 0.212, 0.265, 0.318, 0.488}, kBusyUs[5] = {0.0, 0.085, 0.17, 0.307, 0.339};
     constexpr double kEndsUs[5] = {0.0, 5.0, 7.0, 9.5, 13.5};

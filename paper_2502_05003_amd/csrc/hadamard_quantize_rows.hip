@@ -12,9 +12,9 @@
 //
 // Measured against the general kernel (b = 4, us): bf16 8192 x 2560 48.7 -> 15.6, 8192 x 5120 94 -> 29.7,
 // 333 x 2560 7.2 -> 5.1; fp32 8192 x 2560 48.9 -> 26.7.  What bounds it is the vector unit: of 11008 x 2560, b = 4 with its
-// mask, 24.6 us for 1045 vector instructions per row.  Hence straight code where the row fills a group of tiles (no test
-// for its end, no zeroing of what is not there) and for each block size (see one_tile_stages): 20.8 us, and 8192 elements
-// in blocks of 4096, 4096 rows, 32.1 -> 23.1.
+// mask, 25.9 us for 1045 vector instructions per row.  Hence straight code where the row fills a group of tiles (no test
+// for its end, no zeroing of what is not there) and for each block size (see one_tile_stages): 21.9 us in the same run (22.7 and
+// 20.8 in another), and 8192 elements in blocks of 4096, 4096 rows, 33.1 -> 23.0.
 #include "hadamard_tile.h"
 #include "quest_internal.h"
 #include "row_staging.h"

@@ -273,12 +273,13 @@ hipError_t prepare_trust_backward_mfma_kernels()
 // Hadamard block of at most 32, or 128, 512, 1024, 2048, 4096 where it divides the row, and for rows of 640, 768
 // and 1280 with a block of at most 32 or their widest one; fp32 out (a weight gradient for an fp32
 // optimizer) for all of these row lengths with their widest block.  Everything else is better off in the kernel that
-// cuts the gradient without regard to its rows (trust_backward_rows.hip), and so are the rows that are not whole pieces
-// of 2048 elements once there are enough of them (us, here / there: 4882 x 512 3.9 / 4.5, 6835 x 512
+// cuts the gradient without regard to its rows (trust_backward_rows.hip), and so are the rows that are not whole tiles
+// of 1024 elements once there are enough of them (us, here / there: 4882 x 512 3.9 / 4.5, 6835 x 512
 // 5.0 / 4.9, 15625 x 512 8.5 / 6.8; 3906 x 640 4.1 / 4.5, 7812 x 640 6.0 / 5.3; 1953 x 1280 4.4 / 4.5, 3906 x 1280
 // 6.2 / 5.4; of rows with an instantiation before: 2048 x 1792 5.3 / 4.9, 16384 x 2816 35.9 / 33.3; whole
-// pieces with the block size known to the compiler, 22016 x 2048 32.3 / 33.9, 2048 x 4096 7.1 / 8.1).  Both make the
-// same bits: the same sums in the same order.
+// tiles with the block size known to the compiler, 22016 x 2048 32.3 / 33.9, 2048 x 4096 7.1 / 8.1; of rows of 1024 neither
+// is the better one throughout, 2048 x 1024 4.35 / 4.48, 8192 x 1024 8.3 / 7.3, 16384 x 1024 13.7 / 14.4, 65536 x 1024 48.9 / 47.7,
+// to fp32 8192 x 1024 10.5 / 9.0, 65536 x 1024 71 / 76).  Both make the same bits: the same sums in the same order.
 bool launch_trust_backward_mfma(const BackwardArgs &a, hipStream_t stream)
 {
     if (a.g_dtype != QUEST_BF16 || (a.cols % 128) != 0)

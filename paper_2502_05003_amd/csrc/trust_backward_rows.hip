@@ -9,7 +9,9 @@
 //
 // Data flow of a unit as in that file: a wave brings it into its own LDS buffer by global -> LDS transfers, one
 // unit ahead of the one that it transforms; the stores are issued by hand and counted, and the wait for a unit is for "all
-// but that many".  Bound by the memory (4.1 bytes per element).  Cut at rows instead, in units of the one tile that a block
+// but that many", or but 24 where a unit has 32 or 64 (fp32 outputs, blocks of 4096), whose oldest stores have long gone
+// (us, so / all but 32 or 63: fp32 11008 x 2560 32.0 / 32.0, blocks of 4096 8192 x 12288 72.9 / 72.7, to fp32 111.8 /
+// 112.5).  Bound by the memory (4.1 bytes per element).  Cut at rows instead, in units of the one tile that a block
 // spans, loaded into registers (us, so / now): 18432 x 5632 81.7 -> 71.9 = 6.0 TB/s, 11008 x 2560 23.7 -> 21.9,
 // 2000 x 3584 8.3 -> 6.4, 8192 x 6144 block 2048 40.5 -> 35.9, 1000 x 12288 block 4096 12.0 -> 9.8.
 #include "gemm_tile.h"
@@ -256,7 +258,10 @@ hipError_t prepare_trust_backward_rows_kernels()
 
 // Not blocks of 8 or less, which the general kernel has in registers straight from its loads and never exchanges (us, here /
 // there: block 8, 8192 x 3392 23.3 / 20.1, 8192 x 1280 to fp32 14.0 / 11.9, 300 x 448 3.2 / 2.6; 8192 x 448 6.4 / 7.3; block 16,
-// 8192 x 3392 23.3 / 33.6, 300 x 448 3.2 / 3.0).
+// 8192 x 3392 23.3 / 33.6, 300 x 448 3.2 / 3.0).  Nor rows of 1664, 1792 and 2816 in such blocks, for which there was an
+// instantiation of the other matrix-core kernel (that / the general one, block 8: 333 x 1792 4.0 / 3.3, 1000 x 2816 5.5 / 5.0,
+// 8192 x 1792 13.5 / 12.8, 8192 x 2816 20.1 / 20.8, 16384 x 1792 24.4 / 25.5, 16384 x 2816 37.5 / 38.8; block 1 16384 x
+// 1792 24.4 / 25.0): the number of rows may not decide, as the two add in different orders in blocks of 4 and 8.
 bool trust_backward_rows_covers(const BackwardArgs &a)
 {
     return a.g_dtype == QUEST_BF16 && a.cols % 64 == 0 && a.log2n >= 4 && a.log2n <= 12;
