@@ -44,6 +44,12 @@ quest_plan_ring quest_plan_grad_gemm_ring(int32_t form, int32_t bits, int64_t M,
 /* quest_lowbit_gemm (bits 1 .. 4; with_workspace: scratch given) and quest_lowbit_gemm_fp4 (bits = 0) */
 quest_plan quest_plan_forward(int32_t bits, int64_t M, int64_t N, int64_t K, int32_t with_workspace);
 
+/* The block of a product that FEW takes: of the output, units of 128 contraction elements that a wave has in flight, waves */
+typedef struct {
+    int32_t block_rows, block_cols, in_flight, waves;
+} quest_plan_few;
+quest_plan_few quest_plan_forward_few(int32_t bits, int64_t M, int64_t N, int64_t K);
+
 /* quest_hadamard_quantize (mode 0), _absmax (1) and _fp4 (2); rows: of both operands; f32: fp32 rows */
 quest_plan quest_plan_quantize(int32_t mode, int32_t f32, int64_t rows, int64_t cols, int32_t had_block, int32_t bits);
 

@@ -108,7 +108,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void skinny_gemm_kernel(
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
-    constexpr int waves = WAVES;
+    // The largest block's loop over one-bit codes wants its step unknown: as a constant the compiler carries the codes that are
+    // fetched ahead through seven moves per 32 matrix instructions (us: 988 x 2816 x 10816 57.4, so 47.4; 3637 x 768 x 5568 32.1, 27.4).
+    // With two bits it is better either way, by up to 5 % unknown where a compute unit has two of the blocks at most, by up to
+    // 14 % known where it has more; with the others it makes no difference.
+    int waves = WAVES;
+    if constexpr (MT * NT == 16 && GRID == 1)
+        asm("" : "+s"(waves));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row16 = lane & 15, quarter = lane >> 4;
     const int n0 = blockIdx.x * 16 * NT, m0 = blockIdx.y * 16 * MT;
@@ -220,7 +226,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void skinny_gemm_kernel(
     for (int t = tid; t < MT * NT * 64; t += 64 * WAVES) {
         Acc sum = park[t];
 #pragma unroll
-        for (int v = 1; v < waves; ++v)
+        for (int v = 1; v < WAVES; ++v)
             sum += park[v * (MT * NT * 64) + t];
         const int tile = t >> 6, l = t & 63;
         const int m = m0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
@@ -278,30 +284,68 @@ int64_t block_count(int64_t M, int64_t N, int mt, int nt)
 //   4096 x 1024, 128 rows: 4x2/8 4.0, 2x2/4 4.2, 4x4/4 4.4  5632 x 2048, 128 rows: 4x4/4 7.8, 2x2/4 8.2, 4x2/8 8.4
 // With 16 rows or fewer the activations are next to nothing, and 1x1 is within 3 % of the best
 // everywhere (11008 x 4096, 8 rows: 1x1 6.9, 1x2 7.4).  Where blocks are many the largest one pays when the
-// contraction is long enough for what it saves in reads (5632 x 5632, 128 rows: 4x4/4 14.1, 4x2/8 17.6), else 4x2 with its
-// shorter summation, by eight waves as long as a unit has two of its blocks at most (2048 x 1664, 512 rows: 4x2/8
-// 5.6, 4x2/4 6.2, 4x4/4 6.3; 2 bits: 4096 x 1024, 333 rows: 4x2/4 7.1, 4x4/4 7.6, 4x2/8 7.7).
+// contraction is long enough for what it saves in reads (5632 x 5632, 128 rows: 4x4/4 14.1, 4x2/8 17.6), from 16 units
+// on (E2M1 of 14: 256 x 1792, 2346 rows 7.5, 8.5; of 13 and 15, whose rows start within lines, 4 to 20 % more); else 4x2 with
+// its shorter summation, by eight waves as long as a compute unit has two of its blocks at most (2048 x 1664, 512 rows: 4x2/8 5.6,
+// 4x2/4 6.2, 4x4/4 6.3).  Of more blocks the compute unit with most of them decides: 4x4, of which it holds two at a time, where it
+// has no more sixteens so and most places of the last round are taken (2 bits: 1664 x 1664, 972 rows, 2 x 16 and 4 x 8: 4x4/4 8.7,
+// 4x2/4 9.5; 11008 x 1664, 97 rows, 2 x 16 and 3 x 8: 8.2, 7.8), with 8 units in one round (1 bit: 1024 x 1024, 1600 rows 8.2, 9.1; 512
+// x 1024, 3000 rows, 2 x 16 and 3 x 8: 8.1, 7.8; 4 bits: 9920 x 1088, 807 rows, four rounds, 27.5, 25.8), with fewer not.  Two units of
+// a wave in flight pay where it has just two (2 bits: 4096 x 1024, 333 rows 7.66, 7.75; 1664 x 1664, 972 rows 10.8, 9.5).  At 1671
+// shapes of 33 .. 4096 rows with more than 256 blocks of 4x2 the one chosen takes 1.5 % more than the best of them in the mean.
+quest_plan_few choose_block(int64_t M, int64_t N, int64_t K, int grid)
+{
+    constexpr int64_t kUnitsOfChip = 256;
+    auto blocks = [&](int mt, int nt) { return block_count(M, N, mt, nt); };
+    auto fits = [&](int mt, int nt) { return blocks(mt, nt) <= kUnitsOfChip; };
+    auto block = [](int mt, int nt, int in_flight, int waves) { return quest_plan_few{16 * mt, 16 * nt, in_flight, waves}; };
+    const int64_t units = K / kUnit;
+    if (M <= 16 || fits(1, 1)) {
+        // two units of a wave in flight when workgroups are few and the contraction is long (2048 x 5632, 1 row: 4.2
+        // against 4.3; 24 rows, a workgroup for each compute unit, 5.1 against 4.9), by four waves for large E2M1 weights, two to four
+        // workgroups for a compute unit (11008 x 11008, 10 rows: 18.0 against 20.3; integer codes take 3 % more so)
+        if (units >= 32 && 2 * blocks(1, 1) <= kUnitsOfChip)
+            return block(1, 1, 2, 8);
+        if (grid == 0 && units >= 64 && blocks(1, 1) > 2 * kUnitsOfChip && blocks(1, 1) <= 4 * kUnitsOfChip)
+            return block(1, 1, 2, 4);
+        return block(1, 1, 1, 8);
+    }
+    if (fits(1, 2))
+        return block(1, 2, 2, 4);
+    if (M <= 32 || fits(2, 2))
+        return block(2, 2, 2, 4);
+    if (!fits(4, 2) && (units >= 16 || (grid == 0 && units == 14)))
+        return block(4, 4, 1, 4);
+    if (blocks(4, 2) <= 2 * kUnitsOfChip)
+        return block(4, 2, 1, 8);
+    auto most = [&](int mt, int nt) { return (blocks(mt, nt) + kUnitsOfChip - 1) / kUnitsOfChip; };   // of a compute unit
+    const int64_t rounds = (most(4, 4) + 1) / 2;
+    if (2 * most(4, 4) <= most(4, 2) &&
+        (units > 8 ? 2 * blocks(4, 4) >= 3 * rounds * kUnitsOfChip : units == 8 && rounds == 1))
+        return block(4, 4, 1, 4);
+    return block(4, 2, units == 8 ? 2 : 1, 4);
+}
+
 template <int GRID>
 hipError_t launch_grid(const SkinnyGemmArgs &a, hipStream_t stream)
 {
-    constexpr int64_t kUnitsOfChip = 256;
-    auto fits = [&](int mt, int nt) { return block_count(a.M, a.N, mt, nt) <= kUnitsOfChip; };
-    if (a.M <= 16 || fits(1, 1)) {
-        // two units of a wave in flight when workgroups are few and the contraction is long (2048 x 5632, 1 row: 4.2
-        // against 4.3; 24 rows, a workgroup for each compute unit, 5.1 against 4.9)
-        if (a.K >= 32 * kUnit && 2 * block_count(a.M, a.N, 1, 1) <= kUnitsOfChip)
-            return launch<GRID, 1, 1, 2, 8>(a, stream);
-        return launch<GRID, 1, 1, 1, 8>(a, stream);
+    const quest_plan_few b = choose_block(a.M, a.N, a.K, GRID);
+    if (b.block_rows == 16 && b.block_cols == 16) {
+        if constexpr (GRID == 0) {
+            if (b.waves == 4)
+                return launch<GRID, 1, 1, 2, 4>(a, stream);
+        }
+        return b.in_flight == 2 ? launch<GRID, 1, 1, 2, 8>(a, stream) : launch<GRID, 1, 1, 1, 8>(a, stream);
     }
-    if (fits(1, 2))
+    if (b.block_rows == 16)
         return launch<GRID, 1, 2, 2, 4>(a, stream);
-    if (a.M <= 32 || fits(2, 2))
+    if (b.block_rows == 32)
         return launch<GRID, 2, 2, 2, 4>(a, stream);
-    if (!fits(4, 2) && a.K >= 16 * kUnit)
+    if (b.block_cols == 64)
         return launch<GRID, 4, 4, 1, 4>(a, stream);
-    if (block_count(a.M, a.N, 4, 2) <= 2 * kUnitsOfChip)
+    if (b.waves == 8)
         return launch<GRID, 4, 2, 1, 8>(a, stream);
-    return a.K >= 8 * kUnit ? launch<GRID, 4, 2, 2, 4>(a, stream) : launch<GRID, 4, 2, 1, 4>(a, stream);
+    return b.in_flight == 2 ? launch<GRID, 4, 2, 2, 4>(a, stream) : launch<GRID, 4, 2, 1, 4>(a, stream);
 }
 
 }  // namespace
@@ -342,3 +386,8 @@ hipError_t launch_skinny_gemm(const SkinnyGemmArgs &a, hipStream_t stream)
 }
 
 }  // namespace quest
+
+quest_plan_few quest_plan_forward_few(int32_t bits, int64_t M, int64_t N, int64_t K)
+{
+    return quest::choose_block(M, N, K, bits);
+}

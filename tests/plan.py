@@ -17,15 +17,22 @@ class _Plan(ctypes.Structure):
 Ring = namedtuple("Ring", "on anew mixed")
 
 
+Few = namedtuple("Few", "rows cols in_flight waves")
+
+
 class _Ring(ctypes.Structure):
     _fields_ = [(name, ctypes.c_int32) for name in Ring._fields]
+
+
+class _Few(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int32) for name in ("block_rows", "block_cols", "in_flight", "waves")]
 
 
 def _ask(name, *args, result=_Plan):
     function = getattr(q.load(), name)
     function.restype = result
     p = function(*args)
-    return (Plan if result is _Plan else Ring)(*(getattr(p, field) for field, _ in result._fields_))
+    return {_Plan: Plan, _Ring: Ring, _Few: Few}[result](*(getattr(p, field) for field, _ in result._fields_))
 
 
 def _i64(*values):
@@ -44,6 +51,11 @@ def ring(form, M, N, K, bits=4):
 def forward(M, N, K, bits, workspace=True):
     """bits = 0: E2M1 codes"""
     return _ask("quest_plan_forward", bits, *_i64(M, N, K), int(workspace))
+
+
+def few(M, N, K, bits):
+    """The block where forward() says FEW; bits = 0: E2M1 codes"""
+    return _ask("quest_plan_forward_few", bits, *_i64(M, N, K), result=_Few)
 
 
 def quantize(rows, cols, block, bits, dtype, absmax=False, fp4=False):

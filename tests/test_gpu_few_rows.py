@@ -106,3 +106,21 @@ def test_calls_go_to_the_current_stream():
 @pytest.mark.parametrize("M,N,K", [(65, 8200, 192), (70, 8200, 1088), (66, 8200, 2112)])
 def test_integer_grids_many_blocks(M, N, K, bits):
     test_integer_grids(M, N, K, bits)
+
+
+# the other blocks of many: 4x4 of 8 and 12 units, in one round; 4x2 by eight waves, 4x4 of 14 E2M1 units
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("M,N,K", [(130, 8200, 1088), (130, 8200, 1600), (66, 6200, 1792)])
+def test_integer_grids_many_blocks_of_few_units(M, N, K, bits):
+    test_integer_grids(M, N, K, bits)
+
+
+# the other blocks that E2M1 codes can get: two sixteens square, 4x2 by four and by eight waves, 4x4 of 14 and 16 units, and one for
+# few rows of large weights
+FP4_MANY = [(33, 3000, 128), (40, 16500, 256), (40, 16500, 1024), (66, 6200, 1664), (66, 6200, 1792), (66, 8100, 2048),
+            (10, 8300, 8192)]
+
+
+@pytest.mark.parametrize("M,N,K", FP4_MANY)
+def test_fp4_grid_many_blocks(M, N, K):
+    test_fp4_grid(M, N, K)

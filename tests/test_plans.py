@@ -85,6 +85,41 @@ def test_forward_cases_reach_every_kernel():
     assert found[3] >= {few, general, (plan.TILES, 256, 128)} and found[4] >= {few, general, (plan.TILES, 256, 128)}
 
 
+# the block each of these products runs fastest with (of 16 rows and 16 columns: 1, of 64 and 32: 4x2), us there and with the
+# block in brackets
+@pytest.mark.parametrize("M,N,K,bits,rows,cols,in_flight,waves", [
+    (460, 3552, 1792, 1, 64, 64, 1, 4),       # 10.9 (4x2, two units in flight, 14.8)
+    (972, 1664, 1664, 2, 64, 64, 1, 4),       # 8.7 (so 10.8, one unit 9.5)
+    (763, 4096, 1280, 1, 64, 64, 1, 4),       # 13.6 (18.2, 16.5)
+    (3937, 422, 1600, 4, 64, 64, 1, 4),       # 12.0 (14.0, 12.9)
+    (97, 11008, 1664, 2, 64, 32, 1, 4),       # 7.7 (8.6; 4x4 8.2)
+    (333, 4096, 1024, 2, 64, 32, 2, 4),       # 7.7 (one unit 7.8, 4x4 8.1)
+    (1600, 1024, 1024, 2, 64, 64, 1, 4),      # 8.2 (9.1)
+    (573, 5225, 1088, 3, 64, 32, 2, 4),       # 14.2 (4x4 16.2)
+    (2346, 256, 1792, 0, 64, 64, 1, 4),       # 7.6 (4x2 8.5)
+    (512, 2048, 1664, 4, 64, 32, 1, 8),       # 6.3 (four waves 6.6, 4x4 7.1)
+    (512, 1664, 2048, 4, 64, 64, 1, 4),       # 8.6 (4x2 9.1)
+    (10, 11008, 11008, 0, 16, 16, 2, 4),      # 18.0 (eight waves 20.3)
+    (13, 11008, 11008, 3, 16, 16, 1, 8),      # 20.0
+    (1, 2048, 5632, 4, 16, 16, 2, 8), (1, 5632, 2048, 4, 16, 16, 1, 8), (24, 2048, 5632, 4, 16, 16, 1, 8)])
+def test_blocks_of_few_rows(M, N, K, bits, rows, cols, in_flight, waves):
+    assert plan.forward(M, N, K, bits).kernel == plan.FEW
+    assert plan.few(M, N, K, bits) == (rows, cols, in_flight, waves)
+
+
+def test_few_rows_cases_have_every_block():
+    import test_gpu_few_rows as few
+    shapes = few.SHAPES + [shape for test in (few.test_integer_grids_many_blocks, few.test_integer_grids_many_blocks_of_few_units)
+                           for mark in test.pytestmark if mark.args[0] == "M,N,K" for shape in mark.args[1]]
+    every = {(16, 16, 1, 8), (16, 16, 2, 8), (16, 32, 2, 4), (32, 32, 2, 4), (64, 32, 1, 8), (64, 32, 1, 4), (64, 32, 2, 4),
+             (64, 64, 1, 4)}
+    for bits in (1, 2, 3, 4):
+        assert {tuple(plan.few(M, N, K, bits)) for M, N, K in shapes if plan.forward(M, N, K, bits).kernel == plan.FEW} == every
+    fp4 = [s for s in few.SHAPES if s[2] % 128 == 0] + [(30, 96, 640)] + few.FP4_MANY
+    assert {tuple(plan.few(M, N, K, 0)) for M, N, K in fp4 if plan.forward(M, N, K, 0).kernel == plan.FEW} == \
+        every | {(16, 16, 2, 4)}
+
+
 def test_quantizer_kernels():
     assert plan.quantize(24, 2560, 512, 4, "bf16") == plan.quantize(8192, 2560, 512, 4, "bf16") == plan.ROWS
     assert plan.quantize(24, 2048, 2048, 4, "bf16") == plan.quantize(8192, 2048, 2048, 4, "bf16") == plan.INSTANCE
