@@ -209,3 +209,28 @@ def test_a_row_that_a_workgroup_shares_has_the_same_bytes(cols, n, grid):
             keep = np.arange(rows) != 9
             for name in ("codes", "scales") + (("mask",) if want_mask else ()):
                 assert np.array_equal(part[name][keep].view(np.uint8), whole[name][:rows][keep].view(np.uint8)), (name, rows)
+
+
+# both operands' rows count: 128 are shared by workgroups, 129 are not; the first operand's rows end before, at and after a workgroup's
+@pytest.mark.parametrize("rows_x,rows_w", [(1, 1), (100, 28), (100, 29), (0, 7), (7, 0)])
+@pytest.mark.parametrize("cols,fp4", [(5632, False), (5632, True), (11008, False)])
+def test_pairs_that_workgroups_share_equal_single_calls(rows_x, rows_w, cols, fp4):
+    operands = [torch.randn(r, cols, device=DEV).bfloat16() for r in (rows_x, rows_w)]
+    def buffers(r):
+        return dict(codes=torch.full((r, cols // 2), 0xAA, dtype=torch.uint8, device=DEV),
+                    scales=torch.full((r,), -1.0, device=DEV), mask=torch.full((r, cols // 8), 0x55, dtype=torch.uint8, device=DEV))
+    pair, single = ([buffers(r) for r in (rows_x, rows_w)] for _ in range(2))
+    block = cols & -cols
+    named = {f"{operand}_{k}": v for operand, out in zip("xw", pair) for k, v in out.items()}
+    if fp4:
+        q.quest_hadamard_quantize_fp4_pair(*operands, block, **named)
+    else:
+        q.quest_hadamard_quantize_pair(*operands, block, 4, **named)
+    for t, out in zip(operands, single):
+        if t.shape[0] and fp4:
+            q.quest_hadamard_quantize_fp4(t, block, **out)
+        elif t.shape[0]:
+            q.quest_hadamard_quantize(t, block, 4, **out)
+    torch.cuda.synchronize()
+    for a, b in zip(pair, single):
+        assert all(torch.equal(a[k], b[k]) for k in a)
